@@ -49,7 +49,7 @@ struct Layout {
     int tile;
     int64_t m_pad, n_pad, k_pad;
     int planes, nprod, eplanes;
-    size_t maxA, maxB, sigA, sigB, XA, YB, muA, nuB, barA, barB, resA, resB, ep, prods, total;
+    size_t maxA, maxB, XA, YB, muA, nuB, barA, barB, resA, resB, ep, prods, total;
 };
 
 // real: real operands (one residue plane, one product and one E' plane per modulus)
@@ -70,11 +70,9 @@ Layout make_layout(const ozc_context *h, int64_t m, int64_t n, int64_t k, bool w
         off = align_up(off + bytes);
         return o;
     };
-    // maxA ... YB must stay adjacent and in this order: the scaling phase zeroes them with one fill
+    // XA and YB must stay adjacent: calls with predicted statistics clear them with one fill
     L.maxA = take(8 * (size_t)L.m_pad);
     L.maxB = take(8 * (size_t)L.n_pad);
-    L.sigA = take(8 * (size_t)L.m_pad);
-    L.sigB = take(8 * (size_t)L.n_pad);
     L.XA = take(4 * (size_t)L.m_pad);
     L.YB = take(4 * (size_t)L.n_pad);
     L.muA = take(2 * (size_t)L.m_pad);
@@ -383,9 +381,13 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     h->last.m = m;
     h->last.n = n;
     h->last.k = k;
-    if (!h->keep_status) OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
-    if (m == 0 || n == 0) return OZC_STATUS_SUCCESS;
+    // Calls that compute no product clear the non-finite flag here; the others do it in
+    // their scaling scan.
     const bool alpha_zero = alpha[0] == 0.0 && alpha[1] == 0.0;
+    const bool pre = h->pre.maxA != nullptr && ins == nullptr && !real;
+    if (!h->keep_status && (m == 0 || n == 0 || k == 0 || (alpha_zero && ins == nullptr) || pre))
+        OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
+    if (m == 0 || n == 0) return OZC_STATUS_SUCCESS;
     if ((alpha_zero || k == 0) && ins == nullptr) {
         OZC_TRY(launch_scale_c(C, m, n, ldc, ek, alpha[0], alpha[1], beta[0], beta[1], s));
         return OZC_STATUS_SUCCESS;
@@ -395,14 +397,16 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     const Layout L = make_layout(h, m, n, k, ins && ins->prods, real);
     char *ws = nullptr;
     st = ensure_workspace(h, L.total, &ws);
-    if (st != OZC_STATUS_SUCCESS) return st;
+    if (st != OZC_STATUS_SUCCESS) {  // no scan will clear the flag
+        if (!h->keep_status) OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
+        return st;
+    }
     h->last.workspace = L.total;
     h->last.int8_ops = 2.0 * (double)L.nprod * (double)h->nmod * (double)m * (double)n * (double)k;
 
     const NTable *tab = h->tab_dev + (h->nmod - 1);
     const NTable &th = h->tab_host[(size_t)h->nmod - 1];
     uint64_t *maxA = (uint64_t *)(ws + L.maxA), *maxB = (uint64_t *)(ws + L.maxB);
-    uint64_t *sigA = (uint64_t *)(ws + L.sigA), *sigB = (uint64_t *)(ws + L.sigB);
     int32_t *XA = (int32_t *)(ws + L.XA), *YB = (int32_t *)(ws + L.YB);
     int16_t *muA = (int16_t *)(ws + L.muA), *nuB = (int16_t *)(ws + L.nuB);
     int8_t *resA = (int8_t *)(ws + L.resA), *resB = (int8_t *)(ws + L.resB);
@@ -418,28 +422,24 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     const int fault = h->fault;
     // Step III: scaling exponents
     OZC_TRY(pe.mark(0));
-    // Statistics computed by the moduli-count prediction of this call (same operands,
-    // same k) are taken over; otherwise one fill zeroes maxA, maxB, sigA, sigB, XA, YB
-    // (adjacent in the layout) and the scans run.
-    const bool pre = h->pre.maxA != nullptr && ins == nullptr && !real;
-    const uint64_t *cmaxA = pre ? h->pre.maxA : maxA, *cmaxB = pre ? h->pre.maxB : maxB;
-    const uint64_t *csigA = pre ? h->pre.sigA : sigA, *csigB = pre ? h->pre.sigB : sigB;
-    if (pre) {
-        OZC_TRY(launch_fill_u64((uint64_t *)XA, (int64_t)(L.muA - L.XA) / 8, 0, s));
-    } else {
-        OZC_TRY(launch_fill_u64(maxA, (int64_t)(L.muA - L.maxA) / 8, 0, s));
-        OZC_TRY(launch_pair_scans(vA, vB, ek, maxA, maxB, sigA, sigB, false, s));
-    }
+    // Statistics computed by the moduli-count prediction of this call (same operands, same
+    // k) are taken over; otherwise one scan reads both operands.  Partial results of rows
+    // scanned in several parts go where the residues will be written.
+    uint32_t *clear = h->keep_status ? nullptr : status;
     int abits;
     if (h->mode == OZC_MODE_FAST) {
-        if (!pre) {
-            OZC_TRY(launch_pair_scans(vA, vB, ek, maxA, maxB, sigA, sigB, true, s));
-        }
-        OZC_TRY(launch_pair_fast_exponents(cmaxA, csigA, m, L.m_pad, muA, cmaxB, csigB, n, L.n_pad,
-                                           nuB, tab, status, s));
+        if (pre)
+            OZC_TRY(launch_pair_fast_exponents(h->pre.maxA, h->pre.sigA, m, L.m_pad, muA, h->pre.maxB,
+                                               h->pre.sigB, n, L.n_pad, nuB, tab, status, s));
+        else
+            OZC_TRY(launch_row_exponents(vA, vB, ek, L.m_pad, L.n_pad, muA, nuB, resA, resB, tab, clear, s));
         abits = th.max_abits_fast;
     } else {
         int8_t *barA = (int8_t *)(ws + L.barA), *barB = (int8_t *)(ws + L.barB);
+        const uint64_t *cmaxA = pre ? h->pre.maxA : maxA, *cmaxB = pre ? h->pre.maxB : maxB;
+        if (pre) OZC_TRY(launch_fill_u64((uint64_t *)XA, (int64_t)(L.muA - L.XA) / 8, 0, s));
+        else
+            OZC_TRY(launch_row_maxima(vA, vB, ek, L.m_pad, L.n_pad, maxA, maxB, XA, YB, resA, resB, clear, s));
         OZC_TRY(launch_ceil7(vA, ek, cmaxA, barA, L.m_pad, L.k_pad, s));
         OZC_TRY(launch_ceil7(vB, ek, cmaxB, barB, L.n_pad, L.k_pad, s));
         BoundArgs ba{barA, barB, L.m_pad, L.n_pad, L.k_pad, XA, YB, L.tile, real ? 1 : 0};
@@ -453,8 +453,8 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
 
     // Steps IV, V-i/ii: truncation and residues
     OZC_TRY(pe.mark(1));
-    OZC_TRY(launch_split(vA, ek, muA, tab, h->nmod, L.planes, abits, resA, L.m_pad, L.k_pad, s));
-    OZC_TRY(launch_split(vB, ek, nuB, tab, h->nmod, L.planes, abits, resB, L.n_pad, L.k_pad, s));
+    OZC_TRY(launch_pair_split(vA, vB, ek, muA, nuB, tab, h->nmod, L.planes, abits, resA, L.m_pad, resB,
+                              L.n_pad, L.k_pad, status, s));
 
     // Step V-iii/iv: INT8 products and their residues
     OZC_TRY(pe.mark(2));

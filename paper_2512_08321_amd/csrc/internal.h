@@ -83,24 +83,29 @@ __host__ __device__ constexpr bool elem_real(int ek) { return ek >= kElemD; }
 
 // Kernel launchers (all asynchronous on `stream`).
 hipError_t launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s);
-hipError_t launch_row_maxabs(const OperandView &v, int ek, uint64_t *maxbits, hipStream_t s);
-// Both operands of one call in one launch: row maxima (sigma = false) or sums of
-// squares (sigma = true, maxima final, sigA and sigB zeroed), with tauA, tauB and
-// zeros (all or none, zeroed; zeros shared) also the predictor's statistics; the same
-// results as launch_row_maxabs / launch_row_sigma on each operand.
-hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, int ek, uint64_t *maxA,
-                             uint64_t *maxB, uint64_t *sigA, uint64_t *sigB, bool sigma,
-                             hipStream_t s, uint64_t *tauA = nullptr, uint64_t *tauB = nullptr,
-                             uint64_t *zeros = nullptr);
-// sigma must be zeroed.  With tau and zeros (both or neither, zeroed): also the
-// predictor's statistics tau_r = sum ceil(|x| 2^(20 - e_r)) and the zero-real count.
-hipError_t launch_row_sigma(const OperandView &v, int ek, const uint64_t *maxbits,
-                            uint64_t *sigma, hipStream_t s, uint64_t *tau = nullptr,
-                            uint64_t *zeros = nullptr);
-hipError_t launch_fast_exponents(const uint64_t *maxbits, const uint64_t *sigma, int64_t rows,
-                                 int64_t rows_pad, const NTable *tab, int16_t *mu,
-                                 uint32_t *status, hipStream_t s);
-// launch_fast_exponents for op(A) (m rows) and op(B) (n columns) in one launch
+// Fast-mode exponents of the rows of op(A) (mu, m_pad entries) and the columns of op(B)
+// (nu, n_pad), one read of each operand.  scratchA and scratchB: free memory for rows
+// scanned in several parts, at least row_scan_scratch(rows_pad, k) bytes each.  status (or
+// null): cleared (the residue split sets it for rows holding inf or NaN).
+hipError_t launch_row_exponents(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
+                                int64_t n_pad, int16_t *mu, int16_t *nu, void *scratchA,
+                                void *scratchB, const NTable *tab, uint32_t *status, hipStream_t s);
+// The same scan for accurate mode: row maxima, and the bound maxima X, Y cleared.
+hipError_t launch_row_maxima(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
+                             int64_t n_pad, uint64_t *maxA, uint64_t *maxB, int32_t *X, int32_t *Y,
+                             void *scratchA, void *scratchB, uint32_t *status, hipStream_t s);
+// Parts have at least 1024 k-elements and take 16 bytes per padded row.
+inline int64_t row_scan_scratch(int64_t rows_pad, int64_t k) {
+    return 16 * rows_pad * ((k + 1023) / 1024);
+}
+// The predictor's scans of both operands of one call in one launch: row maxima (no sums
+// given), or, maxima final and the sums zeroed, sigma = sum ceil(|x| 2^(20 - e_r))^2,
+// tau = sum ceil(|x| 2^(20 - e_r)) and the zero-real count (zeros is shared).
+hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, bool single,
+                             uint64_t *maxA, uint64_t *maxB, hipStream_t s, uint64_t *sigA = nullptr,
+                             uint64_t *sigB = nullptr, uint64_t *tauA = nullptr,
+                             uint64_t *tauB = nullptr, uint64_t *zeros = nullptr);
+// Exponents of op(A) (m rows) and op(B) (n columns) from their maxima and integer sums
 hipError_t launch_pair_fast_exponents(const uint64_t *maxA, const uint64_t *sigA, int64_t m,
                                       int64_t m_pad, int16_t *mu, const uint64_t *maxB,
                                       const uint64_t *sigB, int64_t n, int64_t n_pad, int16_t *nu,
@@ -111,11 +116,13 @@ hipError_t launch_ceil7(const OperandView &v, int ek, const uint64_t *maxbits,
 hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int64_t rows,
                                  int64_t rows_pad, const NTable *tab, int16_t *mu,
                                  uint32_t *status, hipStream_t s);
-// abits bounds the bit length of |a'| (at most 32 * kMaxSplitWords - 1).  nplanes: 3 (Karatsuba:
-// R, I, reduced R + I) or 2 (R, I) for complex operands, 1 (R) for real ones.
-hipError_t launch_split(const OperandView &v, int ek, const int16_t *mu, const NTable *tab,
-                        int nmod, int nplanes, int abits, int8_t *dst, int64_t rows_pad,
-                        int64_t k_pad, hipStream_t s);
+// Residues of both operands.  abits bounds the bit length of |a'| (at most
+// 32 * kMaxSplitWords - 1).  nplanes: 3 (Karatsuba: R, I, reduced R + I) or 2 (R, I) for
+// complex operands, 1 (R) for real ones.
+hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int ek, const int16_t *mu,
+                             const int16_t *nu, const NTable *tab, int nmod, int nplanes, int abits,
+                             int8_t *resA, int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad,
+                             uint32_t *status, hipStream_t s);
 
 struct GemmArgs {
     const int8_t *A;      // [N][planes][k_pad/64][m_pad][64] (slab-major planes)

@@ -7,6 +7,8 @@
 // are contiguous (contig_h) and rows that are contiguous with each other
 // (consecutive rows adjacent, stride_r == 1).  Every kernel has a variant for
 // each so that global loads stay coalesced.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace ozc {
@@ -213,6 +215,39 @@ __device__ __forceinline__ void sigma_strided_body(const OperandView &v, const u
 // exact integer form).  Accurate mode: mu_r = (5 - e_r) + t with t the largest
 // integer such that 2 X_r 4^t <= P - 1, X_r the row maximum of the bound product.
 
+// Smallest d with s <= fast_thr[d] (at most kThr - 1).  fast_thr[d] = floor(X 4^d) for one
+// X, so its bit length is that of fast_thr[0] plus 2 d: the bit length of s leaves one
+// entry to compare with.  (Entries clamped to 2^64 - 1 are met by every s.)
+__device__ __forceinline__ int fast_index(uint64_t s, const OZC_AS_CONST NTable *ct) {
+    const int b0 = 64 - __clzll((long long)ct->fast_thr[0]), bs = 64 - __clzll((long long)s);
+    const int d = bs > b0 ? (bs - b0 + 1) >> 1 : 0;
+    if (d >= kThr - 1) return kThr - 1;
+    return bs == b0 + 2 * d && ct->fast_thr[d] < s ? d + 1 : d;
+}
+
+// The exponent of a fast-mode row from its maximum (bit pattern mb, finite, nonzero) and
+// the FP64 sum S of its squares alone, where these decide it.  sigma enters the rule only
+// through the index above, a step function with steps of a factor 4, and with
+// y = |x| 2^(F - e) and n reals in the row
+//   S 2^(2F - 2e) <= sigma < sum (y + 1)^2 <= S' + 2 sqrt(n S') + n,  S' = S 2^(2F - 2e)
+// (Cauchy-Schwarz; the rounding of S, at most n 2^-53 <= 2^-35 relative, is covered by
+// factors 1 -+ 2^-30).  When both ends have the same index, it is sigma's.  They differ
+// for about one row in 10^3..10^4 (S' >= 2^40, so the interval is 4e-4 wide at k = 16384),
+// and for exponents so large or small that the squares may leave the FP64 range: then
+// the exact integer sum is needed (returns false).
+__device__ __forceinline__ bool exponent_from_squares(uint64_t mb, double S, double n,
+                                                      const OZC_AS_CONST NTable *ct, int &mu) {
+    const int e = ilogb_bits(mb);
+    if (e < -450 || e > 450) return false;
+    const double Sp = __builtin_ldexp(S, 2 * (kSigmaFracBits - e));
+    const double hi = Sp * (1.0 + 0x1p-30);
+    const double up = (hi + 2.0 * __builtin_sqrt(n * hi) + n) * (1.0 + 0x1p-30) + 1.0;
+    const int dl = fast_index((uint64_t)(Sp * (1.0 - 0x1p-30)), ct);
+    const int du = fast_index((uint64_t)up, ct);
+    mu = ct->fast_tmax - dl - e;
+    return dl == du;
+}
+
 __device__ __forceinline__ void fast_exponents_body(const uint64_t *maxbits, const uint64_t *sigma,
                                                     int64_t rows, int64_t rows_pad,
                                                     const NTable *tab, int16_t *mu,
@@ -226,11 +261,8 @@ __device__ __forceinline__ void fast_exponents_body(const uint64_t *maxbits, con
             out = kExpNonfinite;
             atomicOr(status, 1u);
         } else if (mb != 0) {
-            const uint64_t s = sigma[r];
-            int d = 0;
             const OZC_AS_CONST NTable *ct = const_ptr(tab);
-            while (d < kThr - 1 && ct->fast_thr[d] < s) ++d;
-            out = (int16_t)(ct->fast_tmax - d - ilogb_bits(mb));
+            out = (int16_t)(ct->fast_tmax - fast_index(sigma[r], ct) - ilogb_bits(mb));
         }
     }
     mu[r] = out;
@@ -264,6 +296,158 @@ __global__ __launch_bounds__(256) void accu_exponents_kernel(const uint64_t *max
                                                              int64_t rows_pad, const NTable *tab,
                                                              int16_t *mu, uint32_t *status) {
     accu_exponents_body(maxbits, X, rows, rows_pad, tab, mu, status, blockIdx.x);
+}
+
+// ---------------------------------------------------------------- one-read scaling scan
+// Maximum and FP64 sum of squares of every row in ONE read of the operand, and the
+// exponents from them (exponent_from_squares); the integer sums are formed only for the
+// rows that need them.  The maxima-then-integer-sums scans read every operand twice.
+// Bound by HBM: 16 rows x `chunk` k-elements per block of 1024 threads, eight loads in
+// flight per thread.  Rows with contiguous k take a wave each; rows contiguous with each
+// other take 16 rows (256-byte runs of complex128) x 64 k per load.
+// With one part per row (chunk >= k) the block finishes its rows, exponents included: one
+// launch, no atomics and nothing to clear.  With several parts they go to part_max and
+// part_sq ([part][row]) and scan_finish_kernel combines them.
+// Accurate mode takes the maxima only, and clears the rows' bound-product maxima X.
+// Whole calls against the two-read scans with their fill and exponent launches: ZGEMM 64^3
+// 46.1 -> 29.0 us (9 launches -> 4, one split launch among them), 384 x 320 x 40000
+// 1237 -> 1111 us, CGEMM 4096^3 at N = 6 1481 -> 1402 us, ZGEMM 4096^3 3305 -> 3204 us.
+constexpr int kScanRows = 16, kScanThreads = 1024, kScanLanes = kScanThreads / kScanRows;
+constexpr int kScanUnroll = 8;
+
+struct RowScan {
+    OperandView v;
+    int64_t rows_pad, chunk;
+    int32_t parts, groups;   // parts per row, groups of kScanRows rows (rows_pad / 16)
+    uint64_t *part_max;      // parts > 1: [parts][rows_pad]
+    double *part_sq;
+    int16_t *mu;             // fast mode: exponents
+    uint64_t *maxbits;       // accurate mode: row maxima ...
+    int32_t *X;              // ... and bound maxima to clear
+};
+
+// sigma of one row by `lanes` threads (thread `lane` of them): the partial sum.
+template <int EK>
+__device__ __forceinline__ uint64_t exact_sigma_part(const OperandView &v, int64_t r, uint64_t mb,
+                                                     int lane, int lanes) {
+    const int sh = kSigmaFracBits - ilogb_bits(mb);
+    uint64_t s = 0;
+    for (int64_t h = lane; h < v.k; h += lanes) {
+        double re, im;
+        load_elem<EK>(v.base, r * v.stride_r + h * v.stride_h, re, im);
+        const uint64_t a = ceil_scaled(re, sh), b = ceil_scaled(im, sh);
+        s += a * a + b * b;
+    }
+    return s;
+}
+
+// Exponents (or, accurate mode, maxima) of the block's kScanRows rows from r0 on: m and q
+// hold row r0 + tid's maximum and sum of squares in threads tid < kScanRows.  All threads
+// of the block call this (it synchronises).
+template <int EK, bool ACCU>
+__device__ __forceinline__ void scan_finish(const RowScan &a, int64_t r0, uint64_t m, double q,
+                                            const NTable *tab) {
+    __shared__ uint64_t need[kScanRows];
+    __shared__ unsigned long long exact[kScanRows];
+    const int tid = threadIdx.x;
+    const int64_t row = r0 + tid;
+    const bool mine = tid < kScanRows && row < a.rows_pad;
+    if constexpr (ACCU) {
+        if (mine && row < a.v.rows) {
+            a.maxbits[row] = m;
+            a.X[row] = 0;
+        }
+        return;
+    }
+    const OZC_AS_CONST NTable *ct = const_ptr(tab);
+    int mu = kExpZero;
+    bool open = false;
+    if (mine && row < a.v.rows) {
+        if (m >= kInfBits) mu = kExpNonfinite;
+        else if (m != 0)
+            open = !exponent_from_squares(m, q, (double)(elem_real(EK) ? a.v.k : 2 * a.v.k), ct, mu);
+    }
+    if (tid < kScanRows) {
+        need[tid] = open ? m : 0;
+        exact[tid] = 0;
+    }
+    if (__syncthreads_or(open)) {
+        for (int i = 0; i < kScanRows; ++i) {
+            if (need[i] == 0) continue;
+            uint64_t s = exact_sigma_part<EK>(a.v, r0 + i, need[i], tid, blockDim.x);
+            s = wave_sum_u64(s);
+            if ((tid & 63) == 0) atomicAdd(&exact[i], (unsigned long long)s);
+        }
+        __syncthreads();
+        if (open) mu = ct->fast_tmax - fast_index(exact[tid], ct) - ilogb_bits(m);
+    }
+    if (mine) a.mu[row] = (int16_t)mu;
+}
+
+template <int EK, bool ACCU>
+__device__ __forceinline__ void row_scan_body(const RowScan &a, int group, int part, const NTable *tab) {
+    __shared__ uint64_t lm[kScanThreads / 64][kScanRows];
+    __shared__ double lq[kScanThreads / 64][kScanRows];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r0 = (int64_t)group * kScanRows;
+    const bool contig = a.v.contig_h != 0;
+    const int64_t r = r0 + (contig ? wave : lane % kScanRows);
+    const int hl = contig ? lane : tid / kScanRows;
+    const int64_t h0 = part * a.chunk, h1 = min(a.v.k, h0 + a.chunk);
+    uint64_t m = 0;
+    double q = 0.0;
+    if (r < a.v.rows && h0 < h1) {
+        const int64_t base = r * a.v.stride_r;
+        for (int64_t h = h0 + hl; h < h1; h += kScanLanes * kScanUnroll) {
+            double re[kScanUnroll], im[kScanUnroll];
+            // clamped addresses: the loads are unconditional, so all of them are in flight
+#pragma unroll
+            for (int u = 0; u < kScanUnroll; ++u)
+                load_elem<EK>(a.v.base, base + min(h + u * kScanLanes, h1 - 1) * a.v.stride_h, re[u], im[u]);
+#pragma unroll
+            for (int u = 0; u < kScanUnroll; ++u) {
+                const bool in = h + u * kScanLanes < h1;  // past the end: the last element again
+                m = max(m, max(abs_bits(re[u]), abs_bits(im[u])));
+                if constexpr (!ACCU) {
+                    const double x = in ? re[u] : 0.0, y = in ? im[u] : 0.0;
+                    q = fma(x, x, q);
+                    if constexpr (!elem_real(EK)) q = fma(y, y, q);
+                }
+            }
+        }
+    }
+    // rows contiguous with each other: the lanes of a row are 16 apart
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        if (!contig && off < kScanRows) break;
+        m = max(m, __shfl_xor(m, off, 64));
+        if constexpr (!ACCU) q += __shfl_xor(q, off, 64);
+    }
+    if (contig) {
+        if (lane == 0) {
+            lm[0][wave] = m;
+            if constexpr (!ACCU) lq[0][wave] = q;
+        }
+    } else if (lane < kScanRows) {
+        lm[wave][lane] = m;
+        if constexpr (!ACCU) lq[wave][lane] = q;
+    }
+    __syncthreads();
+    if (tid < kScanRows) {
+        m = lm[0][tid];
+        if constexpr (!ACCU) q = lq[0][tid];
+        if (!contig) {
+            for (int w = 1; w < kScanThreads / 64; ++w) {
+                m = max(m, lm[w][tid]);
+                if constexpr (!ACCU) q += lq[w][tid];
+            }
+        }
+        if (a.parts > 1 && r0 + tid < a.rows_pad) {
+            a.part_max[part * a.rows_pad + r0 + tid] = m;
+            if constexpr (!ACCU) a.part_sq[part * a.rows_pad + r0 + tid] = q;
+        }
+    }
+    if (a.parts == 1) scan_finish<EK, ACCU>(a, r0, m, q, tab);
 }
 
 // ---------------------------------------------------------------- accurate-mode magnitudes
@@ -409,11 +593,12 @@ __device__ __forceinline__ float smod_u8(float xs, float p, float ip, float rbia
     return __builtin_fmaf(-__builtin_floorf(__builtin_fmaf(xs, ip, rbias)), p, xs);
 }
 
-template <int EK, bool CONTIG_H, int NPLANES, int W>
+// status (may be null): bit 0 is set when a row holds inf or NaN.
+template <int EK, int NPLANES, int W>
 __device__ __forceinline__ void split_body(const OperandView &v, const int16_t *__restrict__ mu,
                                            const NTable *__restrict__ tab, int nmod,
                                            int8_t *__restrict__ dst, int64_t rows_pad,
-                                           int64_t k_pad, int64_t bx, int64_t by) {
+                                           int64_t k_pad, int64_t bx, int64_t by, uint32_t *status) {
     const int tid = threadIdx.x;
     constexpr int TPR = kTileH / kEPT;  // threads per row
     const int rl = tid / TPR;
@@ -427,6 +612,7 @@ __device__ __forceinline__ void split_body(const OperandView &v, const int16_t *
     if (r >= v.rows) return;
     const int ex = global_ptr(mu)[r];
     const bool live = ex != kExpZero && ex != kExpNonfinite;
+    if (status && ex == kExpNonfinite && h0 == 0) atomicOr(status, 1u);
     int8_t *out = dst + (bx * rows_pad + r) * kTileH + kEPT * oc;
     if (!live || h0 >= v.k) {  // k padding, or a row without scaling: every residue is 0
         const int z[kEPT] = {};
@@ -479,28 +665,54 @@ __device__ __forceinline__ void split_body(const OperandView &v, const int16_t *
 
 // ---------------------------------------------------------------- kernels (one problem)
 
-template <int EK>
-__global__ __launch_bounds__(256) void row_maxabs_contig(OperandView v, uint64_t *maxbits) {
-    maxabs_contig_body<EK>(v, maxbits, blockIdx.x, blockIdx.y);
+// Both operands of one call in one launch, the blocks of A first.
+template <int EK, bool ACCU>
+__global__ __launch_bounds__(kScanThreads) void pair_row_scan_kernel(RowScan a, RowScan b,
+                                                                     const NTable *tab,
+                                                                     uint32_t *status) {
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = 0;  // set again by the split
+    const int nA = a.groups * a.parts;
+    int blk = (int)blockIdx.x;
+    const bool second = blk >= nA;
+    if (second) blk -= nA;
+    const RowScan &w = second ? b : a;
+    row_scan_body<EK, ACCU>(w, blk % w.groups, blk / w.groups, tab);
 }
-template <int EK>
-__global__ __launch_bounds__(256) void row_maxabs_strided(OperandView v, uint64_t *maxbits, int hc) {
-    maxabs_strided_body<EK>(v, maxbits, blockIdx.x, blockIdx.y, hc);
+
+// Rows scanned in several parts: 16 rows per block, 16 threads per row over the parts.
+// (a side with one part has no blocks here)
+template <int EK, bool ACCU>
+__global__ __launch_bounds__(256) void scan_finish_kernel(RowScan a, RowScan b, int blocksA,
+                                                          const NTable *tab) {
+    __shared__ uint64_t lm[16][kScanRows];
+    __shared__ double lq[16][kScanRows];
+    int blk = (int)blockIdx.x;
+    const bool second = blk >= blocksA;
+    if (second) blk -= blocksA;
+    const RowScan &w = second ? b : a;
+    const int tid = threadIdx.x, rl = tid % kScanRows, pl = tid / kScanRows;
+    const int64_t r0 = (int64_t)blk * kScanRows;
+    uint64_t m = 0;
+    double q = 0.0;
+    if (r0 + rl < w.v.rows) {
+        for (int p = pl; p < w.parts; p += 16) {
+            m = max(m, w.part_max[p * w.rows_pad + r0 + rl]);
+            if constexpr (!ACCU) q += w.part_sq[p * w.rows_pad + r0 + rl];
+        }
+    }
+    lm[pl][rl] = m;
+    lq[pl][rl] = q;
+    __syncthreads();
+    if (tid < kScanRows) {
+        for (int p = 1; p < 16; ++p) {
+            m = max(m, lm[p][tid]);
+            q += lq[p][tid];
+        }
+    }
+    scan_finish<EK, ACCU>(w, r0, m, q, tab);
 }
-template <int EK, bool STATS>
-__global__ __launch_bounds__(256) void row_sigma_contig(OperandView v, const uint64_t *maxbits,
-                                                        uint64_t *sigma, uint64_t *tau,
-                                                        uint64_t *zeros) {
-    sigma_contig_body<EK, STATS>(v, maxbits, sigma, tau, zeros, blockIdx.x, blockIdx.y);
-}
-template <int EK, bool STATS>
-__global__ __launch_bounds__(256) void row_sigma_strided(OperandView v, const uint64_t *maxbits,
-                                                         uint64_t *sigma, uint64_t *tau,
-                                                         uint64_t *zeros, int hc) {
-    sigma_strided_body<EK, STATS>(v, maxbits, sigma, tau, zeros, blockIdx.x, blockIdx.y, hc);
-}
-// The scans of both operands of one call in one launch, blocks of A first, then those
-// of B, each on the grid its own launch would have: one ramp-up and tail per pass
+// The predictor's scans (maxima, then integer sums with its statistics) of both operands
+// of one call in one launch per pass, blocks of A first, then those of B, each on the grid its own launch would have: one ramp-up and tail per pass
 // instead of two, which shows where an operand takes tens of microseconds.  The
 // maxima and the integer sums of squares are combined by atomics, so the result does
 // not depend on the order of the blocks.
@@ -530,12 +742,6 @@ __global__ __launch_bounds__(256) void pair_scan_kernel(ScanSide a, ScanSide b) 
     if (blk < a.blocks) scan_side<EK, PASS>(a, blk);
     else scan_side<EK, PASS>(b, blk - a.blocks);
 }
-__global__ __launch_bounds__(256) void fast_exponents_kernel(const uint64_t *maxbits,
-                                                             const uint64_t *sigma, int64_t rows,
-                                                             int64_t rows_pad, const NTable *tab,
-                                                             int16_t *mu, uint32_t *status) {
-    fast_exponents_body(maxbits, sigma, rows, rows_pad, tab, mu, status, blockIdx.x);
-}
 // The exponents of both operands of one call in one launch (the blocks of A first).
 struct ExpSide {
     const uint64_t *maxbits, *sigma;
@@ -548,13 +754,25 @@ __global__ __launch_bounds__(256) void pair_fast_exponents_kernel(ExpSide a, Exp
     if (blk < a.blocks) fast_exponents_body(a.maxbits, a.sigma, a.rows, a.rows_pad, tab, a.mu, status, blk);
     else fast_exponents_body(b.maxbits, b.sigma, b.rows, b.rows_pad, tab, b.mu, status, blk - a.blocks);
 }
-template <int EK, bool CONTIG_H, int NPLANES, int W>
-__global__ __launch_bounds__(256) void split_kernel(OperandView v, const int16_t *__restrict__ mu,
-                                                    const NTable *__restrict__ tab, int nmod,
-                                                    int8_t *__restrict__ dst, int64_t rows_pad,
-                                                    int64_t k_pad) {
-    split_body<EK, CONTIG_H, NPLANES, W>(v, mu, tab, nmod, dst, rows_pad, k_pad, blockIdx.x,
-                                             blockIdx.y);
+// The residues of both operands of one call in one launch (the blocks of A first).
+struct SplitSide {
+    OperandView v;
+    const int16_t *mu;
+    int8_t *dst;
+    int64_t rows_pad;
+    uint32_t blocks;  // (k_pad / 64) x (rows_pad / kDirectRows)
+};
+template <int EK, int NPLANES, int W>
+__global__ __launch_bounds__(256) void pair_split_kernel(SplitSide a, SplitSide b,
+                                                         const NTable *__restrict__ tab, int nmod,
+                                                         int64_t k_pad, uint32_t *status) {
+    uint32_t blk = blockIdx.x;
+    const bool second = blk >= a.blocks;
+    if (second) blk -= a.blocks;
+    const SplitSide &w = second ? b : a;
+    const uint32_t gx = (uint32_t)(k_pad / kTileH);
+    split_body<EK, NPLANES, W>(w.v, w.mu, tab, nmod, w.dst, w.rows_pad, k_pad, blk % gx, blk / gx,
+                               status);
 }
 
 template <int EK, bool CONTIG_H>
@@ -642,12 +860,8 @@ __global__ __launch_bounds__(256) void batch_split_kernel(const BatchOperand *op
     const BatchOperand &op = ops[o];
     const int64_t lb = b - op.blk_split, gx = op.k_pad / kTileH;
     const int64_t bx = lb % gx, by = lb / gx;
-    if (op.v.contig_h)
-        split_body<EK, true, NPLANES, W>(op.v, op.mu, op.tab, op.nmod, op.res, op.rows_pad,
-                                             op.k_pad, bx, by);
-    else
-        split_body<EK, false, NPLANES, W>(op.v, op.mu, op.tab, op.nmod, op.res, op.rows_pad,
-                                              op.k_pad, bx, by);
+    split_body<EK, NPLANES, W>(op.v, op.mu, op.tab, op.nmod, op.res, op.rows_pad, op.k_pad, bx, by,
+                               nullptr);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v) {
@@ -674,14 +888,14 @@ hipError_t batch_split_w(const BatchOperand *ops, int nops, int64_t blocks, int 
     return hipGetLastError();
 }
 
-template <int EK, bool CONTIG_H, int NPLANES>
-hipError_t split_w(const OperandView &v, const int16_t *mu, const NTable *tab, int nmod, int nw,
-                    int8_t *dst, int64_t rows_pad, int64_t k_pad, hipStream_t s) {
-    dim3 grid((unsigned)(k_pad / kTileH), (unsigned)(rows_pad / kDirectRows));
+template <int EK, int NPLANES>
+hipError_t pair_split_w(const SplitSide &a, const SplitSide &b, const NTable *tab, int nmod, int nw,
+                        int64_t k_pad, uint32_t *status, hipStream_t s) {
+    dim3 grid(a.blocks + b.blocks);
 #define OZC_SPLIT_CASE(W)                                                                    \
     case W:                                                                                  \
-        hipLaunchKernelGGL((split_kernel<EK, CONTIG_H, NPLANES, W>), grid, dim3(256), 0,  \
-                           s, v, mu, tab, nmod, dst, rows_pad, k_pad);                       \
+        hipLaunchKernelGGL((pair_split_kernel<EK, NPLANES, W>), grid, dim3(256), 0, s, a, b, \
+                           tab, nmod, k_pad, status);                                        \
         break;
     switch (nw) {
         OZC_W_CASES(OZC_SPLIT_CASE)
@@ -711,66 +925,6 @@ static int strided_chunk(const OperandView &v) {
     return hc;
 }
 
-template <int EK>
-hipError_t row_maxabs_ek(const OperandView &v, uint64_t *maxbits, hipStream_t s) {
-    if (v.contig_h) {
-        dim3 grid((unsigned)((v.rows + 3) / 4), (unsigned)((v.k + kHChunk - 1) / kHChunk));
-        hipLaunchKernelGGL(row_maxabs_contig<EK>, grid, dim3(256), 0, s, v, maxbits);
-    } else {
-        const int hc = strided_chunk(v);
-        dim3 grid((unsigned)((v.rows + 255) / 256), (unsigned)((v.k + hc - 1) / hc));
-        hipLaunchKernelGGL(row_maxabs_strided<EK>, grid, dim3(256), 0, s, v, maxbits, hc);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_row_maxabs(const OperandView &v, int ek, uint64_t *maxbits, hipStream_t s) {
-    if (v.rows <= 0 || v.k <= 0) return hipSuccess;
-    switch (ek) {
-        case kElemZ: return row_maxabs_ek<kElemZ>(v, maxbits, s);
-        case kElemC: return row_maxabs_ek<kElemC>(v, maxbits, s);
-        case kElemD: return row_maxabs_ek<kElemD>(v, maxbits, s);
-        case kElemS: return row_maxabs_ek<kElemS>(v, maxbits, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-template <int EK, bool STATS>
-hipError_t row_sigma_ek(const OperandView &v, const uint64_t *maxbits, uint64_t *sigma,
-                        uint64_t *tau, uint64_t *zeros, hipStream_t s) {
-    if (v.contig_h) {
-        dim3 grid((unsigned)((v.rows + 3) / 4), (unsigned)((v.k + kHChunk - 1) / kHChunk));
-        hipLaunchKernelGGL((row_sigma_contig<EK, STATS>), grid, dim3(256), 0, s, v, maxbits, sigma,
-                           tau, zeros);
-    } else {
-        const int hc = strided_chunk(v);
-        dim3 grid((unsigned)((v.rows + 255) / 256), (unsigned)((v.k + hc - 1) / hc));
-        hipLaunchKernelGGL((row_sigma_strided<EK, STATS>), grid, dim3(256), 0, s, v, maxbits, sigma,
-                           tau, zeros, hc);
-    }
-    return hipGetLastError();
-}
-
-template <bool STATS>
-hipError_t row_sigma_stats(const OperandView &v, int ek, const uint64_t *maxbits, uint64_t *sigma,
-                           uint64_t *tau, uint64_t *zeros, hipStream_t s) {
-    switch (ek) {
-        case kElemZ: return row_sigma_ek<kElemZ, STATS>(v, maxbits, sigma, tau, zeros, s);
-        case kElemC: return row_sigma_ek<kElemC, STATS>(v, maxbits, sigma, tau, zeros, s);
-        case kElemD: return row_sigma_ek<kElemD, STATS>(v, maxbits, sigma, tau, zeros, s);
-        case kElemS: return row_sigma_ek<kElemS, STATS>(v, maxbits, sigma, tau, zeros, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_row_sigma(const OperandView &v, int ek, const uint64_t *maxbits,
-                            uint64_t *sigma, hipStream_t s, uint64_t *tau, uint64_t *zeros) {
-    if (v.rows <= 0 || v.k <= 0) return hipSuccess;
-    if ((tau == nullptr) != (zeros == nullptr)) return hipErrorInvalidValue;
-    if (tau) return row_sigma_stats<true>(v, ek, maxbits, sigma, tau, zeros, s);
-    return row_sigma_stats<false>(v, ek, maxbits, sigma, nullptr, nullptr, s);
-}
-
 static ScanSide scan_side_of(const OperandView &v, uint64_t *maxbits, uint64_t *sigma,
                              uint64_t *tau, uint64_t *zeros) {
     ScanSide sd{v, maxbits, sigma, tau, zeros, 0, 0, 0};
@@ -793,27 +947,93 @@ hipError_t pair_scans_ek(const ScanSide &a, const ScanSide &b, int pass, hipStre
     if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks);
     if (pass == 2) hipLaunchKernelGGL((pair_scan_kernel<EK, 2>), grid, dim3(256), 0, s, a, b);
-    else if (pass == 1) hipLaunchKernelGGL((pair_scan_kernel<EK, 1>), grid, dim3(256), 0, s, a, b);
     else hipLaunchKernelGGL((pair_scan_kernel<EK, 0>), grid, dim3(256), 0, s, a, b);
     return hipGetLastError();
 }
 
-hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, int ek, uint64_t *maxA,
-                             uint64_t *maxB, uint64_t *sigA, uint64_t *sigB, bool sigma,
-                             hipStream_t s, uint64_t *tauA, uint64_t *tauB, uint64_t *zeros) {
+hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, bool single,
+                             uint64_t *maxA, uint64_t *maxB, hipStream_t s, uint64_t *sigA,
+                             uint64_t *sigB, uint64_t *tauA, uint64_t *tauB, uint64_t *zeros) {
     const bool stats = tauA != nullptr;
-    if (stats != (tauB != nullptr) || stats != (zeros != nullptr) || (stats && !sigma))
+    if (stats != (tauB != nullptr) || stats != (zeros != nullptr) || stats != (sigA != nullptr) ||
+        stats != (sigB != nullptr))
         return hipErrorInvalidValue;
     const ScanSide a = scan_side_of(va, maxA, sigA, tauA, zeros);
     const ScanSide b = scan_side_of(vb, maxB, sigB, tauB, zeros);
-    const int pass = stats ? 2 : (sigma ? 1 : 0);
+    return single ? pair_scans_ek<kElemC>(a, b, stats ? 2 : 0, s)
+                  : pair_scans_ek<kElemZ>(a, b, stats ? 2 : 0, s);
+}
+
+// Parts of a row: one while a thread's share of it is at most 64 loads or both operands'
+// row groups give every CU a block of 1024 threads (one launch does the whole phase then);
+// otherwise parts of at least 2048 k that bring the grid to about 1024 blocks.
+static RowScan row_scan_of(const OperandView &v, int64_t rows_pad, int64_t groups_all, void *scratch) {
+    RowScan w{};
+    w.v = v;
+    w.rows_pad = rows_pad;
+    w.groups = (int32_t)(rows_pad / kScanRows);
+    int64_t parts = 1;
+    if (v.k > 64 * kScanLanes && groups_all < 512)
+        parts = std::max<int64_t>(1, std::min((v.k + 2047) / 2048, (1023 + groups_all) / groups_all));
+    w.chunk = (v.k + parts - 1) / parts;
+    w.parts = (int32_t)parts;
+    w.part_max = (uint64_t *)scratch;
+    w.part_sq = (double *)(w.part_max + parts * rows_pad);
+    return w;
+}
+
+template <int EK>
+static hipError_t row_scans_ek(const RowScan &a, const RowScan &b, bool accurate, const NTable *tab,
+                               uint32_t *status, hipStream_t s) {
+    const int64_t blocks = (int64_t)a.groups * a.parts + (int64_t)b.groups * b.parts;
+    const int fa = a.parts > 1 ? a.groups : 0, fb = b.parts > 1 ? b.groups : 0;
+    if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)blocks), block(kScanThreads);
+    if (accurate) hipLaunchKernelGGL((pair_row_scan_kernel<EK, true>), grid, block, 0, s, a, b, tab, status);
+    else hipLaunchKernelGGL((pair_row_scan_kernel<EK, false>), grid, block, 0, s, a, b, tab, status);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || fa + fb == 0) return e;
+    const dim3 fgrid((unsigned)(fa + fb));
+    if (accurate) hipLaunchKernelGGL((scan_finish_kernel<EK, true>), fgrid, dim3(256), 0, s, a, b, fa, tab);
+    else hipLaunchKernelGGL((scan_finish_kernel<EK, false>), fgrid, dim3(256), 0, s, a, b, fa, tab);
+    return hipGetLastError();
+}
+
+static hipError_t row_scans(RowScan &a, RowScan &b, int ek, bool accurate, const NTable *tab,
+                            uint32_t *status, hipStream_t s) {
     switch (ek) {
-        case kElemZ: return pair_scans_ek<kElemZ>(a, b, pass, s);
-        case kElemC: return pair_scans_ek<kElemC>(a, b, pass, s);
-        case kElemD: return pair_scans_ek<kElemD>(a, b, pass, s);
-        case kElemS: return pair_scans_ek<kElemS>(a, b, pass, s);
+        case kElemZ: return row_scans_ek<kElemZ>(a, b, accurate, tab, status, s);
+        case kElemC: return row_scans_ek<kElemC>(a, b, accurate, tab, status, s);
+        case kElemD: return row_scans_ek<kElemD>(a, b, accurate, tab, status, s);
+        case kElemS: return row_scans_ek<kElemS>(a, b, accurate, tab, status, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_row_exponents(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
+                                int64_t n_pad, int16_t *mu, int16_t *nu, void *scratchA,
+                                void *scratchB, const NTable *tab, uint32_t *status, hipStream_t s) {
+    if (va.rows <= 0 || vb.rows <= 0 || va.k <= 0 || m_pad % kScanRows || n_pad % kScanRows)
+        return hipErrorInvalidValue;
+    const int64_t groups = (m_pad + n_pad) / kScanRows;
+    RowScan a = row_scan_of(va, m_pad, groups, scratchA), b = row_scan_of(vb, n_pad, groups, scratchB);
+    a.mu = mu;
+    b.mu = nu;
+    return row_scans(a, b, ek, false, tab, status, s);
+}
+
+hipError_t launch_row_maxima(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
+                             int64_t n_pad, uint64_t *maxA, uint64_t *maxB, int32_t *X, int32_t *Y,
+                             void *scratchA, void *scratchB, uint32_t *status, hipStream_t s) {
+    if (va.rows <= 0 || vb.rows <= 0 || va.k <= 0 || m_pad % kScanRows || n_pad % kScanRows)
+        return hipErrorInvalidValue;
+    const int64_t groups = (m_pad + n_pad) / kScanRows;
+    RowScan a = row_scan_of(va, m_pad, groups, scratchA), b = row_scan_of(vb, n_pad, groups, scratchB);
+    a.maxbits = maxA;
+    b.maxbits = maxB;
+    a.X = X;
+    b.X = Y;
+    return row_scans(a, b, ek, true, nullptr, status, s);
 }
 
 hipError_t launch_pair_fast_exponents(const uint64_t *maxA, const uint64_t *sigA, int64_t m,
@@ -830,15 +1050,6 @@ hipError_t launch_pair_fast_exponents(const uint64_t *maxA, const uint64_t *sigA
     return hipGetLastError();
 }
 
-hipError_t launch_fast_exponents(const uint64_t *maxbits, const uint64_t *sigma, int64_t rows,
-                                 int64_t rows_pad, const NTable *tab, int16_t *mu,
-                                 uint32_t *status, hipStream_t s) {
-    if (rows_pad <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fast_exponents_kernel, dim3((unsigned)((rows_pad + 255) / 256)), dim3(256),
-                       0, s, maxbits, sigma, rows, rows_pad, tab, mu, status);
-    return hipGetLastError();
-}
-
 hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int64_t rows,
                                  int64_t rows_pad, const NTable *tab, int16_t *mu,
                                  uint32_t *status, hipStream_t s) {
@@ -848,31 +1059,25 @@ hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int6
     return hipGetLastError();
 }
 
-hipError_t launch_split(const OperandView &v, int ek, const int16_t *mu, const NTable *tab,
-                        int nmod, int nplanes, int abits, int8_t *dst, int64_t rows_pad,
-                        int64_t k_pad, hipStream_t s) {
+hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int ek, const int16_t *mu,
+                             const int16_t *nu, const NTable *tab, int nmod, int nplanes, int abits,
+                             int8_t *resA, int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad,
+                             uint32_t *status, hipStream_t s) {
     if (abits > kMaxSplitBits) return hipErrorInvalidValue;
     const int nw = split_words(abits);
-    if (rows_pad % kDirectRows || k_pad % kTileH) return hipErrorInvalidValue;
+    if (m_pad % kDirectRows || n_pad % kDirectRows || k_pad % kTileH) return hipErrorInvalidValue;
     if ((nplanes == 1) != elem_real(ek)) return hipErrorInvalidValue;
-#define OZC_SPLIT_ARGS v, mu, tab, nmod, nw, dst, rows_pad, k_pad, s
-#define OZC_SPLIT_EK(EKV)                                                                  \
-    if (v.contig_h) return nplanes == 3 ? split_w<EKV, true, 3>(OZC_SPLIT_ARGS)            \
-                                        : split_w<EKV, true, 2>(OZC_SPLIT_ARGS);           \
-    return nplanes == 3 ? split_w<EKV, false, 3>(OZC_SPLIT_ARGS)                           \
-                        : split_w<EKV, false, 2>(OZC_SPLIT_ARGS);
+    const int64_t blkA = batch_split_blocks(m_pad, k_pad), blkB = batch_split_blocks(n_pad, k_pad);
+    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
+    const SplitSide a{va, mu, resA, m_pad, (uint32_t)blkA}, b{vb, nu, resB, n_pad, (uint32_t)blkB};
+#define OZC_SPLIT_ARGS a, b, tab, nmod, nw, k_pad, status, s
     switch (ek) {
-        case kElemZ: OZC_SPLIT_EK(kElemZ)
-        case kElemC: OZC_SPLIT_EK(kElemC)
-        case kElemD:
-            return v.contig_h ? split_w<kElemD, true, 1>(OZC_SPLIT_ARGS)
-                              : split_w<kElemD, false, 1>(OZC_SPLIT_ARGS);
-        case kElemS:
-            return v.contig_h ? split_w<kElemS, true, 1>(OZC_SPLIT_ARGS)
-                              : split_w<kElemS, false, 1>(OZC_SPLIT_ARGS);
+        case kElemZ: return nplanes == 3 ? pair_split_w<kElemZ, 3>(OZC_SPLIT_ARGS) : pair_split_w<kElemZ, 2>(OZC_SPLIT_ARGS);
+        case kElemC: return nplanes == 3 ? pair_split_w<kElemC, 3>(OZC_SPLIT_ARGS) : pair_split_w<kElemC, 2>(OZC_SPLIT_ARGS);
+        case kElemD: return pair_split_w<kElemD, 1>(OZC_SPLIT_ARGS);
+        case kElemS: return pair_split_w<kElemS, 1>(OZC_SPLIT_ARGS);
         default: return hipErrorInvalidValue;
     }
-#undef OZC_SPLIT_EK
 #undef OZC_SPLIT_ARGS
 }
 
