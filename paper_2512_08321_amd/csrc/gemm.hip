@@ -64,24 +64,51 @@ struct Plan {
     }
 };
 
-// Symmetric residue of an INT32 accumulator, or of an accumulator plus or minus a
-// residue, in FP64: q = rint(x (1/p)) is the nearest integer to x / p (|x| < 2^31, so
-// the rounded product is off by less than 2^-22, and x / p lies at least 1/(2p) from a
-// half-integer unless p = 256, where 1/p is exact), and x - q p is exact.  For p = 256
-// a tie gives +128 instead of -128: the same byte.  The argument stays in INT32: an
-// accumulator is bounded by k 127^2 (odd p; k <= 2^17) and the residues added to it
-// (at most three times 127) keep it below 2^31 - p; for p = 256 the wrap-around modulo
-// 2^32 leaves the residue unchanged.
-// Five FP64 instructions, against two quarter-rate integer multiplies and fix-ups for
-// a Barrett reduction (2.5% faster batches, 1.5% at 4096^3).
-__device__ __forceinline__ int reduce_fp(int x, double pd, double ipd) {
-    const double xd = (double)x;
-    return (int)fma(-rint(xd * ipd), pd, xd);
+// s + 128 of the symmetric residue s of an INT32 value x, an accumulator or an accumulator
+// plus or minus residues, given as v = x + 2^31 modulo 2^32 (accumulators start at 2^31).
+// As in the residue split, one byte dot product gives x' = sum_j v_j (2^(8 j) mod p) + 128 -
+// (2^31 mod p), congruent to x + 128 and below 2^20 in magnitude, and the rest is exact in
+// FP32: s + 128 = x' - p floor(fl(x' fl(1/p) + 0.5 - 128 fl(1/p))).  x stays in INT32: an
+// accumulator is bounded by k 127^2 (odd p; k <= 2^17) and the residues added to it (at
+// most three times 127) keep it below 2^31 - p; for p = 256 the wrap-around modulo 2^32
+// leaves the byte unchanged.
+// Six instructions per output with the packing of four residues into a word; the epilogue
+// is bound by them where k is short.  The rule before, rint(x (1/p)) in FP64, took five FP64
+// ones and two more to pack, and E' went out in 4-byte stores; products then and now, same
+// box: ZGEMM 4096^3 at N = 14 2505 -> 2377 us, 4096 x 4096 x 128 435 -> 301 us, DGEMM 1536 x
+// 2048 x 1000 75 -> 57 us, SGEMM 3000 x 3000 x 700 at N = 8 102 -> 70 us.
+struct ModRule {
+    uint32_t wb, bias;
+    float p, ip, rb;
+};
+constexpr int kAccBias = (int)0x80000000;
+__device__ __forceinline__ ModRule mod_rule(const NTable *tab, int l) {
+    const OZC_AS_CONST ModConst &mc = const_ptr(tab)->mod[l];
+    return ModRule{mc.wbyte[0], mc.wbias[0], mc.pf, mc.ipf, mc.rbias};
+}
+template <int U>
+__device__ __forceinline__ uint32_t put_residue(uint32_t v, const ModRule &r, uint32_t w) {
+    const float x = (float)(int32_t)__builtin_amdgcn_udot4(v, r.wb, r.bias, false);
+    const float s = __builtin_fmaf(-__builtin_floorf(__builtin_fmaf(x, r.ip, r.rb)), r.p, x);
+    return __builtin_amdgcn_cvt_pk_u8_f32(s, U, w);
 }
 
-__device__ __forceinline__ uint32_t pack4(const int (&v)[4]) {
-    return (uint32_t)(v[0] & 0xff) | ((uint32_t)(v[1] & 0xff) << 8) |
-           ((uint32_t)(v[2] & 0xff) << 16) | ((uint32_t)(v[3] & 0xff) << 24);
+// A lane of a 32 x 32 block holds one column: rows 8 g + 4 (lane / 32) + 0..3 in word g.
+// v_permlane32_swap exchanges words with lane +- 32 so that each lane has 16 consecutive
+// rows, 16 (lane / 32) + 0..15, and E' moves in 16-byte accesses; it is its own inverse.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x4 rows16(const uint32_t (&w)[4]) {
+    const auto e = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto f = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    return u32x4{e[0], e[1], f[0], f[1]};
+}
+__device__ __forceinline__ void rows4(const u32x4 &r, uint32_t (&w)[4]) {
+    const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[1], false, false);
+    const auto f = __builtin_amdgcn_permlane32_swap(r[2], r[3], false, false);
+    w[0] = e[0];
+    w[2] = e[1];
+    w[1] = f[0];
+    w[3] = f[1];
 }
 
 __device__ __forceinline__ int byte_of(uint32_t w, int u) { return (int)(int8_t)(w >> (8 * u)); }
@@ -106,19 +133,22 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-__device__ __forceinline__ void map_tile(int64_t L, int64_t TR, int64_t TC, int64_t total, int &l,
+__device__ __forceinline__ void map_tile(uint32_t L, uint32_t TR, uint32_t TC, uint32_t total, int &l,
                                          int64_t &ti, int64_t &tj) {
-    int64_t q = L;
-    if ((total & 7) == 0) q = (L & 7) * (total >> 3) + (L >> 3);  // XCD x -> contiguous part x
-    const int64_t T = TR * TC;
-    l = (int)(q / T);
-    const int64_t t = q - (int64_t)l * T;
-    constexpr int64_t G = 4;
-    const int64_t grp = t / (G * TC);
-    const int64_t rem = t - grp * (G * TC);
-    const int64_t rows = min(G, TR - grp * G);
-    ti = grp * G + rem % rows;
-    tj = rem / rows;
+    // XCD x (blocks x, x + 8, ...) -> contiguous part x of total / 8 tiles, one more in the
+    // first total % 8 parts.  Block counts are below 2^31: 32-bit divisions.
+    const uint32_t x = L & 7, rem8 = total & 7;
+    const uint32_t q = x * (total >> 3) + min(x, rem8) + (L >> 3);
+    const uint32_t T = TR * TC, mod = q / T;
+    l = (int)mod;
+    const uint32_t t = q - mod * T;
+    constexpr uint32_t G = 4;
+    const uint32_t grp = t / (G * TC);
+    const uint32_t rem = t - grp * (G * TC);
+    const uint32_t rows = min(G, TR - grp * G);
+    const uint32_t col = rem / rows;
+    ti = grp * G + (rem - col * rows);
+    tj = col;
 }
 
 // WM x WN waves of BM x BN blocks; KS 64-byte k sub-slabs per pipeline stage.
@@ -209,9 +239,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
 
     const int nk = (int)(k_pad / C::KSTEP);
 
-    ModConst mc;
-    if constexpr (!bound) mc = a.tab->mod[l];
-    const double pd = bound ? 1.0 : (double)mc.p, ipd = 1.0 / pd;
+    ModRule rule{};
+    if constexpr (!bound) rule = mod_rule(a.tab, l);
+    constexpr int bias = bound || DUMP ? 0 : kAccBias;  // accumulators' start
     const int64_t planeC = bound ? 0 : a.n_pad * a.m_pad;
 
     // Each wave fills whole 1 KB chunks (16 rows) of the A and B slabs: lane i of a
@@ -263,7 +293,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
 #pragma unroll 1
     for (int sgi = 0; sgi < P::nseg; ++sgi) {
         if (!bound || sgi == 0) {
-            static_for<BM>([&](auto bi) { static_for<BN>([&](auto bj) { acc[bi][bj] = v16i{}; }); });
+            static_for<BM>([&](auto bi) { static_for<BN>([&](auto bj) { acc[bi][bj] = (v16i)bias; }); });
         }
         // Fragments of one 32-wide half (kk) of a 64-wide k-slab held in LDS buffer Lbuf.
         auto read_frags = [&](const uint4 *Lbuf, int kk, v4i (&fa)[BM], v4i (&fb)[BN]) {
@@ -373,23 +403,26 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
         constexpr bool karatsuba = KIND == KIND_KARATSUBA;
         // the E'_R registers fit beside small tiles' accumulators only
         constexpr bool keep_er = karatsuba && C::REG_CARRY && C::BM * C::BN <= 4;
-        auto eword = [&](int8_t *E, int bi, int bj, int g) {
-            const int64_t i = i0 + wm * WTM + bi * 32 + 8 * g + 4 * (lane >> 5);
+        auto e16 = [&](int8_t *E, int bi, int bj) {
+            const int64_t i = i0 + wm * WTM + bi * 32 + 16 * (lane >> 5);
             const int64_t j = j0 + wn * WTN + bj * 32 + (lane & 31);
-            return reinterpret_cast<uint32_t *>(E + j * a.m_pad + i);
+            return reinterpret_cast<u32x4 *>(E + j * a.m_pad + i);
+        };
+        // four residues per word of value(0..15), the lane's accumulator-order rows
+        auto residues = [&](auto value, uint32_t (&w)[4]) {
+            static_for<4>([&](auto g) {
+                w[g] = 0;
+                static_for<4>([&](auto u) {
+                    w[g] = put_residue<u>((uint32_t)value(4 * (int)g + u) ^ (DUMP ? (uint32_t)kAccBias : 0u),
+                                          rule, w[g]);
+                });
+                w[g] ^= 0x80808080u;
+            });
         };
         int8_t *ER = nullptr, *EI = nullptr;
         if constexpr (!bound) {
             ER = a.eprime + (int64_t)l * P::eplanes * planeC;
             EI = ER + planeC;  // not used by real products
-            if (C::PREFETCH && !C::REG_CARRY && sgi >= 1 && (karatsuba || sgi != 2)) {
-                static_for<BM>([&](auto bi) {
-                    static_for<BN>([&](auto bj) {
-                        static_for<4>([&](auto g) { cw[bi][bj][g] = *eword(EI, bi, bj, g); });
-                    });
-                });
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the carries are in registers
-            }
         }
         if constexpr (C::PREFETCH) {
             if (sgi + 1 < P::nseg) issue_first(sgi + 1);
@@ -433,11 +466,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             // E' = mod(A'_l B'_l): one reduction per output (Algorithm 1 Step V-iv)
             static_for<BM>([&](auto bi) {
                 static_for<BN>([&](auto bj) {
-                    static_for<4>([&](auto g) {
-                        int o[4];
-                        static_for<4>([&](auto u) { o[u] = reduce_fp(acc[bi][bj][4 * (int)g + u], pd, ipd); });
-                        *eword(ER, bi, bj, g) = pack4(o);
-                    });
+                    uint32_t o[4];
+                    residues([&](int r) { return acc[bi][bj][r]; }, o);
+                    *e16(ER, bi, bj) = rows16(o);
                 });
             });
         } else {
@@ -447,54 +478,45 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
                 // above it (they might alias), so word-by-word read-back waited for a memory
                 // round trip per word.  Reading all BM rows before any store was no faster
                 // overall (fewer E' write-backs, but more operand misses in L2).
-                if (!C::PREFETCH && !C::REG_CARRY && sgi >= 1 && (karatsuba || sgi != 2)) {
-                    static_for<BN>([&](auto bj) {
-                        static_for<4>([&](auto g) { cw[bi][bj][g] = *eword(EI, bi, bj, g); });
-                    });
+                if (!C::REG_CARRY && sgi >= 1 && (karatsuba || sgi != 2)) {
+                    u32x4 back[BN];
+                    static_for<BN>([&](auto bj) { back[bj] = *e16(EI, bi, bj); });
+                    static_for<BN>([&](auto bj) { rows4(back[bj], cw[bi][bj]); });
                 }
                 static_for<BN>([&](auto bj) {
-                    static_for<4>([&](auto g) {
-                        uint32_t *er = eword(ER, bi, bj, g);
-                        uint32_t *ei = eword(EI, bi, bj, g);
-                        // The first product of a pair is reduced and carried; the second
-                        // enters the reduction unreduced (accumulator +- carried residue
-                        // stays in range, see reduce_fp): 4 reductions per output and
-                        // modulus in both forms, 3 for Karatsuba with keep_er.
-                        int o[4];
-                        auto acc_u = [&](int u) { return acc[bi][bj][4 * (int)g + u]; };
-                        if (sgi == 0 || (!karatsuba && sgi == 2)) {
-                            static_for<4>([&](auto u) { o[u] = reduce_fp(acc_u(u), pd, ipd); });
-                            if constexpr (C::REG_CARRY) cw[bi][bj][g] = pack4(o);
-                            else *ei = pack4(o);
-                        } else if (sgi == 1) {
-                            // Karatsuba: E'_R = mod(D - E), carry mod(D + E); expanded: E'_R = mod(RR - II)
-                            const uint32_t w = cw[bi][bj][g];
-                            static_for<4>([&](auto u) { o[u] = reduce_fp(byte_of(w, u) - acc_u(u), pd, ipd); });
-                            *er = pack4(o);
-                            if constexpr (keep_er) {
-                                cr[bi][bj][g] = pack4(o);
-                            } else if constexpr (karatsuba) {
-                                static_for<4>([&](auto u) { o[u] = reduce_fp(byte_of(w, u) + acc_u(u), pd, ipd); });
-                                if constexpr (C::REG_CARRY) cw[bi][bj][g] = pack4(o);
-                                else *ei = pack4(o);
-                            }
-                        } else if constexpr (keep_er) {
-                            // E'_I = mod(F - D - E) = mod(F - 2 mod(D) + E'_R), since
-                            // D + E = 2 D - (D - E): one reduction fewer than carrying mod(D + E)
-                            const uint32_t w = cw[bi][bj][g], r = cr[bi][bj][g];
-                            static_for<4>([&](auto u) {
-                                o[u] = reduce_fp(acc_u(u) - 2 * byte_of(w, u) + byte_of(r, u), pd, ipd);
-                            });
-                            *ei = pack4(o);
-                        } else {
-                            // Karatsuba: E'_I = mod(F - mod(D + E)); expanded: E'_I = mod(RI + IR)
-                            const uint32_t w = cw[bi][bj][g];
-                            static_for<4>([&](auto u) {
-                                o[u] = reduce_fp(karatsuba ? acc_u(u) - byte_of(w, u) : byte_of(w, u) + acc_u(u), pd, ipd);
-                            });
-                            *ei = pack4(o);
+                    u32x4 *er = e16(ER, bi, bj), *ei = e16(EI, bi, bj);
+                    // The first product of a pair is reduced and carried; the second
+                    // enters the reduction unreduced (accumulator +- carried residue
+                    // stays in range, see put_residue): 4 reductions per output and
+                    // modulus in both forms, 3 for Karatsuba with keep_er.
+                    uint32_t o[4];
+                    auto x = [&](int r) { return acc[bi][bj][r]; };
+                    auto d = [&](int r) { return byte_of(cw[bi][bj][r >> 2], r & 3); };
+                    if (sgi == 0 || (!karatsuba && sgi == 2)) {
+                        residues(x, o);
+                        if constexpr (C::REG_CARRY) static_for<4>([&](auto g) { cw[bi][bj][g] = o[g]; });
+                        else *ei = rows16(o);
+                    } else if (sgi == 1) {
+                        // Karatsuba: E'_R = mod(D - E), carry mod(D + E); expanded: E'_R = mod(RR - II)
+                        residues([&](int r) { return d(r) - x(r); }, o);
+                        *er = rows16(o);
+                        if constexpr (keep_er) {
+                            static_for<4>([&](auto g) { cr[bi][bj][g] = o[g]; });
+                        } else if constexpr (karatsuba) {
+                            residues([&](int r) { return d(r) + x(r); }, o);
+                            if constexpr (C::REG_CARRY) static_for<4>([&](auto g) { cw[bi][bj][g] = o[g]; });
+                            else *ei = rows16(o);
                         }
-                    });
+                    } else if constexpr (keep_er) {
+                        // E'_I = mod(F - D - E) = mod(F - 2 mod(D) + E'_R), since
+                        // D + E = 2 D - (D - E): one reduction fewer than carrying mod(D + E)
+                        residues([&](int r) { return x(r) - 2 * d(r) + byte_of(cr[bi][bj][r >> 2], r & 3); }, o);
+                        *ei = rows16(o);
+                    } else {
+                        // Karatsuba: E'_I = mod(F - mod(D + E)); expanded: E'_I = mod(RI + IR)
+                        residues([&](int r) { return karatsuba ? x(r) - d(r) : d(r) + x(r); }, o);
+                        *ei = rows16(o);
+                    }
                 });
             });
         }
@@ -504,11 +526,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
 template <int KIND, typename C, bool DUMP>
 __global__ __launch_bounds__(C::THREADS) void residue_gemm_kernel(GemmArgs a, BoundArgs b) {
     constexpr bool bound = Plan<KIND>::bound;
-    const int64_t TR = (bound ? b.m_pad : a.m_pad) / C::TM, TC = (bound ? b.n_pad : a.n_pad) / C::TN;
-    const int nmod = bound ? 1 : a.nmod;
+    const uint32_t TR = (uint32_t)((bound ? b.m_pad : a.m_pad) / C::TM);
+    const uint32_t TC = (uint32_t)((bound ? b.n_pad : a.n_pad) / C::TN);
+    const uint32_t nmod = bound ? 1 : a.nmod;
     int l;
     int64_t ti, tj;
-    map_tile((int64_t)blockIdx.x, TR, TC, (int64_t)nmod * TR * TC, l, ti, tj);
+    map_tile(blockIdx.x, TR, TC, nmod * TR * TC, l, ti, tj);
     gemm_tile<KIND, C, DUMP>(a, b, l, ti, tj);
 }
 
