@@ -287,7 +287,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
 
     v16i acc[BM][BN];
     uint32_t cw[BM][BN][4];  // packed carry residues (kept here, or reloaded from E'_I)
-    uint32_t cr[BM][BN][4];  // Karatsuba, carry in registers, small tiles: E'_R, kept for E'_I
     if constexpr (C::PREFETCH) issue_first(0);
 
 #pragma unroll 1
@@ -396,13 +395,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
         // Karatsuba, mod(RR) and mod(RI) for the expanded form) stays in registers, or
         // is parked in this thread's own E'_I words, which receive the final E'_I last
         // (each lane re-reads only what it wrote, so no synchronisation is needed).
-        // With the carry in registers and small tiles, Karatsuba keeps mod(D) and E'_R
-        // instead of mod(D + E): three reductions per output rather than four.
         // Parked carries are loaded and awaited first; then the next product's first
         // stages are queued, so that their copies overlap the rest of this epilogue.
         constexpr bool karatsuba = KIND == KIND_KARATSUBA;
-        // the E'_R registers fit beside small tiles' accumulators only
-        constexpr bool keep_er = karatsuba && C::REG_CARRY && C::BM * C::BN <= 4;
         auto e16 = [&](int8_t *E, int bi, int bj) {
             const int64_t i = i0 + wm * WTM + bi * 32 + 16 * (lane >> 5);
             const int64_t j = j0 + wn * WTN + bj * 32 + (lane & 31);
@@ -488,7 +483,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
                     // The first product of a pair is reduced and carried; the second
                     // enters the reduction unreduced (accumulator +- carried residue
                     // stays in range, see put_residue): 4 reductions per output and
-                    // modulus in both forms, 3 for Karatsuba with keep_er.
+                    // modulus in both forms.
                     uint32_t o[4];
                     auto x = [&](int r) { return acc[bi][bj][r]; };
                     auto d = [&](int r) { return byte_of(cw[bi][bj][r >> 2], r & 3); };
@@ -500,18 +495,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
                         // Karatsuba: E'_R = mod(D - E), carry mod(D + E); expanded: E'_R = mod(RR - II)
                         residues([&](int r) { return d(r) - x(r); }, o);
                         *er = rows16(o);
-                        if constexpr (keep_er) {
-                            static_for<4>([&](auto g) { cr[bi][bj][g] = o[g]; });
-                        } else if constexpr (karatsuba) {
+                        if constexpr (karatsuba) {
                             residues([&](int r) { return d(r) + x(r); }, o);
                             if constexpr (C::REG_CARRY) static_for<4>([&](auto g) { cw[bi][bj][g] = o[g]; });
                             else *ei = rows16(o);
                         }
-                    } else if constexpr (keep_er) {
-                        // E'_I = mod(F - D - E) = mod(F - 2 mod(D) + E'_R), since
-                        // D + E = 2 D - (D - E): one reduction fewer than carrying mod(D + E)
-                        residues([&](int r) { return x(r) - 2 * d(r) + byte_of(cr[bi][bj][r >> 2], r & 3); }, o);
-                        *ei = rows16(o);
                     } else {
                         // Karatsuba: E'_I = mod(F - mod(D + E)); expanded: E'_I = mod(RI + IR)
                         residues([&](int r) { return karatsuba ? x(r) - d(r) : d(r) + x(r); }, o);
@@ -521,6 +509,191 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             });
         }
     }
+}
+
+// ---------------------------------------------------------------- products held to the end
+// Waves of 64 x 64 outputs that hold every product of the plan in INT32 accumulators of
+// its own until the end (192 registers for complex products), so the ring of LDS buffers
+// runs through the products without a break and each output is reduced twice (once per
+// part) instead of three or four times with residues carried in between:
+//   Karatsuba: E'_R = mod(D - E), E'_I = mod(F - D - E)
+//   expanded:  E'_R = mod(RR - II), E'_I = mod(RI + IR) (one accumulator for RI + IR)
+// |F - D - E| <= 3 k 127^2 stays below 2^31 for kOnceChunk k-elements (p = 256 may wrap:
+// harmless modulo 2^32); longer k runs in chunks, the accumulators replaced by their
+// symmetric residues in between.
+// The first accumulator starts at the bias 2^31 that put_residue expects: it carries over
+// to both results (X - Y and Z - X - Y modulo 2^32).
+// Against the 128 x 128 tiles with carried residues, same box, products: ZGEMM 64^3 10.8 ->
+// 8.5 us, 256^3 expanded 15.5 -> 12.4 us, 1000 x 900 x 1100 70 -> 65 us.  On 256 x 256-tile
+// shapes it loses from k = 1024 on (2048^3 at N = 13: 390 against 354 us, 4096^3 3200 against
+// 2377 us): a 64 x 64 wave reads a third more LDS per matrix instruction and a 128 x 128
+// block copies twice the bytes into it.
+constexpr int kOnceChunk = 32768 / BK;  // k-slabs
+template <int WM_, int WN_, int NSTAGE_, int NACC_>
+struct OnceCfg {
+    static constexpr int WM = WM_, WN = WN_, BM = 2, BN = 2, NSTAGE = NSTAGE_, NACC = NACC_;
+    static constexpr int TM = WM * 64, TN = WN * 64, THREADS = 64 * WM * WN;
+    static constexpr int STAGE = (TM + TN) * 4;  // uint4 per 64-wide k-slab in LDS
+};
+
+// One output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + slabs - 1, E' to `ep`
+// (the E' planes of all moduli).  Ends with a block barrier.
+template <int KIND, typename C>
+__device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, int64_t ti, int64_t tj,
+                                          int s0, int slabs) {
+    using P = Plan<KIND>;
+    static_assert(!P::bound, "bound products fold maxima, they have no E'");
+    constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN, NSTAGE = C::NSTAGE;
+    constexpr int NACC = C::NACC;
+    static_assert(NACC == (P::real ? 1 : 3), "one accumulator per held product");
+    __shared__ uint4 lds[NSTAGE][C::STAGE];  // [buffer][A rows, B rows]
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wv % C::WM, wn = wv / C::WM;
+    const int64_t i0 = ti * TM, j0 = tj * TN;
+    const int64_t planeA = a.m_pad * a.k_pad, planeB = a.n_pad * a.k_pad;
+    const int64_t slabA = a.m_pad * BK, slabB = a.n_pad * BK;
+    const int8_t *baseA = uniform_ptr(a.A + (int64_t)l * P::nplanes * planeA + i0 * BK + s0 * slabA);
+    const int8_t *baseB = uniform_ptr(a.B + (int64_t)l * P::nplanes * planeB + j0 * BK + s0 * slabB);
+    const ModRule rule = mod_rule(a.tab, l);
+
+    // ring of NSTAGE one-slab buffers, filled AHEAD slabs ahead (see gemm_tile)
+    constexpr int NW = C::WM * C::WN, QA = TM / 16 / NW, QB = TN / 16 / NW, NLOAD = QA + QB;
+    static_assert(TM / 16 % NW == 0 && TN / 16 % NW == 0 && QA <= 4 && QB <= 4, "chunks per wave");
+    static_assert(NSTAGE >= 3, "DMA ring needs at least three buffers");
+    constexpr int AHEAD = NSTAGE - 1, LATER = AHEAD - 2 > 0 ? AHEAD - 2 : 0;
+    const int crow = lane >> 2, cg = (lane & 3) ^ swz_bits(crow);
+    const uint32_t voffA = (uint32_t)(wv * QA * 1024 + crow * BK + cg * 16);
+    const uint32_t voffB = (uint32_t)(wv * QB * 1024 + crow * BK + cg * 16);
+    const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)(&lds[0][0]);
+    v16i acc[NACC][BM][BN];
+    static_for<NACC>([&](auto z) {
+        static_for<BM>([&](auto bi) {
+            static_for<BN>([&](auto bj) { acc[z][bi][bj] = (v16i)(z == 0 ? kAccBias : 0); });
+        });
+    });
+    const uint32_t frow = (uint32_t)(lane & 31), fsw = (uint32_t)swz_bits(lane & 31);
+    auto read_frags = [&](int buf, int kk, v4i (&fa)[BM], v4i (&fb)[BN]) {
+        const uint32_t g = (uint32_t)(kk * 2 + (lane >> 5)) ^ fsw;
+        const uint4 *FA = lds[buf] + (wm * 64 + frow) * 4 + g;
+        const uint4 *FB = lds[buf] + TM * 4 + (wn * 64 + frow) * 4 + g;
+        static_for<2>([&](auto i) {
+            const uint4 t = FB[i * 32 * 4], u = FA[i * 32 * 4];
+            fb[i] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+            fa[i] = v4i{(int)u.x, (int)u.y, (int)u.z, (int)u.w};
+        });
+    };
+    auto interleave = [&]() {  // one LDS read per matrix instruction
+        static_for<BM * BN>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        });
+    };
+    for (int c0 = 0;;) {
+        const int nk = min(slabs - c0, kOnceChunk);
+        const int8_t *sa = baseA, *sb = baseB;  // the next slab to queue
+        int iseg = 0, ist = 0, ibuf = 0;        // its product, slab and buffer
+        auto issue = [&]() {
+            const uint32_t buf = lbase + (uint32_t)(ibuf * C::STAGE * 16);
+            static_for<QA>([&](auto q) { dma16<q * 1024>(sa, voffA, buf + (uint32_t)(wv * QA * 1024)); });
+            static_for<QB>([&](auto q) { dma16<q * 1024>(sb, voffB, buf + (uint32_t)(TM * 64 + wv * QB * 1024)); });
+            ibuf = ibuf + 1 == NSTAGE ? 0 : ibuf + 1;
+            sa += slabA;
+            sb += slabB;
+            if (++ist == nk) {  // first slab of the next product's planes
+                ist = 0;
+                ++iseg;
+                const int pa = KIND == KIND_4M ? iseg & 1 : iseg;
+                const int pb = KIND == KIND_4M ? (iseg ^ (iseg >> 1)) & 1 : iseg;
+                sa = uniform_ptr(baseA + pa * planeA);
+                sb = uniform_ptr(baseB + pb * planeB);
+            }
+        };
+        const int T = P::nseg * nk;
+        static_for<AHEAD>([&](auto t) {
+            if (t < T) issue();
+        });
+
+        v4i fa[2][BM], fb[2][BN];
+        if (T > 2 && AHEAD >= 3) vmcnt_wait<2 * NLOAD>();
+        else if (T > 1) vmcnt_wait<NLOAD>();
+        else vmcnt_wait<0>();
+        block_barrier();
+        read_frags(0, 0, fa[0], fb[0]);
+        int t = 0, cur = 0;
+        static_for<P::nseg>([&](auto seg) {
+            constexpr int z = seg < NACC ? (int)seg : NACC - 1;
+            auto mfmas = [&](const v4i (&xa)[BM], const v4i (&xb)[BN]) {
+                static_for<BM>([&](auto bi) {
+                    static_for<BN>([&](auto bj) {
+                        acc[z][bi][bj] =
+                            __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[bi], xb[bj], acc[z][bi][bj], 0, 0, 0);
+                    });
+                });
+            };
+#pragma unroll 1
+            for (int s = 0; s < nk; ++s, ++t) {
+                read_frags(cur, 1, fa[1], fb[1]);
+                mfmas(fa[0], fb[0]);
+                interleave();
+                // after the last slab of all the wait and the barrier close the ring, and the
+                // fragments read ahead are not used: one path, so that the accumulators of both
+                // halves stay in place
+                if (t + 1 + LATER < T) vmcnt_wait<LATER * NLOAD>();
+                else vmcnt_wait<0>();
+                block_barrier();  // slab t+1 visible; slab t-1's buffer free
+                if (t + AHEAD < T) issue();
+                cur = cur + 1 == NSTAGE ? 0 : cur + 1;
+                read_frags(cur, 0, fa[0], fb[0]);
+                mfmas(fa[1], fb[1]);
+                interleave();
+            }
+        });
+        block_barrier();  // all waves done with the ring before it is refilled
+        c0 += nk;
+        if (c0 >= slabs) break;
+        baseA += nk * slabA;
+        baseB += nk * slabB;
+        static_for<NACC>([&](auto z) {
+            static_for<BM>([&](auto bi) {
+                static_for<BN>([&](auto bj) {
+                    static_for<16>([&](auto r) {
+                        const int v = acc[z][bi][bj][(int)r];
+                        const uint32_t u = put_residue<0>((uint32_t)(z == 0 ? v : v ^ kAccBias), rule, 0u);
+                        acc[z][bi][bj][(int)r] = (int)u - 128 + (z == 0 ? kAccBias : 0);
+                    });
+                });
+            });
+        });
+    }
+
+    const int64_t planeC = a.n_pad * a.m_pad;
+    int8_t *E = ep + (int64_t)l * P::eplanes * planeC + i0 + wm * 64 + 16 * (lane >> 5);
+    auto store = [&](auto bi, auto bj, int plane, auto value) {
+        uint32_t w[4];
+        static_for<4>([&](auto g) {
+            w[g] = 0;
+            static_for<4>([&](auto u) {
+                w[g] = put_residue<u>((uint32_t)value(4 * (int)g + u), rule, w[g]);
+            });
+            w[g] ^= 0x80808080u;
+        });
+        const int64_t j = j0 + wn * 64 + bj * 32 + (lane & 31);
+        *global_ptr(reinterpret_cast<u32x4 *>(E + plane * planeC + j * a.m_pad + bi * 32)) = rows16(w);
+    };
+    static_for<BM>([&](auto bi) {
+        static_for<BN>([&](auto bj) {
+            if constexpr (P::real) {
+                store(bi, bj, 0, [&](int r) { return acc[0][bi][bj][r]; });
+            } else {
+                store(bi, bj, 0, [&](int r) { return acc[0][bi][bj][r] - acc[1][bi][bj][r]; });
+                store(bi, bj, 1, [&](int r) {
+                    if constexpr (KIND == KIND_4M) return acc[2][bi][bj][r] ^ kAccBias;
+                    else return acc[2][bi][bj][r] - acc[0][bi][bj][r] - acc[1][bi][bj][r];
+                });
+            }
+        });
+    });
 }
 
 template <int KIND, typename C, bool DUMP>
@@ -535,12 +708,35 @@ __global__ __launch_bounds__(C::THREADS) void residue_gemm_kernel(GemmArgs a, Bo
     gemm_tile<KIND, C, DUMP>(a, b, l, ti, tj);
 }
 
+template <int KIND, typename C>
+__global__ __launch_bounds__(C::THREADS, 2) void once_gemm_kernel(GemmArgs a) {
+    const uint32_t TR = (uint32_t)(a.m_pad / C::TM), TC = (uint32_t)(a.n_pad / C::TN);
+    int l;
+    int64_t ti, tj;
+    map_tile(blockIdx.x, TR, TC, (uint32_t)a.nmod * TR * TC, l, ti, tj);
+    once_tile<KIND, C>(a, a.eprime, l, ti, tj, 0, (int)(a.k_pad / BK));
+}
+
+// A batch's tile of either class.
+template <int KIND, typename C>
+struct BatchTile {
+    __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
+        gemm_tile<KIND, C, false>(a, BoundArgs{}, l, ti, tj);
+    }
+};
+template <int KIND, int WM, int WN, int NSTAGE, int NACC>
+struct BatchTile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>> {
+    __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
+        once_tile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>>(a, a.eprime, l, ti, tj, 0, (int)(a.k_pad / BK));
+    }
+};
+
 // Persistent kernel over the work queue of a batch: each block takes the next
 // item from the counter until the queue is empty.  Items of one problem are
 // numbered (modulus group, tile row, tile column); problems are ordered by the
 // host (largest k first).
 template <int KIND, typename C>
-__global__ __launch_bounds__(C::THREADS) void batch_gemm_kernel(const BatchGemm *probs, int nprob,
+__global__ __launch_bounds__(C::THREADS, 2) void batch_gemm_kernel(const BatchGemm *probs, int nprob,
                                                                 int64_t items, int group,
                                                                 uint32_t *counters, int64_t chunk) {
     __shared__ int64_t item_s;
@@ -574,24 +770,27 @@ __global__ __launch_bounds__(C::THREADS) void batch_gemm_kernel(const BatchGemm 
         for (;;) {
             if (threadIdx.x == 0) item_s = (int64_t)ahead;
             __syncthreads();
-            const int64_t j = item_s;
+            // item numbers are block-uniform: in a scalar register, so that everything
+            // derived from them (the problem's record, the copies' addresses) is scalar
+            const uint32_t j32 = __builtin_amdgcn_readfirstlane((uint32_t)item_s);
             __syncthreads();
-            if (j >= nq) break;
+            if (j32 >= nq) break;
             if (threadIdx.x == 0) ahead = atomicAdd(&counters[q] + zero, 1u);
-            const uint32_t j32 = (uint32_t)j, jc = j32 / ch;
+            const uint32_t jc = j32 / ch;
             const int64_t w = ((int64_t)jc * kBatchQueues + q) * ch + (j32 - jc * ch);
-            const int64_t f0 = probs[lo].item0;
-            const int64_t f1 = lo + 1 < nprob ? probs[lo + 1].item0 : items;
+            const OZC_AS_CONST BatchGemm *pl = const_ptr(probs);
+            const int64_t f0 = pl[lo].item0;
+            const int64_t f1 = lo + 1 < nprob ? pl[lo + 1].item0 : items;
             if (w < f0 || w >= f1) {  // last problem whose first item is <= w
                 int hi = w < f0 ? lo - 1 : nprob - 1;
                 lo = w < f0 ? 0 : lo + 1;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
-                    if (probs[mid].item0 <= w) lo = mid;
+                    if (pl[mid].item0 <= w) lo = mid;
                     else hi = mid - 1;
                 }
             }
-            const BatchGemm &pb = probs[lo];
+            const OZC_AS_CONST BatchGemm &pb = pl[lo];
             const uint32_t T = (uint32_t)pb.TR * (uint32_t)pb.TC, local = (uint32_t)(w - pb.item0);
             const int lg = (int)(local / T);
             const uint32_t t = local - (uint32_t)lg * T;
@@ -599,7 +798,7 @@ __global__ __launch_bounds__(C::THREADS) void batch_gemm_kernel(const BatchGemm 
             GemmArgs a{pb.A, pb.B, pb.m_pad, pb.n_pad, pb.k_pad, pb.nmod, KIND == KIND_4M ? 1 : 0,
                        pb.tab, pb.eprime, nullptr, C::TM};
             const int l1 = min(pb.nmod, (lg + 1) * group);
-            for (int l = lg * group; l < l1; ++l) gemm_tile<KIND, C, false>(a, BoundArgs{}, l, ti, tj);
+            for (int l = lg * group; l < l1; ++l) BatchTile<KIND, C>::run(a, l, ti, tj);
         }
     }
 }
@@ -651,6 +850,22 @@ void launch_kind(const GemmArgs &a, const BoundArgs &b, bool dump, int64_t block
     else hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, false>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a, b);
 }
 
+// 128 x 128 output tiles, 256 threads, 64 KB LDS: two blocks per CU, two waves per SIMD
+using Once128 = OnceCfg<2, 2, 4, 3>;
+using Once128Real = OnceCfg<2, 2, 4, 1>;
+
+template <int KIND, typename C>
+hipError_t launch_once(const GemmArgs &a, int64_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL((once_gemm_kernel<KIND, C>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int KIND, typename C>
+void launch_dump(const GemmArgs &a, int64_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0,
+                       s, a, BoundArgs{});
+}
+
 }  // namespace
 
 int gemm_tile_for(int64_t m, int64_t n) { return (m >= 1024 && n >= 1024) ? 256 : 128; }
@@ -669,23 +884,25 @@ hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {
     BoundArgs none{};
     const bool dump = a.prods != nullptr;
     if (a.algo < 0 || a.algo > 2) return hipErrorInvalidValue;
-    // one product per modulus: the long-k schedule keeps no carry, so it serves every k
-    if (a.algo == 2) {
-        if (tile == 256) launch_kind<KIND_REAL, CfgLarge>(a, none, dump, blocks, s);
-        else launch_kind<KIND_REAL, CfgSmall>(a, none, dump, blocks, s);
+    if (tile == 128 && !dump) {
+        if (a.algo == 2) return launch_once<KIND_REAL, Once128Real>(a, blocks, s);
+        if (a.algo == 1) return launch_once<KIND_4M, Once128>(a, blocks, s);
+        return launch_once<KIND_KARATSUBA, Once128>(a, blocks, s);
+    }
+    if (tile == 128) {  // with the raw products written out
+        if (a.algo == 2) launch_dump<KIND_REAL, CfgSmall>(a, blocks, s);
+        else if (a.algo == 1) launch_dump<KIND_4M, CfgSmall>(a, blocks, s);
+        else launch_dump<KIND_KARATSUBA, CfgSmall>(a, blocks, s);
         return hipGetLastError();
     }
-    if (tile == 256) {
-        if (a.k_pad >= kLongK) {
-            if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLarge>(a, none, dump, blocks, s);
-            else launch_kind<KIND_4M, CfgLarge>(a, none, dump, blocks, s);
-        } else {
-            if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLargeShortK>(a, none, dump, blocks, s);
-            else launch_kind<KIND_4M, CfgLargeShortK>(a, none, dump, blocks, s);
-        }
+    // one product per modulus: the long-k schedule keeps no carry, so it serves every k
+    if (a.algo == 2) launch_kind<KIND_REAL, CfgLarge>(a, none, dump, blocks, s);
+    else if (a.k_pad >= kLongK) {
+        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLarge>(a, none, dump, blocks, s);
+        else launch_kind<KIND_4M, CfgLarge>(a, none, dump, blocks, s);
     } else {
-        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgSmall>(a, none, dump, blocks, s);
-        else launch_kind<KIND_4M, CfgSmall>(a, none, dump, blocks, s);
+        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLargeShortK>(a, none, dump, blocks, s);
+        else launch_kind<KIND_4M, CfgLargeShortK>(a, none, dump, blocks, s);
     }
     return hipGetLastError();
 }
@@ -697,8 +914,9 @@ hipError_t launch_bound_gemm(const BoundArgs &b, hipStream_t s) {
     if (b.m_pad % tile || b.n_pad % tile || b.k_pad % BK) return hipErrorInvalidValue;
     const int64_t blocks = (b.m_pad / tile) * (b.n_pad / tile);
     GemmArgs none{};
-    if (b.real) launch_kind<KIND_BOUND_REAL, CfgSmall>(none, b, false, blocks, s);
-    else launch_kind<KIND_BOUND, CfgSmall>(none, b, false, blocks, s);
+    const dim3 grid((unsigned)blocks), block(CfgSmall::THREADS);
+    if (b.real) hipLaunchKernelGGL((residue_gemm_kernel<KIND_BOUND_REAL, CfgSmall, false>), grid, block, 0, s, none, b);
+    else hipLaunchKernelGGL((residue_gemm_kernel<KIND_BOUND, CfgSmall, false>), grid, block, 0, s, none, b);
     return hipGetLastError();
 }
 
@@ -721,7 +939,7 @@ hipError_t launch_batch_bound(const BatchBound *probs, int nprob, int64_t items,
 }
 
 int batch_gemm_blocks_per_cu(int tile) {
-    return tile == 256 ? blocks_per_cu<KIND_KARATSUBA, CfgLargeShortK>() : blocks_per_cu<KIND_KARATSUBA, CfgSmall>();
+    return tile == 256 ? blocks_per_cu<KIND_KARATSUBA, CfgLargeShortK>() : blocks_per_cu<KIND_KARATSUBA, Once128>();
 }
 
 hipError_t launch_batch_gemm(const BatchGemm *probs, int nprob, int64_t items, int tile, int group,
@@ -740,8 +958,8 @@ hipError_t launch_batch_gemm(const BatchGemm *probs, int nprob, int64_t items, i
         if (algo == 0) launch_batch_kind<KIND_KARATSUBA, CfgLargeShortK>(probs, nprob, items, group, counters, grid_blocks, s);
         else launch_batch_kind<KIND_4M, CfgLargeShortK>(probs, nprob, items, group, counters, grid_blocks, s);
     } else {
-        if (algo == 0) launch_batch_kind<KIND_KARATSUBA, CfgSmall>(probs, nprob, items, group, counters, grid_blocks, s);
-        else launch_batch_kind<KIND_4M, CfgSmall>(probs, nprob, items, group, counters, grid_blocks, s);
+        if (algo == 0) launch_batch_kind<KIND_KARATSUBA, Once128>(probs, nprob, items, group, counters, grid_blocks, s);
+        else launch_batch_kind<KIND_4M, Once128>(probs, nprob, items, group, counters, grid_blocks, s);
     }
     return hipGetLastError();
 }
