@@ -1,5 +1,6 @@
 // C-ABI of the emulated complex GEMM (include/ozc.h): argument checks,
 // workspace layout and the order of kernel launches on the caller's stream.
+#include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -90,7 +91,23 @@ Layout make_layout(const ozc_context *h, int64_t m, int64_t n, int64_t k, bool w
 }
 
 
-ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, char **ws) {
+// The call's workspace: at least `bytes`, and up to *extra more where they can be had (the
+// handle's own memory grows; a caller's or the fixed workspace may be too small).  *extra
+// receives what there is of them, all or nothing.
+ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t *extra, char **ws) {
+    if (*extra) {
+        const size_t want = bytes + *extra;
+        const size_t have = h->use_fixed ? (size_t)OZC_NOALLOC_WORKSPACE
+                                         : (h->ws_user ? h->ws_user_bytes : SIZE_MAX);
+        if (want > have) *extra = 0;
+        else if (!h->use_fixed && !h->ws_user && want > h->ws_own_bytes) {
+            size_t none = 0;
+            const ozc_status_t st = ensure_workspace(h, want, &none, ws);
+            if (st != OZC_STATUS_ALLOC_FAILED) return st;
+            *extra = 0;  // as much as the call cannot do without
+        }
+    }
+
     if (h->use_fixed) {  // checked against the size before any work was enqueued
         if (!h->ws_fixed || bytes > (size_t)OZC_NOALLOC_WORKSPACE) return OZC_STATUS_NOT_SUPPORTED;
         *ws = (char *)h->ws_fixed;
@@ -396,12 +413,19 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
 
     const Layout L = make_layout(h, m, n, k, ins && ins->prods, real);
     char *ws = nullptr;
-    st = ensure_workspace(h, L.total, &ws);
+    // products cut along k need E' planes beyond the layout; intermediates and double-double
+    // outputs take whole ones
+    const int galgo = real ? 2 : (h->algo == OZC_ALGO_KARATSUBA ? 0 : 1);
+    KSplit ks{h->nmod, 1};
+    if (!ins && !h->dd_lo) ks = choose_k_split(L.tile, galgo, h->nmod, L.m_pad, L.n_pad, L.k_pad, h->cus);
+    size_t extra = (size_t)(h->nmod - ks.l_split) * (ks.parts - 1) * L.eplanes * (size_t)L.m_pad * L.n_pad;
+    st = ensure_workspace(h, L.total, &extra, &ws);
+    if (extra == 0) ks = KSplit{h->nmod, 1};
     if (st != OZC_STATUS_SUCCESS) {  // no scan will clear the flag
         if (!h->keep_status) OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
         return st;
     }
-    h->last.workspace = L.total;
+    h->last.workspace = L.total + extra;
     h->last.int8_ops = 2.0 * (double)L.nprod * (double)h->nmod * (double)m * (double)n * (double)k;
 
     const NTable *tab = h->tab_dev + (h->nmod - 1);
@@ -458,8 +482,9 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
 
     // Step V-iii/iv: INT8 products and their residues
     OZC_TRY(pe.mark(2));
-    const int galgo = real ? 2 : (h->algo == OZC_ALGO_KARATSUBA ? 0 : 1);
-    GemmArgs ga{resA, resB, L.m_pad, L.n_pad, L.k_pad, h->nmod, galgo, tab, ep, prods, L.tile};
+    int8_t *ep_parts = (int8_t *)(ws + L.total);
+    GemmArgs ga{resA, resB, L.m_pad, L.n_pad, L.k_pad, h->nmod, galgo, tab, ep, prods, L.tile,
+                ks.l_split, ks.parts, ep_parts};
     OZC_TRY(launch_residue_gemm(ga, s));
     if (fault == 1 && h->attempt == 0) OZC_TRY(launch_debug_xor_byte(ep, s));
     OZC_TRY(pe.mark(3));
@@ -468,6 +493,9 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     if (C) {
         CrtArgs ca{};
         ca.eprime = ep;
+        ca.eprime_parts = ep_parts;
+        ca.l_split = ks.l_split;
+        ca.parts = ks.parts;
         ca.m = m;
         ca.n = n;
         ca.m_pad = L.m_pad;
@@ -671,6 +699,9 @@ ozc_status_t ozc_create(ozc_handle_t *handle, int device) {
     ozc_context *h = new (std::nothrow) ozc_context();
     if (!h) return OZC_STATUS_ALLOC_FAILED;
     h->device = device;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
+        h->cus = cus;
     h->tab_host.resize(kMaxModuli);
     build_tables(h->tab_host.data());
     if (hipMalloc(&h->tab_dev, sizeof(NTable) * kMaxModuli) != hipSuccess ||

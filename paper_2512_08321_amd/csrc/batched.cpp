@@ -344,7 +344,8 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
         c.a.n = q.n;
         c.a.m_pad = d.m_pad;
         c.a.n_pad = d.n_pad;
-        c.a.nmod = d.nmod;
+        c.a.nmod = c.a.l_split = d.nmod;
+        c.a.parts = 1;
         c.a.nchunks = d.nchunks;
         c.a.tab = nullptr;  // bound later
         c.a.mu = (const int16_t *)(uintptr_t)(mu_off + d.muA);

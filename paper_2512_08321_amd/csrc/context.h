@@ -19,6 +19,7 @@ struct PreStats {
 
 struct ozc_context {
     int device = 0;
+    int cus = 256;                      // compute units of the device
     hipStream_t stream = nullptr;
     int nmod = 14;
     ozc_mode_t mode = OZC_MODE_FAST;

@@ -215,7 +215,9 @@ __device__ __forceinline__ void store_c(void *C, int64_t idx, double re, double 
 // Real outputs (EK real) reconstruct the one E' plane of each modulus; alpha and beta
 // are real then (imaginary parts zero), so the fused multiply-add order below reduces
 // to x = alpha c, out = fma(beta, C, x).
-template <int C, int EK, bool DD = false>
+// PARTS: the moduli from a.l_split on have E' in a.parts parts (their registers would cost
+// the ordinary kernel occupancy).
+template <int C, int EK, bool DD = false, bool PARTS = false>
 __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
     constexpr bool REAL = elem_real(EK);
     constexpr int EPL = REAL ? 1 : 2;  // E' planes per modulus
@@ -226,8 +228,8 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
     if (j >= a.n || ib >= a.m) return;
 
     const int64_t planeC = a.n_pad * a.m_pad;
-    // S = sum_l s_l E'_l in 38-bit chunks: |partial sums| < 24 2^38 2^7 < 2^50, every
-    // fused multiply-add exact
+    // S = sum_l s_l E'_l in 38-bit chunks: |partial sums| < kMaxPartSum 2^38 2^7 < 2^52
+    // (< 24 2^45 < 2^50 without parts), every fused multiply-add exact
     double accR[4][C], accI[4][C];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -236,17 +238,11 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
 
     ConstTab tab = const_ptr(a.tab);
     const OZC_AS_GLOBAL int8_t *E = global_ptr(a.eprime) + j * a.m_pad + ib;
-#pragma unroll 4
-    for (int l = 0; l < a.nmod; ++l) {
-        const uint32_t wr = *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(E + (int64_t)(EPL * l) * planeC);
-        const uint32_t wi =
-            REAL ? 0u : *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(E + (int64_t)(EPL * l + 1) * planeC);
-        double er[4], ei[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            er[u] = (double)(int)(int8_t)(wr >> (8 * u));
-            ei[u] = (double)(int)(int8_t)(wi >> (8 * u));
-        }
+    auto words = [&](const OZC_AS_GLOBAL int8_t *e, uint32_t &wr, uint32_t &wi) {
+        wr = *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(e);
+        wi = REAL ? 0u : *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(e + planeC);
+    };
+    auto add = [&](int l, const double (&er)[4], const double (&ei)[4]) {
         const OZC_AS_CONST double *sc = tab->mod[l].schunk;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -256,6 +252,49 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
                 accR[u][c] = fma(s, er[u], accR[u][c]);
                 if constexpr (!REAL) accI[u][c] = fma(s, ei[u], accI[u][c]);
             }
+        }
+    };
+#pragma unroll 4
+    for (int l = 0; l < (PARTS ? a.l_split : a.nmod); ++l) {
+        uint32_t wr, wi;
+        words(E + (int64_t)(EPL * l) * planeC, wr, wi);
+        double er[4], ei[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            er[u] = (double)(int)(int8_t)(wr >> (8 * u));
+            ei[u] = (double)(int)(int8_t)(wi >> (8 * u));
+        }
+        add(l, er, ei);
+    }
+    if constexpr (PARTS) {  // products cut along k: the parts' residues add up
+        const int ns = a.nmod - a.l_split;
+        const OZC_AS_GLOBAL int8_t *E2 = global_ptr(a.eprime_parts) + j * a.m_pad + ib;
+#pragma unroll 2
+        for (int ls = 0; ls < ns; ++ls) {
+            uint32_t pr[kMaxParts], pi[kMaxParts];  // all parts' loads before the first use
+#pragma unroll
+            for (int q = 0; q < kMaxParts; ++q) {
+                pr[q] = pi[q] = 0;
+                if (q < a.parts)
+                    words(q == 0 ? E + (int64_t)(EPL * (a.l_split + ls)) * planeC
+                                 : E2 + (int64_t)(EPL * ((q - 1) * ns + ls)) * planeC, pr[q], pi[q]);
+            }
+            int sr[4] = {}, si[4] = {};
+#pragma unroll
+            for (int q = 0; q < kMaxParts; ++q) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    sr[u] += (int)(int8_t)(pr[q] >> (8 * u));
+                    si[u] += (int)(int8_t)(pi[q] >> (8 * u));
+                }
+            }
+            double er[4], ei[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                er[u] = (double)sr[u];
+                ei[u] = (double)si[u];
+            }
+            add(a.l_split + ls, er, ei);
         }
     }
 
@@ -307,9 +346,9 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
     }
 }
 
-template <int C, int EK>
+template <int C, int EK, bool PARTS>
 __global__ __launch_bounds__(256) void crt_output_kernel(CrtArgs a) {
-    crt_output_body<C, EK>(a, blockIdx.x);
+    crt_output_body<C, EK, false, PARTS>(a, blockIdx.x);
 }
 
 template <int C>
@@ -361,17 +400,24 @@ hipError_t launch_C(const CrtArgs &a, hipStream_t s) {
     const int64_t threads = ((a.m + 3) / 4) * a.n;
     dim3 grid((unsigned)((threads + 255) / 256));
     if (a.C_lo) {
-        if (a.ek != kElemZ) return hipErrorInvalidValue;
+        if (a.ek != kElemZ || (a.parts > 1 && a.l_split < a.nmod)) return hipErrorInvalidValue;
         hipLaunchKernelGGL((crt_dd_kernel<C>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
+    const bool parts = a.parts > 1 && a.l_split < a.nmod;
+#define OZC_CRT(EKV)                                                                                     \
+    case EKV:                                                                                            \
+        if (parts) hipLaunchKernelGGL((crt_output_kernel<C, EKV, true>), grid, dim3(256), 0, s, a);      \
+        else hipLaunchKernelGGL((crt_output_kernel<C, EKV, false>), grid, dim3(256), 0, s, a);           \
+        break;
     switch (a.ek) {
-        case kElemZ: hipLaunchKernelGGL((crt_output_kernel<C, kElemZ>), grid, dim3(256), 0, s, a); break;
-        case kElemC: hipLaunchKernelGGL((crt_output_kernel<C, kElemC>), grid, dim3(256), 0, s, a); break;
-        case kElemD: hipLaunchKernelGGL((crt_output_kernel<C, kElemD>), grid, dim3(256), 0, s, a); break;
-        case kElemS: hipLaunchKernelGGL((crt_output_kernel<C, kElemS>), grid, dim3(256), 0, s, a); break;
+        OZC_CRT(kElemZ)
+        OZC_CRT(kElemC)
+        OZC_CRT(kElemD)
+        OZC_CRT(kElemS)
         default: return hipErrorInvalidValue;
     }
+#undef OZC_CRT
     return hipGetLastError();
 }
 

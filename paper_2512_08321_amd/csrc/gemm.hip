@@ -32,6 +32,8 @@
 // product does not depend on how the hardware orders k inside the 32-wide
 // step.  Accumulator register r of lane l holds row 8(r/4) + 4(l/32) + (r mod 4),
 // column (l mod 32).
+#include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "internal.h"
@@ -133,13 +135,17 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// A wave-uniform value into a scalar register: integer divisions leave theirs in vector
+// registers, and with it every address computed from it.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
 __device__ __forceinline__ void map_tile(uint32_t L, uint32_t TR, uint32_t TC, uint32_t total, int &l,
                                          int64_t &ti, int64_t &tj) {
     // XCD x (blocks x, x + 8, ...) -> contiguous part x of total / 8 tiles, one more in the
     // first total % 8 parts.  Block counts are below 2^31: 32-bit divisions.
     const uint32_t x = L & 7, rem8 = total & 7;
     const uint32_t q = x * (total >> 3) + min(x, rem8) + (L >> 3);
-    const uint32_t T = TR * TC, mod = q / T;
+    const uint32_t T = TR * TC, mod = uniform(q / T);
     l = (int)mod;
     const uint32_t t = q - mod * T;
     constexpr uint32_t G = 4;
@@ -147,8 +153,8 @@ __device__ __forceinline__ void map_tile(uint32_t L, uint32_t TR, uint32_t TC, u
     const uint32_t rem = t - grp * (G * TC);
     const uint32_t rows = min(G, TR - grp * G);
     const uint32_t col = rem / rows;
-    ti = grp * G + (rem - col * rows);
-    tj = col;
+    ti = uniform(grp * G + (rem - col * rows));
+    tj = uniform(col);
 }
 
 // WM x WN waves of BM x BN blocks; KS 64-byte k sub-slabs per pipeline stage.
@@ -212,11 +218,12 @@ __device__ __forceinline__ void vmcnt_wait() {
 }
 __device__ __forceinline__ void block_barrier() { __builtin_amdgcn_s_barrier(); }
 
-// One output tile (ti, tj) of modulus l: all products of the plan and their epilogues.
+// One output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + nk - 1: all products of
+// the plan and their epilogues, E' to the modulus' planes at ep.
 // Ends with a block barrier, so a caller may run the next tile right away.
 template <int KIND, typename C, bool DUMP>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b, int l, int64_t ti,
-                                          int64_t tj) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b, int8_t *ep, int l,
+                                          int64_t ti, int64_t tj, int s0, int nk) {
     using P = Plan<KIND>;
     constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN, KS = C::KS;
     constexpr int WTM = BM * 32, WTN = BN * 32;  // wave tile
@@ -234,10 +241,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
     // planes are slab-major: k-slab s (64 wide) of a plane is m_pad x 64 bytes at s * slabA
     const int64_t planeA = m_pad * k_pad, planeB = n_pad * k_pad;
     const int64_t slabA = m_pad * BK, slabB = n_pad * BK;
-    const int8_t *baseA = (bound ? b.A : a.A) + (int64_t)l * P::nplanes * planeA + i0 * BK;
-    const int8_t *baseB = (bound ? b.B : a.B) + (int64_t)l * P::nplanes * planeB + j0 * BK;
-
-    const int nk = (int)(k_pad / C::KSTEP);
+    static_assert(C::KS == 1, "one k-slab per ring stage");
+    const int8_t *baseA = (bound ? b.A : a.A) + (int64_t)l * P::nplanes * planeA + i0 * BK + s0 * slabA;
+    const int8_t *baseB = (bound ? b.B : a.B) + (int64_t)l * P::nplanes * planeB + j0 * BK + s0 * slabB;
 
     ModRule rule{};
     if constexpr (!bound) rule = mod_rule(a.tab, l);
@@ -414,11 +420,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
                 w[g] ^= 0x80808080u;
             });
         };
-        int8_t *ER = nullptr, *EI = nullptr;
-        if constexpr (!bound) {
-            ER = a.eprime + (int64_t)l * P::eplanes * planeC;
-            EI = ER + planeC;  // not used by real products
-        }
+        int8_t *ER = ep, *EI = ep + planeC;  // EI: not used by real products
         if constexpr (C::PREFETCH) {
             if (sgi + 1 < P::nseg) issue_first(sgi + 1);
         }
@@ -536,8 +538,8 @@ struct OnceCfg {
     static constexpr int STAGE = (TM + TN) * 4;  // uint4 per 64-wide k-slab in LDS
 };
 
-// One output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + slabs - 1, E' to `ep`
-// (the E' planes of all moduli).  Ends with a block barrier.
+// As gemm_tile: one output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + slabs - 1,
+// E' to the modulus' planes at ep.  Ends with a block barrier.
 template <int KIND, typename C>
 __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, int64_t ti, int64_t tj,
                                           int s0, int slabs) {
@@ -668,7 +670,7 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
     }
 
     const int64_t planeC = a.n_pad * a.m_pad;
-    int8_t *E = ep + (int64_t)l * P::eplanes * planeC + i0 + wm * 64 + 16 * (lane >> 5);
+    int8_t *E = ep + i0 + wm * 64 + 16 * (lane >> 5);
     auto store = [&](auto bi, auto bj, int plane, auto value) {
         uint32_t w[4];
         static_for<4>([&](auto g) {
@@ -696,38 +698,79 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
     });
 }
 
-template <int KIND, typename C, bool DUMP>
-__global__ __launch_bounds__(C::THREADS) void residue_gemm_kernel(GemmArgs a, BoundArgs b) {
-    constexpr bool bound = Plan<KIND>::bound;
-    const uint32_t TR = (uint32_t)((bound ? b.m_pad : a.m_pad) / C::TM);
-    const uint32_t TC = (uint32_t)((bound ? b.n_pad : a.n_pad) / C::TN);
-    const uint32_t nmod = bound ? 1 : a.nmod;
-    int l;
+// E' planes of modulus l in a.eprime.
+template <int KIND>
+__device__ __forceinline__ int8_t *eprime_of(const GemmArgs &a, int l) {
+    return a.eprime + (int64_t)l * Plan<KIND>::eplanes * a.n_pad * a.m_pad;
+}
+
+// The work of block `blk` of a single call: modulus, tile, k-slabs and E' planes.  The
+// first l_split moduli take one block per tile; each tile of the others takes a.parts
+// blocks, which cut its k-slabs evenly and write E' planes of their own (congruent sums:
+// the reconstruction adds the parts' residues).
+struct BlockWork {
+    int l, s0, nk;
     int64_t ti, tj;
-    map_tile(blockIdx.x, TR, TC, nmod * TR * TC, l, ti, tj);
-    gemm_tile<KIND, C, DUMP>(a, b, l, ti, tj);
+    int8_t *ep;
+};
+template <int KIND, typename C>
+__device__ __forceinline__ BlockWork block_work(const GemmArgs &a, uint32_t blk) {
+    const uint32_t TR = (uint32_t)(a.m_pad / C::TM), TC = (uint32_t)(a.n_pad / C::TN);
+    const uint32_t whole = (uint32_t)a.l_split * TR * TC;
+    const int slabs = (int)(a.k_pad / BK);
+    BlockWork w;
+    if (blk < whole) {
+        map_tile(blk, TR, TC, whole, w.l, w.ti, w.tj);
+        w.s0 = 0;
+        w.nk = slabs;
+        w.ep = eprime_of<KIND>(a, w.l);
+        return w;
+    }
+    const int ns = a.nmod - a.l_split;  // split moduli
+    int lp;
+    map_tile(blk - whole, TR, TC, (uint32_t)(ns * a.parts) * TR * TC, lp, w.ti, w.tj);
+    const int part = (int)uniform((uint32_t)lp / (uint32_t)ns), ls = lp - part * ns;
+    w.l = a.l_split + ls;
+    w.s0 = (int)uniform((uint32_t)(slabs * part) / (uint32_t)a.parts);
+    w.nk = (int)uniform((uint32_t)(slabs * (part + 1)) / (uint32_t)a.parts) - w.s0;
+    w.ep = part == 0 ? eprime_of<KIND>(a, w.l)
+                     : a.eprime_parts + (int64_t)((part - 1) * ns + ls) * Plan<KIND>::eplanes * a.n_pad * a.m_pad;
+    return w;
+}
+
+template <int KIND, typename C, bool DUMP>
+__global__ __launch_bounds__(C::THREADS) void residue_gemm_kernel(GemmArgs a) {
+    const BlockWork w = block_work<KIND, C>(a, blockIdx.x);
+    gemm_tile<KIND, C, DUMP>(a, BoundArgs{}, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
 }
 
 template <int KIND, typename C>
 __global__ __launch_bounds__(C::THREADS, 2) void once_gemm_kernel(GemmArgs a) {
-    const uint32_t TR = (uint32_t)(a.m_pad / C::TM), TC = (uint32_t)(a.n_pad / C::TN);
+    const BlockWork w = block_work<KIND, C>(a, blockIdx.x);
+    once_tile<KIND, C>(a, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
+}
+
+template <int KIND, typename C>
+__global__ __launch_bounds__(C::THREADS) void bound_gemm_kernel(BoundArgs b) {
+    const uint32_t TR = (uint32_t)(b.m_pad / C::TM), TC = (uint32_t)(b.n_pad / C::TN);
     int l;
     int64_t ti, tj;
-    map_tile(blockIdx.x, TR, TC, (uint32_t)a.nmod * TR * TC, l, ti, tj);
-    once_tile<KIND, C>(a, a.eprime, l, ti, tj, 0, (int)(a.k_pad / BK));
+    map_tile(blockIdx.x, TR, TC, TR * TC, l, ti, tj);
+    gemm_tile<KIND, C, false>(GemmArgs{}, b, nullptr, 0, ti, tj, 0, (int)(b.k_pad / BK));
 }
 
 // A batch's tile of either class.
 template <int KIND, typename C>
 struct BatchTile {
     __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
-        gemm_tile<KIND, C, false>(a, BoundArgs{}, l, ti, tj);
+        gemm_tile<KIND, C, false>(a, BoundArgs{}, eprime_of<KIND>(a, l), l, ti, tj, 0, (int)(a.k_pad / BK));
     }
 };
 template <int KIND, int WM, int WN, int NSTAGE, int NACC>
 struct BatchTile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>> {
     __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
-        once_tile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>>(a, a.eprime, l, ti, tj, 0, (int)(a.k_pad / BK));
+        once_tile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>>(a, eprime_of<KIND>(a, l), l, ti, tj, 0,
+                                                     (int)(a.k_pad / BK));
     }
 };
 
@@ -776,7 +819,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void batch_gemm_kernel(const BatchGe
             __syncthreads();
             if (j32 >= nq) break;
             if (threadIdx.x == 0) ahead = atomicAdd(&counters[q] + zero, 1u);
-            const uint32_t jc = j32 / ch;
+            const uint32_t jc = uniform(j32 / ch);
             const int64_t w = ((int64_t)jc * kBatchQueues + q) * ch + (j32 - jc * ch);
             const OZC_AS_CONST BatchGemm *pl = const_ptr(probs);
             const int64_t f0 = pl[lo].item0;
@@ -792,11 +835,11 @@ __global__ __launch_bounds__(C::THREADS, 2) void batch_gemm_kernel(const BatchGe
             }
             const OZC_AS_CONST BatchGemm &pb = pl[lo];
             const uint32_t T = (uint32_t)pb.TR * (uint32_t)pb.TC, local = (uint32_t)(w - pb.item0);
-            const int lg = (int)(local / T);
+            const int lg = (int)uniform(local / T);
             const uint32_t t = local - (uint32_t)lg * T;
-            const int64_t ti = t / (uint32_t)pb.TC, tj = t - (uint32_t)ti * (uint32_t)pb.TC;
+            const int64_t ti = uniform(t / (uint32_t)pb.TC), tj = t - (uint32_t)ti * (uint32_t)pb.TC;
             GemmArgs a{pb.A, pb.B, pb.m_pad, pb.n_pad, pb.k_pad, pb.nmod, KIND == KIND_4M ? 1 : 0,
-                       pb.tab, pb.eprime, nullptr, C::TM};
+                       pb.tab, pb.eprime, nullptr, C::TM, pb.nmod, 1, nullptr};
             const int l1 = min(pb.nmod, (lg + 1) * group);
             for (int l = lg * group; l < l1; ++l) BatchTile<KIND, C>::run(a, l, ti, tj);
         }
@@ -823,7 +866,7 @@ __global__ __launch_bounds__(C::THREADS) void batch_bound_kernel(const BatchBoun
         const BatchBound &pb = probs[lo];
         const int64_t t = w - pb.item0;
         const int64_t ti = t / pb.TC, tj = t - ti * pb.TC;
-        gemm_tile<KIND_BOUND, C, false>(GemmArgs{}, pb.b, 0, ti, tj);
+        gemm_tile<KIND_BOUND, C, false>(GemmArgs{}, pb.b, nullptr, 0, ti, tj, 0, (int)(pb.b.k_pad / BK));
     }
 }
 
@@ -845,9 +888,9 @@ int blocks_per_cu() {
 }
 
 template <int KIND, typename C>
-void launch_kind(const GemmArgs &a, const BoundArgs &b, bool dump, int64_t blocks, hipStream_t s) {
-    if (dump) hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a, b);
-    else hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, false>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a, b);
+void launch_kind(const GemmArgs &a, bool dump, int64_t blocks, hipStream_t s) {
+    if (dump) hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a);
+    else hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, false>), dim3((unsigned)blocks), dim3(C::THREADS), 0, s, a);
 }
 
 // 128 x 128 output tiles, 256 threads, 64 KB LDS: two blocks per CU, two waves per SIMD
@@ -863,7 +906,7 @@ hipError_t launch_once(const GemmArgs &a, int64_t blocks, hipStream_t s) {
 template <int KIND, typename C>
 void launch_dump(const GemmArgs &a, int64_t blocks, hipStream_t s) {
     hipLaunchKernelGGL((residue_gemm_kernel<KIND, C, true>), dim3((unsigned)blocks), dim3(C::THREADS), 0,
-                       s, a, BoundArgs{});
+                       s, a);
 }
 
 }  // namespace
@@ -873,15 +916,63 @@ int gemm_kstep_for(int tile) { return tile == 256 ? CfgLarge::KSTEP : CfgSmall::
 int gemm_tile_rows(int tile) { return tile == 256 ? CfgLarge::TM : CfgSmall::TM; }
 int gemm_tile_cols(int tile) { return tile == 256 ? CfgLarge::TN : CfgSmall::TN; }
 
+// How a single call's products are cut along k.  A launch whose tiles leave CUs idle, or
+// whose last round of blocks is short, gains from more and shorter blocks; every part pays
+// an epilogue and E' planes of its own that the reconstruction reads too.  Times in us, one
+// slab (64 k) of one product of a tile and the rest of a block, from sweeps over k on one
+// part: 128 x 128 tiles 0.38 alone on a CU and 0.6 with a second block there, 256 x 256 tiles
+// 0.8; the rest 4 and 17 (one real product: 2 and 6).
+// 384 x 320 x 40000 at N = 14 (126 tiles): 4 parts; 2048^3 at N = 13 (832 tiles of 256 x 256 on
+// 256 CUs): the last modulus in 4 parts instead of a fourth round that is a quarter full.
+KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad, int64_t k_pad, int cus) {
+    const bool real = algo == 2, small = tile == 128;
+    const int nseg = real ? 1 : (algo == 1 ? 4 : 3);
+    const double T = (double)(m_pad / tile) * (double)(n_pad / tile);
+    const int64_t slabs = k_pad / BK;
+    const double rest = small ? (real ? 2.0 : 4.0) : (real ? 6.0 : 17.0);
+    const double slots = small ? 2.0 * cus : cus;
+    // a further E' plane written and read, and the reconstruction's longer chain of loads
+    const double plane_us = (real ? 1.0 : 2.0) * (double)m_pad * (double)n_pad * 2.0 / 4e6;
+    auto block_us = [&](int64_t n, double blocks) {
+        return nseg * (double)n * (small ? (blocks <= cus ? 0.38 : 0.6) : 0.8) + rest;
+    };
+    auto rounds = [&](double blocks) { return std::ceil(blocks / slots); };
+    KSplit best{nmod, 1};
+    const double whole = rounds(nmod * T) * block_us(slabs, nmod * T);
+    double best_us = 0.93 * whole;
+    // what an even spread of the blocks over the slots would take, epilogues included: no
+    // split does better
+    if (nmod * T >= slots && nmod * T / slots * block_us(slabs, nmod * T) + 4.0 >= best_us) return best;
+    if (whole <= 4.0 + 2.0 * rest) return best;  // too short for another epilogue
+    for (int parts : {2, 3, 4, 6, 8}) {
+        if (parts > slabs) break;
+        for (int ls = 0; ls < nmod; ++ls) {
+            if (ls + (nmod - ls) * parts > kMaxPartSum) continue;
+            const double n1 = ls * T, n2 = (nmod - ls) * T * parts;
+            const double b1 = block_us(slabs, n1 + n2), b2 = block_us((slabs + parts - 1) / parts, n1 + n2);
+            double us = ls == 0 ? rounds(n2) * b2
+                                : std::max(rounds(n1) * b1, (n1 * b1 + n2 * b2) / slots + 0.5 * b2);
+            us += (nmod - ls) * (parts - 1) * plane_us + 4.0;
+            if (us < best_us) {
+                best_us = us;
+                best = KSplit{ls, parts};
+            }
+        }
+    }
+    return best;
+}
+
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {
     const int tile = a.tile;
     if (tile != 128 && tile != 256) return hipErrorInvalidValue;
     const int tr = gemm_tile_rows(tile), tc = gemm_tile_cols(tile);
     if (a.m_pad % tr || a.n_pad % tc || a.k_pad % gemm_kstep_for(tile) || a.nmod < 1)
         return hipErrorInvalidValue;
-    const int64_t blocks = (int64_t)a.nmod * (a.m_pad / tr) * (a.n_pad / tc);
+    if (a.l_split < 0 || a.l_split > a.nmod || a.parts < 1 || a.parts > kMaxParts || a.parts > a.k_pad / BK ||
+        (a.parts > 1 && a.l_split < a.nmod && !a.eprime_parts))
+        return hipErrorInvalidValue;
+    const int64_t blocks = (a.l_split + (int64_t)(a.nmod - a.l_split) * a.parts) * (a.m_pad / tr) * (a.n_pad / tc);
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    BoundArgs none{};
     const bool dump = a.prods != nullptr;
     if (a.algo < 0 || a.algo > 2) return hipErrorInvalidValue;
     if (tile == 128 && !dump) {
@@ -896,13 +987,13 @@ hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {
         return hipGetLastError();
     }
     // one product per modulus: the long-k schedule keeps no carry, so it serves every k
-    if (a.algo == 2) launch_kind<KIND_REAL, CfgLarge>(a, none, dump, blocks, s);
+    if (a.algo == 2) launch_kind<KIND_REAL, CfgLarge>(a, dump, blocks, s);
     else if (a.k_pad >= kLongK) {
-        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLarge>(a, none, dump, blocks, s);
-        else launch_kind<KIND_4M, CfgLarge>(a, none, dump, blocks, s);
+        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLarge>(a, dump, blocks, s);
+        else launch_kind<KIND_4M, CfgLarge>(a, dump, blocks, s);
     } else {
-        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLargeShortK>(a, none, dump, blocks, s);
-        else launch_kind<KIND_4M, CfgLargeShortK>(a, none, dump, blocks, s);
+        if (a.algo == 0) launch_kind<KIND_KARATSUBA, CfgLargeShortK>(a, dump, blocks, s);
+        else launch_kind<KIND_4M, CfgLargeShortK>(a, dump, blocks, s);
     }
     return hipGetLastError();
 }
@@ -913,10 +1004,10 @@ hipError_t launch_bound_gemm(const BoundArgs &b, hipStream_t s) {
     constexpr int tile = 128;
     if (b.m_pad % tile || b.n_pad % tile || b.k_pad % BK) return hipErrorInvalidValue;
     const int64_t blocks = (b.m_pad / tile) * (b.n_pad / tile);
-    GemmArgs none{};
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(CfgSmall::THREADS);
-    if (b.real) hipLaunchKernelGGL((residue_gemm_kernel<KIND_BOUND_REAL, CfgSmall, false>), grid, block, 0, s, none, b);
-    else hipLaunchKernelGGL((residue_gemm_kernel<KIND_BOUND, CfgSmall, false>), grid, block, 0, s, none, b);
+    if (b.real) hipLaunchKernelGGL((bound_gemm_kernel<KIND_BOUND_REAL, CfgSmall>), grid, block, 0, s, b);
+    else hipLaunchKernelGGL((bound_gemm_kernel<KIND_BOUND, CfgSmall>), grid, block, 0, s, b);
     return hipGetLastError();
 }
 

@@ -134,7 +134,18 @@ struct GemmArgs {
     int8_t *eprime;       // [N][2][n_pad][m_pad] (real: [N][n_pad][m_pad])
     int32_t *prods;       // optional raw dump [N][nprod][n_pad][m_pad]
     int tile;             // output tile edge (128 or 256); m_pad, n_pad are multiples
+    int l_split, parts;   // moduli from l_split on cut k into `parts` parts (1 .. k_pad / 64), ...
+    int8_t *eprime_parts; // ... parts 1 .. parts - 1 with E' planes here: [part - 1][l - l_split]
+                          // [2][n_pad][m_pad]; every part's E' is a residue of its share
 };
+// Sum over the moduli of their parts, at most: 128 kMaxPartSum 2^38 stays below 2^52 in the
+// reconstruction's FP64 chunks, and so does the quotient times a chunk of P.
+constexpr int kMaxPartSum = 96;
+constexpr int kMaxParts = 8;
+struct KSplit {
+    int l_split, parts;
+};
+KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad, int64_t k_pad, int cus);
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s);
 // Output tile edge used for an m x n product (the padding of every buffer follows it).
 int gemm_tile_for(int64_t m, int64_t n);
@@ -167,6 +178,8 @@ hipError_t launch_batch_bound(const BatchBound *probs, int nprob, int64_t items,
 
 struct CrtArgs {
     const int8_t *eprime;  // [N][2][n_pad][m_pad] (real outputs: [N][n_pad][m_pad])
+    const int8_t *eprime_parts;  // further parts of the moduli from l_split on (GemmArgs)
+    int l_split, parts;
     int64_t m, n, m_pad, n_pad;
     int nmod;
     int nchunks;           // chunks of P for this N (host copy of tab->nchunks)
