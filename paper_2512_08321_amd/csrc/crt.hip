@@ -10,7 +10,8 @@
 // in FP64 (s_l split into 38-bit chunks, every partial sum an integer below
 // 24 * 2^38 * 2^7 < 2^53), and reduced mod P on the same chunks, which removes
 // the reconstruction error altogether and makes the output bit-reproducible
-// against an exact reference; the rounding works on the 256-bit integer |C'|.
+// against an exact reference; C' is rounded once, by error-free sums of its chunks (the
+// double-double output and rare values: as a 256-bit integer).
 #include "internal.h"
 
 namespace ozc {
@@ -165,6 +166,74 @@ __device__ __forceinline__ double reconstruct(double (&r)[C], ConstTab tab, int 
     return neg ? -d : d;
 }
 
+// a + b = s + e exactly (Knuth).
+__device__ __forceinline__ double two_sum(double a, double b, double &e) {
+    const double s = a + b, t = s - a;
+    e = (a - (s - t)) + (b - t);
+    return s;
+}
+
+// a + b + c rounded once to nearest-even (Boldo and Melquiond, "Emulation of a FMA and
+// correctly rounded sums: proved algorithms using rounding to odd", 2008): the low parts of
+// two error-free sums are added with rounding to odd, which the last addition cannot mistake
+// for a tie.
+__device__ __forceinline__ double sum3(double a, double b, double c) {
+    double ul, tl, ve;
+    const double uh = two_sum(b, c, ul);
+    const double th = two_sum(a, uh, tl);
+    const double v = two_sum(tl, ul, ve);
+    int64_t vb = __double_as_longlong(v);
+    // inexact and even: one step towards the error, to the odd neighbour
+    if (ve != 0.0 && (vb & 1) == 0) vb += (ve > 0.0) == (v > 0.0) ? 1 : -1;
+    return th + __longlong_as_double(vb);
+}
+
+// reconstruct() without the residual, straight from the chunks: the quotient as there, then
+// the chunks' sum rounded once.  Two chunks: a fused multiply-add.  Three: sum3.  More: the
+// low chunks are normalised and all below the third from the top only set its last bit
+// (rounding to odd), which is far below the rounding position unless the top two nearly
+// cancel; those rare values take reconstruct().  The 256-bit integer rounding takes about
+// 80 instructions per value, sum3 about 25, the fused multiply-add one.  Reconstructions of
+// 4096^2 outputs with it and the loads ahead: CGEMM at N = 6 104 -> 86 us (3.9 TB/s), DGEMM
+// at N = 14 131 -> 99 us (3.7 TB/s), ZGEMM at N = 14 206 -> 186..198, at N = 24 326 -> 290 us.
+template <int C>
+__device__ __forceinline__ double reconstruct_fast(double (&r)[C], ConstTab tab, int &sh) {
+    double sa = r[C - 1];
+#pragma unroll
+    for (int c = C - 2; c >= 0; --c) sa = fma(sa, kChunk, r[c]);
+    const double x = sa * tab->inv_P;
+    const double qd = rint(x);
+    if (fabs(x - qd) > 0.5 - 1.0 / 1048576.0) return reconstruct<C>(r, tab, sh);
+    double t[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) t[c] = fma(-qd, tab->Pchunk[c], r[c]);
+    if constexpr (C == 1) {
+        sh = 0;
+        return t[0];
+    } else if constexpr (C == 2) {
+        sh = 0;
+        return fma(t[1], kChunk, t[0]);
+    } else if constexpr (C == 3) {
+        sh = kChunkBits;
+        return sum3(t[2] * kChunk, t[1], t[0] * kInvChunk);
+    } else {
+        bool rest = false;
+#pragma unroll
+        for (int c = 0; c < C - 2; ++c) {
+            const double f = floor(t[c] * kInvChunk);
+            t[c] = fma(-f, kChunk, t[c]);  // in [0, 2^38)
+            t[c + 1] += f;
+            if (c < C - 3) rest = rest || t[c] != 0.0;
+        }
+        // t[C-3] + (something in (0, 1)) to odd
+        if (rest) t[C - 3] = fma(2.0, floor(t[C - 3] * 0.5), 1.0);
+        const double a = t[C - 1] * kChunk;
+        if (fabs(a + t[C - 2]) < 0x1p20) return reconstruct<C>(r, tab, sh);
+        sh = kChunkBits * (C - 2);
+        return sum3(a, t[C - 2], t[C - 3] * kInvChunk);
+    }
+}
+
 __device__ __forceinline__ void alpha_beta(double cr, double ci, double ar, double ai, double br,
                                            double bi, bool beta_zero, double Cr, double Ci,
                                            double &orr, double &oi) {
@@ -210,21 +279,23 @@ __device__ __forceinline__ void store_c(void *C, int64_t idx, double re, double 
     else global_ptr(reinterpret_cast<float *>(C))[idx] = (float)re;
 }
 
+constexpr int kCrtBatch = 4;
+static_assert(kMaxModuli % kCrtBatch == 0, "the last batch's weights stay inside the table");
+
 // One thread: 4 consecutive rows i of one column j; block bx covers threads
 // 256 bx ... 256 bx + 255 of the ceil(m / 4) x n grid (padding rows get no thread).
 // Real outputs (EK real) reconstruct the one E' plane of each modulus; alpha and beta
 // are real then (imaginary parts zero), so the fused multiply-add order below reduces
 // to x = alpha c, out = fma(beta, C, x).
-// PARTS: the moduli from a.l_split on have E' in a.parts parts (their registers would cost
-// the ordinary kernel occupancy).
 template <int C, int EK, bool DD = false, bool PARTS = false>
 __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
     constexpr bool REAL = elem_real(EK);
     constexpr int EPL = REAL ? 1 : 2;  // E' planes per modulus
+    // below 2^32 threads unless the output has 2^34 elements
     const int64_t m4 = (a.m + 3) >> 2;
     const int64_t t = bx * 256 + threadIdx.x;
-    const int64_t i4 = t % m4, j = t / m4;
-    const int64_t ib = i4 * 4;
+    const int64_t j = (uint64_t)(m4 | (bx * 256 + 255)) >> 32 ? t / m4 : (int64_t)((uint32_t)t / (uint32_t)m4);
+    const int64_t ib = (t - j * m4) * 4;
     if (j >= a.n || ib >= a.m) return;
 
     const int64_t planeC = a.n_pad * a.m_pad;
@@ -238,63 +309,57 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
 
     ConstTab tab = const_ptr(a.tab);
     const OZC_AS_GLOBAL int8_t *E = global_ptr(a.eprime) + j * a.m_pad + ib;
-    auto words = [&](const OZC_AS_GLOBAL int8_t *e, uint32_t &wr, uint32_t &wi) {
-        wr = *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(e);
-        wi = REAL ? 0u : *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(e + planeC);
-    };
-    auto add = [&](int l, const double (&er)[4], const double (&ei)[4]) {
-        const OZC_AS_CONST double *sc = tab->mod[l].schunk;
+    auto add = [&](const double (&sc)[C], const double (&er)[4], const double (&ei)[4]) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const double s = sc[c];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                accR[u][c] = fma(s, er[u], accR[u][c]);
-                if constexpr (!REAL) accI[u][c] = fma(s, ei[u], accI[u][c]);
+                accR[u][c] = fma(sc[c], er[u], accR[u][c]);
+                if constexpr (!REAL) accI[u][c] = fma(sc[c], ei[u], accI[u][c]);
             }
         }
     };
-#pragma unroll 4
-    for (int l = 0; l < (PARTS ? a.l_split : a.nmod); ++l) {
-        uint32_t wr, wi;
-        words(E + (int64_t)(EPL * l) * planeC, wr, wi);
-        double er[4], ei[4];
+    // The E' of every modulus, then the further parts of the moduli from l_split on (their
+    // products were cut along k: the parts' residues add up).  In batches: the next batch's
+    // words and this one's weights are loaded before the sums.  A batch that runs past the
+    // last entry reads that one again and adds nothing.
+    const int entries = a.nmod + (PARTS ? (a.nmod - a.l_split) * (a.parts - 1) : 0);
+    const OZC_AS_GLOBAL int8_t *E2 = PARTS ? global_ptr(a.eprime_parts) + j * a.m_pad + ib : nullptr;
+    uint32_t wr[kCrtBatch], wi[kCrtBatch];
+    auto load = [&](int e0) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            er[u] = (double)(int)(int8_t)(wr >> (8 * u));
-            ei[u] = (double)(int)(int8_t)(wi >> (8 * u));
+        for (int q = 0; q < kCrtBatch; ++q) {
+            const int e = min(e0 + q, entries - 1);
+            const OZC_AS_GLOBAL int8_t *p = !PARTS || e < a.nmod ? E + (int64_t)(EPL * e) * planeC
+                                                                 : E2 + (int64_t)(EPL * (e - a.nmod)) * planeC;
+            wr[q] = *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(p);
+            wi[q] = REAL ? 0u : *reinterpret_cast<const OZC_AS_GLOBAL uint32_t *>(p + planeC);
         }
-        add(l, er, ei);
-    }
-    if constexpr (PARTS) {  // products cut along k: the parts' residues add up
-        const int ns = a.nmod - a.l_split;
-        const OZC_AS_GLOBAL int8_t *E2 = global_ptr(a.eprime_parts) + j * a.m_pad + ib;
-#pragma unroll 2
-        for (int ls = 0; ls < ns; ++ls) {
-            uint32_t pr[kMaxParts], pi[kMaxParts];  // all parts' loads before the first use
+    };
+    load(0);
+    int l = 0;  // PARTS: modulus of the entry
+    for (int e0 = 0; e0 < entries; e0 += kCrtBatch) {
+        uint32_t cr[kCrtBatch], ci[kCrtBatch];
+        double sc[kCrtBatch][C];
 #pragma unroll
-            for (int q = 0; q < kMaxParts; ++q) {
-                pr[q] = pi[q] = 0;
-                if (q < a.parts)
-                    words(q == 0 ? E + (int64_t)(EPL * (a.l_split + ls)) * planeC
-                                 : E2 + (int64_t)(EPL * ((q - 1) * ns + ls)) * planeC, pr[q], pi[q]);
-            }
-            int sr[4] = {}, si[4] = {};
+        for (int q = 0; q < kCrtBatch; ++q) {
+            cr[q] = wr[q];
+            ci[q] = wi[q];
 #pragma unroll
-            for (int q = 0; q < kMaxParts; ++q) {
+            for (int c = 0; c < C; ++c) sc[q][c] = tab->mod[PARTS ? l : e0 + q].schunk[c];
+            if constexpr (PARTS) l = l + 1 < a.nmod ? l + 1 : a.l_split;
+        }
+        if (e0 + kCrtBatch < entries) load(e0 + kCrtBatch);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    sr[u] += (int)(int8_t)(pr[q] >> (8 * u));
-                    si[u] += (int)(int8_t)(pi[q] >> (8 * u));
-                }
-            }
+        for (int q = 0; q < kCrtBatch; ++q) {
+            if (e0 + q >= entries) break;
             double er[4], ei[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                er[u] = (double)sr[u];
-                ei[u] = (double)si[u];
+                er[u] = (double)(int)(int8_t)(cr[q] >> (8 * u));
+                ei[u] = (double)(int)(int8_t)(ci[q] >> (8 * u));
             }
-            add(a.l_split + ls, er, ei);
+            add(sc[q], er, ei);
         }
     }
 
@@ -327,8 +392,8 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
             li = ldexp(ei, sli - (mui + nuj));
         } else {
             int shr, shi = 0;
-            const double dr = reconstruct<C>(accR[u], tab, shr);
-            const double di = REAL ? 0.0 : reconstruct<C>(accI[u], tab, shi);
+            const double dr = reconstruct_fast<C>(accR[u], tab, shr);
+            const double di = REAL ? 0.0 : reconstruct_fast<C>(accI[u], tab, shi);
             cr = ldexp(dr, shr - (mui + nuj));
             ci = REAL ? 0.0 : ldexp(di, shi - (mui + nuj));
         }
@@ -399,12 +464,12 @@ template <int C>
 hipError_t launch_C(const CrtArgs &a, hipStream_t s) {
     const int64_t threads = ((a.m + 3) / 4) * a.n;
     dim3 grid((unsigned)((threads + 255) / 256));
+    const bool parts = a.parts > 1 && a.l_split < a.nmod;
     if (a.C_lo) {
-        if (a.ek != kElemZ || (a.parts > 1 && a.l_split < a.nmod)) return hipErrorInvalidValue;
+        if (a.ek != kElemZ || parts) return hipErrorInvalidValue;
         hipLaunchKernelGGL((crt_dd_kernel<C>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    const bool parts = a.parts > 1 && a.l_split < a.nmod;
 #define OZC_CRT(EKV)                                                                                     \
     case EKV:                                                                                            \
         if (parts) hipLaunchKernelGGL((crt_output_kernel<C, EKV, true>), grid, dim3(256), 0, s, a);      \
@@ -425,7 +490,9 @@ hipError_t launch_C(const CrtArgs &a, hipStream_t s) {
 
 hipError_t launch_crt_output(const CrtArgs &a, hipStream_t s) {
     if (a.m <= 0 || a.n <= 0) return hipSuccess;
-    if (a.m_pad % 4) return hipErrorInvalidValue;
+    if (a.m_pad % 4 || a.nmod < 1 || a.l_split < 0 || a.l_split > a.nmod || a.parts < 1 ||
+        a.l_split + (a.nmod - a.l_split) * a.parts > kMaxPartSum)
+        return hipErrorInvalidValue;
     switch (a.nchunks) {
         case 1: return launch_C<1>(a, s);
         case 2: return launch_C<2>(a, s);
