@@ -308,8 +308,8 @@ ozc_status_t predict_moduli_many(ozc_context *h, bool single, const std::vector<
     OZC_TRY(hipMemcpyAsync(fprob_dev, fprob.data(), sizeof(FeatProblem) * P, hipMemcpyHostToDevice, s));
     OZC_TRY(launch_fill_u64(mb, 3 * rows, 0, s));
     OZC_TRY(launch_fill_u64(zeros, (int64_t)P, 0, s));
-    OZC_TRY(launch_batch_scan(scan_dev, (int)(2 * P), blk_scan, single, 0, s));
-    OZC_TRY(launch_batch_scan(scan_dev, (int)(2 * P), blk_scan, single, 2, s));
+    OZC_TRY(launch_batch_scan(scan_dev, (int)(2 * P), blk_scan, single, false, s));
+    OZC_TRY(launch_batch_scan(scan_dev, (int)(2 * P), blk_scan, single, true, s));
     OZC_TRY(launch_batch_feat_reduce(fprob_dev, (int)P, s));
     OZC_TRY(launch_mlp_infer(kDims, st->params, feat, (int)P, pred, s));
     std::vector<int> cls(P);

@@ -44,8 +44,8 @@ struct BatchPlan {
     std::vector<BatchCrt> crt;      // ordered by CRT launch
     std::vector<Range> crts;        // one CRT launch per chunk count of P
     std::vector<BatchBound> bound;  // accurate mode: bound products
-    int64_t blk_scan = 0, blk_exp = 0, blk_ceil7 = 0, items[2] = {0, 0}, bound_items = 0;
-    size_t stats_off = 0, stats_words = 0, counter_off = 0;
+    int64_t blk_rows = 0, blk_finish = 0, blk_exp = 0, blk_ceil7 = 0, items[2] = {0, 0}, bound_items = 0;
+    size_t stats_off = 0, counter_off = 0;
     std::vector<Problem> degenerate;  // k == 0 or alpha == 0: C = beta C
     char *desc = nullptr;             // device copy of ops, gm[0], gm[1], crt, bound
     BatchOperand *ops_dev = nullptr;
@@ -208,11 +208,11 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
         d.m_pad = round_up(q.m, gemm_tile_rows(d.tile));
         d.n_pad = round_up(q.n, gemm_tile_cols(d.tile));
         d.k_pad = round_up(q.k, gemm_kstep_for(d.tile));
-        d.sA = stats_words;
-        stats_words += 2 * (size_t)d.m_pad;  // maxbits, sigma
-        d.sB = stats_words;
-        stats_words += 2 * (size_t)d.n_pad;
-        if (P.accurate) {  // bound maxima X, Y (int32), zeroed with the statistics
+        if (P.accurate) {  // row maxima and bound maxima X, Y (int32)
+            d.sA = stats_words;
+            stats_words += (size_t)d.m_pad;
+            d.sB = stats_words;
+            stats_words += (size_t)d.n_pad;
             d.xA = stats_words;
             stats_words += ((size_t)d.m_pad + 1) / 2;
             d.xB = stats_words;
@@ -243,7 +243,6 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
     P.counter_off = off;  // 8 work-queue counters per product tile size, 1 for the bounds
     off = align_up(off + 4 * (2 * kBatchQueues + 1));
     P.stats_off = off;
-    P.stats_words = stats_words;
     off = align_up(off + 8 * stats_words);
     const size_t mu_off = off;
     off = align_up(off + mu_bytes);
@@ -276,10 +275,6 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
         BatchOperand a{}, b{};
         a.v = view_A(q.A, q.ta, q.m, q.k, q.lda);
         b.v = view_B(q.B, q.tb, q.n, q.k, q.ldb);
-        a.maxbits = (uint64_t *)(uintptr_t)(P.stats_off + 8 * d.sA);
-        a.sigma = (uint64_t *)(uintptr_t)(P.stats_off + 8 * (d.sA + d.m_pad));
-        b.maxbits = (uint64_t *)(uintptr_t)(P.stats_off + 8 * d.sB);
-        b.sigma = (uint64_t *)(uintptr_t)(P.stats_off + 8 * (d.sB + d.n_pad));
         a.mu = (int16_t *)(uintptr_t)(mu_off + d.muA);
         b.mu = (int16_t *)(uintptr_t)(mu_off + d.muB);
         a.res = (int8_t *)(uintptr_t)(res_off + d.resA);
@@ -289,6 +284,8 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
         a.k_pad = b.k_pad = d.k_pad;
         a.nmod = b.nmod = d.nmod;
         if (P.accurate) {
+            a.maxbits = (uint64_t *)(uintptr_t)(P.stats_off + 8 * d.sA);
+            b.maxbits = (uint64_t *)(uintptr_t)(P.stats_off + 8 * d.sB);
             a.X = (int32_t *)(uintptr_t)(P.stats_off + 8 * d.xA);
             b.X = (int32_t *)(uintptr_t)(P.stats_off + 8 * d.xB);
             a.bar = (int8_t *)(uintptr_t)(bar_off + d.barA);
@@ -305,11 +302,14 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
             if (P.accurate) {
                 o->blk_ceil7 = P.blk_ceil7;
                 P.blk_ceil7 += batch_ceil7_blocks(o->rows_pad, o->k_pad);
+                o->blk_exp = P.blk_exp;
+                P.blk_exp += batch_exp_blocks(o->rows_pad);
             }
-            o->blk_scan = P.blk_scan;
-            P.blk_scan += batch_scan_blocks(o->v);
-            o->blk_exp = P.blk_exp;
-            P.blk_exp += batch_exp_blocks(o->rows_pad);
+            batch_row_scan_plan(*o);
+            o->blk_rows = P.blk_rows;
+            P.blk_rows += batch_row_scan_blocks(*o);
+            o->blk_finish = P.blk_finish;
+            P.blk_finish += batch_scan_finish_blocks(*o);
             o->blk_split = sr.blocks;
             sr.blocks += batch_split_blocks(o->rows_pad, o->k_pad);
             ++sr.count;
@@ -372,7 +372,7 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
             P.items[t] += (int64_t)((g.nmod + P.group - 1) / P.group) * g.TR * g.TC;
         }
     }
-    bool too_big = P.blk_scan >= ((int64_t)1 << 31) || P.items[0] >= ((int64_t)1 << 32) ||
+    bool too_big = P.blk_rows >= ((int64_t)1 << 31) || P.items[0] >= ((int64_t)1 << 32) ||
                    P.items[1] >= ((int64_t)1 << 32) || P.blk_ceil7 >= ((int64_t)1 << 31) ||
                    P.bound_items >= ((int64_t)1 << 32);
     for (const BatchPlan::Range &r : P.splits) too_big = too_big || r.blocks >= ((int64_t)1 << 31);
@@ -384,12 +384,11 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
 ozc_status_t bind(const ozc_context *h, BatchPlan &P, char *ws) {
     const uintptr_t base = (uintptr_t)ws;
     for (BatchOperand &o : P.ops) {
-        o.maxbits = (uint64_t *)(base + (uintptr_t)o.maxbits);
-        o.sigma = (uint64_t *)(base + (uintptr_t)o.sigma);
         o.mu = (int16_t *)(base + (uintptr_t)o.mu);
         o.res = (int8_t *)(base + (uintptr_t)o.res);
         o.tab = h->tab_dev + (o.nmod - 1);
         if (P.accurate) {
+            o.maxbits = (uint64_t *)(base + (uintptr_t)o.maxbits);
             o.X = (int32_t *)(base + (uintptr_t)o.X);
             o.bar = (int8_t *)(base + (uintptr_t)o.bar);
         }
@@ -477,26 +476,25 @@ ozc_status_t launch_batch(ozc_context *h, BatchState *bs, const BatchPlan &P, ch
                           hipStream_t s, int phases, int group) {
     uint32_t *counters = (uint32_t *)(ws + P.counter_off);
     const int nops = (int)P.ops.size();
-    if (phases & PH_PREP) {
-        OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
-        OZC_TRY(launch_fill_u64((uint64_t *)(ws + P.stats_off), (int64_t)P.stats_words, 0, s));
-        OZC_TRY(launch_batch_scan(P.ops_dev, nops, P.blk_scan, P.single, 0, s));
+    uint32_t *status = (uint32_t *)h->status_dev;
+    constexpr int ncounters = 2 * kBatchQueues + 1;
+    const bool clear = (phases & PH_PREP) && nops > 0;  // the scan clears status and counters
+    if ((phases & PH_PREP) && nops == 0) OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
+    if (clear) {
+        OZC_TRY(launch_batch_row_scan(P.ops_dev, nops, P.blk_rows, P.blk_finish, P.single, P.accurate, status,
+                                      counters, ncounters, s));
         if (P.accurate) {
             OZC_TRY(launch_batch_ceil7(P.ops_dev, nops, P.blk_ceil7, P.single, s));
-            uint32_t *bound_counter = counters + 2 * kBatchQueues;
-            OZC_TRY(launch_fill_u32(bound_counter, 1, 0, s));
-            OZC_TRY(launch_batch_bound(P.bound_dev, (int)P.bound.size(), P.bound_items, bound_counter, s));
-            OZC_TRY(launch_batch_accu_exponents(P.ops_dev, nops, P.blk_exp, (uint32_t *)h->status_dev, s));
-        } else {
-            OZC_TRY(launch_batch_scan(P.ops_dev, nops, P.blk_scan, P.single, 1, s));
-            OZC_TRY(launch_batch_fast_exponents(P.ops_dev, nops, P.blk_exp, (uint32_t *)h->status_dev, s));
+            OZC_TRY(launch_batch_bound(P.bound_dev, (int)P.bound.size(), P.bound_items,
+                                       counters + 2 * kBatchQueues, s));
+            OZC_TRY(launch_batch_accu_exponents(P.ops_dev, nops, P.blk_exp, status, s));
         }
         for (const BatchPlan::Range &r : P.splits)
             OZC_TRY(launch_batch_split(P.ops_dev + r.first, r.count, r.blocks, P.single, P.planes,
-                                       r.param, s));
+                                       r.param, status, s));
     }
     if (phases & PH_GEMM) {
-        OZC_TRY(launch_fill_u32(counters, 2 * kBatchQueues, 0, s));
+        if (!clear) OZC_TRY(launch_fill_u32(counters, 2 * kBatchQueues, 0, s));
         const int tiles[2] = {256, 128};
         for (int t = 0; t < 2; ++t) {
             if (P.items[t] == 0) continue;
@@ -552,6 +550,7 @@ ozc_status_t run_plan(ozc_context *h, BatchState *bs, bool single,
         if (st != OZC_STATUS_SUCCESS) {
             Q->release();
             delete Q;
+            (void)launch_fill_u64(h->status_dev, 1, 0, h->stream);  // nothing ran: no non-finite input met
             return st;
         }
         Q->key = std::move(key);
@@ -761,12 +760,14 @@ ozc_status_t run_vbatched(ozc_context *h, bool single, int count, const ozc_op_t
     OZC_TRY(hipSetDevice(h->device));
     BatchState *bs = state_of(h);
     if (!bs) return OZC_STATUS_ALLOC_FAILED;
-    OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, h->stream));
     h->last = ozc_info_t{};
     h->last.num_moduli = h->nmod;
     h->last.mode = h->mode;
     h->last.algo = h->algo;
-    if (probs.empty()) return OZC_STATUS_SUCCESS;
+    if (probs.empty()) {  // otherwise the plan's launches clear the non-finite flag
+        OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, h->stream));
+        return OZC_STATUS_SUCCESS;
+    }
     st = grid_sizes(h, bs);
     if (st != OZC_STATUS_SUCCESS) return st;
     std::vector<int> Ns(probs.size(), h->nmod);

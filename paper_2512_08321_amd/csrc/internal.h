@@ -203,15 +203,20 @@ hipError_t launch_scale_c(void *C, int64_t m, int64_t n, int64_t ldc, int ek, do
 // block) and then runs the same code as the single-problem kernel.
 struct BatchOperand {       // op(A) rows or op(B) columns of one problem
     OperandView v;
-    uint64_t *maxbits, *sigma;  // rows_pad entries each, zeroed before the scan
-    uint64_t *tau, *zeros;      // scan pass 2 only: predictor statistics (zeroed)
+    uint64_t *maxbits;          // accurate mode and the predictor's scans: row maxima
+    uint64_t *sigma;            // the predictor's scans only, zeroed: integer sums ...
+    uint64_t *tau, *zeros;      // ... and statistics
     int16_t *mu;                // rows_pad
     int8_t *res;                // residue planes, slab-major, rows_pad x k_pad each
     const NTable *tab;          // constants of the problem's moduli count
     int8_t *bar;                // accurate mode: the 3 magnitude planes, slab-major
     int32_t *X;                 // accurate mode: bound-product row maxima (rows_pad, zeroed)
     int64_t rows_pad, k_pad;
-    int64_t blk_scan, blk_exp;  // first block in the scan and exponent grids
+    int64_t blk_scan;           // first block in the predictor's scans
+    int64_t blk_rows, blk_finish;  // first block in the scaling scan and its second launch
+    int64_t blk_exp;            // first block in the accurate-mode exponent grid
+    int64_t scan_chunk;         // scaling scan: k-elements per part
+    int32_t scan_parts;
     int64_t blk_ceil7;          // first block in the magnitude grid (accurate mode)
     int64_t blk_split;          // first block in the grid of its split launch
     int32_t nmod;               // the problem's moduli count
@@ -220,12 +225,18 @@ struct BatchOperand {       // op(A) rows or op(B) columns of one problem
 int64_t batch_scan_blocks(const OperandView &v);
 int64_t batch_exp_blocks(int64_t rows_pad);
 int64_t batch_split_blocks(int64_t rows_pad, int64_t k_pad);
-// pass 0: row maxima; 1: sums of squares; 2: sums of squares and the predictor's
-// statistics (tau, zeros)
+// The predictor's scans: row maxima, or (stats) integer sums and statistics
 hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, bool single,
-                             int pass, hipStream_t s);
-hipError_t launch_batch_fast_exponents(const BatchOperand *ops, int nops, int64_t blocks,
-                                       uint32_t *status, hipStream_t s);
+                             bool stats, hipStream_t s);
+// The scaling scan: exponents (accurate mode: maxima, and the bound maxima cleared) of every
+// operand.  scan_parts and scan_chunk come from batch_row_scan_plan.  Clears the status word
+// (or null) and ncounters counters.
+void batch_row_scan_plan(BatchOperand &op);
+int64_t batch_row_scan_blocks(const BatchOperand &op);
+int64_t batch_scan_finish_blocks(const BatchOperand &op);
+hipError_t launch_batch_row_scan(const BatchOperand *ops, int nops, int64_t blocks, int64_t finish,
+                                 bool single, bool accurate, uint32_t *status, uint32_t *counters,
+                                 int ncounters, hipStream_t s);
 // Accurate mode: magnitudes of every operand, then exponents from maxbits and X.
 int64_t batch_ceil7_blocks(int64_t rows_pad, int64_t k_pad);
 hipError_t launch_batch_ceil7(const BatchOperand *ops, int nops, int64_t blocks, bool single,
@@ -237,7 +248,7 @@ inline int split_words(int abits) { return abits < 32 ? 1 : (abits + 32) / 32; }
 constexpr int kMaxSplitBits = 32 * kMaxSplitWords - 1;
 // abits: the largest bit length of |a'| among the operands (the chunk count of the launch).
 hipError_t launch_batch_split(const BatchOperand *ops, int nops, int64_t blocks, bool single,
-                              int nplanes, int abits, hipStream_t s);
+                              int nplanes, int abits, uint32_t *status, hipStream_t s);
 
 struct BatchGemm {          // one problem of a batched product launch
     const int8_t *A, *B;

@@ -450,6 +450,32 @@ __device__ __forceinline__ void row_scan_body(const RowScan &a, int group, int p
     if (a.parts == 1) scan_finish<EK, ACCU>(a, r0, m, q, tab);
 }
 
+// Rows scanned in several parts: the 16 rows from r0 on, 16 threads per row over the parts.
+template <int EK, bool ACCU>
+__device__ __forceinline__ void scan_combine(const RowScan &w, int64_t r0, const NTable *tab) {
+    __shared__ uint64_t lm[16][kScanRows];
+    __shared__ double lq[16][kScanRows];
+    const int tid = threadIdx.x, rl = tid % kScanRows, pl = tid / kScanRows;
+    uint64_t m = 0;
+    double q = 0.0;
+    if (r0 + rl < w.v.rows) {
+        for (int p = pl; p < w.parts; p += 16) {
+            m = max(m, w.part_max[p * w.rows_pad + r0 + rl]);
+            if constexpr (!ACCU) q += w.part_sq[p * w.rows_pad + r0 + rl];
+        }
+    }
+    lm[pl][rl] = m;
+    lq[pl][rl] = q;
+    __syncthreads();
+    if (tid < kScanRows) {
+        for (int p = 1; p < 16; ++p) {
+            m = max(m, lm[p][tid]);
+            q += lq[p][tid];
+        }
+    }
+    scan_finish<EK, ACCU>(w, r0, m, q, tab);
+}
+
 // ---------------------------------------------------------------- accurate-mode magnitudes
 // Tile of 32 rows x 64 k-elements per block.  Each thread takes 8 elements
 // and writes the 7-bit magnitudes ceil(|x| 2^(5 - e)) of the real and
@@ -679,37 +705,13 @@ __global__ __launch_bounds__(kScanThreads) void pair_row_scan_kernel(RowScan a, 
     row_scan_body<EK, ACCU>(w, blk % w.groups, blk / w.groups, tab);
 }
 
-// Rows scanned in several parts: 16 rows per block, 16 threads per row over the parts.
 // (a side with one part has no blocks here)
 template <int EK, bool ACCU>
 __global__ __launch_bounds__(256) void scan_finish_kernel(RowScan a, RowScan b, int blocksA,
                                                           const NTable *tab) {
-    __shared__ uint64_t lm[16][kScanRows];
-    __shared__ double lq[16][kScanRows];
-    int blk = (int)blockIdx.x;
+    const int blk = (int)blockIdx.x;
     const bool second = blk >= blocksA;
-    if (second) blk -= blocksA;
-    const RowScan &w = second ? b : a;
-    const int tid = threadIdx.x, rl = tid % kScanRows, pl = tid / kScanRows;
-    const int64_t r0 = (int64_t)blk * kScanRows;
-    uint64_t m = 0;
-    double q = 0.0;
-    if (r0 + rl < w.v.rows) {
-        for (int p = pl; p < w.parts; p += 16) {
-            m = max(m, w.part_max[p * w.rows_pad + r0 + rl]);
-            if constexpr (!ACCU) q += w.part_sq[p * w.rows_pad + r0 + rl];
-        }
-    }
-    lm[pl][rl] = m;
-    lq[pl][rl] = q;
-    __syncthreads();
-    if (tid < kScanRows) {
-        for (int p = 1; p < 16; ++p) {
-            m = max(m, lm[p][tid]);
-            q += lq[p][tid];
-        }
-    }
-    scan_finish<EK, ACCU>(w, r0, m, q, tab);
+    scan_combine<EK, ACCU>(second ? b : a, (int64_t)(second ? blk - blocksA : blk) * kScanRows, tab);
 }
 // The predictor's scans (maxima, then integer sums with its statistics) of both operands
 // of one call in one launch per pass, blocks of A first, then those of B, each on the grid its own launch would have: one ramp-up and tail per pass
@@ -803,8 +805,8 @@ __host__ __device__ __forceinline__ int64_t scan_grid_y(const OperandView &v) {
     return (v.k + hc - 1) / hc;
 }
 
-// PASS 0: row maxima; 1: sums of squares; 2: sums of squares with the predictor's
-// statistics (BatchOperand::tau, zeros)
+// The predictor's scans.  PASS 0: row maxima; 2: integer sums and statistics
+// (BatchOperand::sigma, tau, zeros)
 template <int EK, int PASS>
 __global__ __launch_bounds__(256) void batch_scan_kernel(const BatchOperand *ops, int nops) {
     const int64_t b = blockIdx.x;
@@ -814,22 +816,50 @@ __global__ __launch_bounds__(256) void batch_scan_kernel(const BatchOperand *ops
     const int64_t bx = lb % gx, by = lb / gx;
     const BatchOperand &op = ops[o];
     if (v.contig_h) {
-        if constexpr (PASS > 0) sigma_contig_body<EK, PASS == 2>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by);
+        if constexpr (PASS > 0) sigma_contig_body<EK, true>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by);
         else maxabs_contig_body<EK>(v, op.maxbits, bx, by);
     } else {
         if constexpr (PASS > 0)
-            sigma_strided_body<EK, PASS == 2>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by, kHChunk / 8);
+            sigma_strided_body<EK, true>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by, kHChunk / 8);
         else maxabs_strided_body<EK>(v, op.maxbits, bx, by, kHChunk / 8);
     }
 }
 
-__global__ __launch_bounds__(256) void batch_fast_exponents_kernel(const BatchOperand *ops, int nops,
-                                                                   uint32_t *status) {
+__device__ __forceinline__ RowScan row_scan_of(const BatchOperand &op) {
+    RowScan w;
+    w.v = op.v;
+    w.rows_pad = op.rows_pad;
+    w.chunk = op.scan_chunk;
+    w.parts = op.scan_parts;
+    w.groups = (int32_t)(op.rows_pad / kScanRows);
+    w.part_max = (uint64_t *)op.res;  // free until the split
+    w.part_sq = (double *)(w.part_max + op.scan_parts * op.rows_pad);
+    w.mu = op.mu;
+    w.maxbits = op.maxbits;
+    w.X = op.X;
+    return w;
+}
+// Also clears the status word (null: not) and `ncounters` work-queue counters of the
+// kernels that follow.
+template <int EK, bool ACCU>
+__global__ __launch_bounds__(kScanThreads) void batch_row_scan_kernel(const BatchOperand *ops, int nops,
+                                                                      uint32_t *status, uint32_t *counters,
+                                                                      int ncounters) {
+    if (blockIdx.x == 0) {
+        if (status && threadIdx.x == 0) *status = 0;
+        if ((int)threadIdx.x < ncounters) counters[threadIdx.x] = 0;
+    }
     const int64_t b = blockIdx.x;
-    const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_exp; });
-    const BatchOperand &op = ops[o];
-    fast_exponents_body(op.maxbits, op.sigma, op.v.rows, op.rows_pad, op.tab, op.mu, status,
-                        b - op.blk_exp);
+    const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_rows; });
+    const RowScan w = row_scan_of(ops[o]);
+    const int lb = (int)(b - ops[o].blk_rows);
+    row_scan_body<EK, ACCU>(w, lb % w.groups, lb / w.groups, ops[o].tab);
+}
+template <int EK, bool ACCU>
+__global__ __launch_bounds__(256) void batch_scan_finish_kernel(const BatchOperand *ops, int nops) {
+    const int64_t b = blockIdx.x;  // an operand scanned in one part has no blocks here
+    const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_finish; });
+    scan_combine<EK, ACCU>(row_scan_of(ops[o]), (b - ops[o].blk_finish) * kScanRows, ops[o].tab);
 }
 
 __global__ __launch_bounds__(256) void batch_accu_exponents_kernel(const BatchOperand *ops, int nops,
@@ -854,14 +884,15 @@ __global__ __launch_bounds__(256) void batch_ceil7_kernel(const BatchOperand *op
 
 // Operands of one launch may have different moduli counts; W covers the largest |a'|.
 template <int EK, int NPLANES, int W>
-__global__ __launch_bounds__(256) void batch_split_kernel(const BatchOperand *ops, int nops) {
+__global__ __launch_bounds__(256) void batch_split_kernel(const BatchOperand *ops, int nops,
+                                                          uint32_t *status) {
     const int64_t b = blockIdx.x;
     const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_split; });
     const BatchOperand &op = ops[o];
     const int64_t lb = b - op.blk_split, gx = op.k_pad / kTileH;
     const int64_t bx = lb % gx, by = lb / gx;
     split_body<EK, NPLANES, W>(op.v, op.mu, op.tab, op.nmod, op.res, op.rows_pad, op.k_pad, bx, by,
-                               nullptr);
+                               status);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v) {
@@ -872,12 +903,13 @@ __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v) {
 #define OZC_W_CASES(CASE) CASE(1) CASE(2) CASE(3) CASE(4)
 
 template <int EK, int NPLANES>
-hipError_t batch_split_w(const BatchOperand *ops, int nops, int64_t blocks, int nw, hipStream_t s) {
+hipError_t batch_split_w(const BatchOperand *ops, int nops, int64_t blocks, int nw, uint32_t *status,
+                         hipStream_t s) {
     dim3 grid((unsigned)blocks);
 #define OZC_BSPLIT_CASE(W)                                                                   \
     case W:                                                                                  \
         hipLaunchKernelGGL((batch_split_kernel<EK, NPLANES, W>), grid, dim3(256), 0, s,  \
-                           ops, nops);                                                       \
+                           ops, nops, status);                                               \
         break;
     switch (nw) {
         OZC_W_CASES(OZC_BSPLIT_CASE)
@@ -1112,29 +1144,52 @@ int64_t batch_split_blocks(int64_t rows_pad, int64_t k_pad) {
 }
 
 hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, bool single,
-                             int pass, hipStream_t s) {
+                             bool stats, hipStream_t s) {
     if (blocks <= 0 || nops <= 0) return hipSuccess;
     dim3 grid((unsigned)blocks);
 #define OZC_SCAN(EKV, PV) hipLaunchKernelGGL((batch_scan_kernel<EKV, PV>), grid, dim3(256), 0, s, ops, nops)
-    switch ((single ? 3 : 0) + pass) {
-        case 0: OZC_SCAN(kElemZ, 0); break;
-        case 1: OZC_SCAN(kElemZ, 1); break;
-        case 2: OZC_SCAN(kElemZ, 2); break;
-        case 3: OZC_SCAN(kElemC, 0); break;
-        case 4: OZC_SCAN(kElemC, 1); break;
-        case 5: OZC_SCAN(kElemC, 2); break;
-        default: return hipErrorInvalidValue;
+    if (single) {
+        if (stats) OZC_SCAN(kElemC, 2);
+        else OZC_SCAN(kElemC, 0);
+    } else {
+        if (stats) OZC_SCAN(kElemZ, 2);
+        else OZC_SCAN(kElemZ, 0);
     }
 #undef OZC_SCAN
     return hipGetLastError();
 }
 
-hipError_t launch_batch_fast_exponents(const BatchOperand *ops, int nops, int64_t blocks,
-                                       uint32_t *status, hipStream_t s) {
-    if (blocks <= 0 || nops <= 0) return hipSuccess;
-    hipLaunchKernelGGL(batch_fast_exponents_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ops, nops,
-                       status);
+// As row_scan_of for a single call, on the operand alone: a batch has other blocks to fill
+// the chip with, so only the serial chain of a long row is cut.
+void batch_row_scan_plan(BatchOperand &op) {
+    int64_t parts = 1;
+    if (op.v.k > 64 * kScanLanes) parts = (op.v.k + 2047) / 2048;
+    op.scan_parts = (int32_t)parts;
+    op.scan_chunk = (op.v.k + parts - 1) / parts;
+}
+int64_t batch_row_scan_blocks(const BatchOperand &op) { return op.rows_pad / kScanRows * op.scan_parts; }
+int64_t batch_scan_finish_blocks(const BatchOperand &op) {
+    return op.scan_parts > 1 ? op.rows_pad / kScanRows : 0;
+}
+
+template <int EK, bool ACCU>
+static hipError_t batch_row_scan_ek(const BatchOperand *ops, int nops, int64_t blocks, int64_t finish,
+                                    uint32_t *status, uint32_t *counters, int ncounters, hipStream_t s) {
+    hipLaunchKernelGGL((batch_row_scan_kernel<EK, ACCU>), dim3((unsigned)blocks), dim3(kScanThreads), 0, s,
+                       ops, nops, status, counters, ncounters);
+    if (finish > 0)
+        hipLaunchKernelGGL((batch_scan_finish_kernel<EK, ACCU>), dim3((unsigned)finish), dim3(256), 0, s,
+                           ops, nops);
     return hipGetLastError();
+}
+hipError_t launch_batch_row_scan(const BatchOperand *ops, int nops, int64_t blocks, int64_t finish,
+                                 bool single, bool accurate, uint32_t *status, uint32_t *counters,
+                                 int ncounters, hipStream_t s) {
+    if (blocks <= 0 || nops <= 0 || ncounters > kScanThreads) return hipErrorInvalidValue;
+#define OZC_ARGS ops, nops, blocks, finish, status, counters, ncounters, s
+    if (single) return accurate ? batch_row_scan_ek<kElemC, true>(OZC_ARGS) : batch_row_scan_ek<kElemC, false>(OZC_ARGS);
+    return accurate ? batch_row_scan_ek<kElemZ, true>(OZC_ARGS) : batch_row_scan_ek<kElemZ, false>(OZC_ARGS);
+#undef OZC_ARGS
 }
 
 hipError_t launch_batch_accu_exponents(const BatchOperand *ops, int nops, int64_t blocks,
@@ -1158,15 +1213,15 @@ hipError_t launch_batch_ceil7(const BatchOperand *ops, int nops, int64_t blocks,
 }
 
 hipError_t launch_batch_split(const BatchOperand *ops, int nops, int64_t blocks, bool single,
-                              int nplanes, int abits, hipStream_t s) {
+                              int nplanes, int abits, uint32_t *status, hipStream_t s) {
     if (blocks <= 0 || nops <= 0) return hipSuccess;
     if (abits > kMaxSplitBits) return hipErrorInvalidValue;
     const int nw = split_words(abits);
     if (single)
-        return nplanes == 3 ? batch_split_w<true, 3>(ops, nops, blocks, nw, s)
-                            : batch_split_w<true, 2>(ops, nops, blocks, nw, s);
-    return nplanes == 3 ? batch_split_w<false, 3>(ops, nops, blocks, nw, s)
-                        : batch_split_w<false, 2>(ops, nops, blocks, nw, s);
+        return nplanes == 3 ? batch_split_w<kElemC, 3>(ops, nops, blocks, nw, status, s)
+                            : batch_split_w<kElemC, 2>(ops, nops, blocks, nw, status, s);
+    return nplanes == 3 ? batch_split_w<kElemZ, 3>(ops, nops, blocks, nw, status, s)
+                        : batch_split_w<kElemZ, 2>(ops, nops, blocks, nw, status, s);
 }
 
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s) {
