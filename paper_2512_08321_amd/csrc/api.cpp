@@ -450,8 +450,12 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     // k) are taken over; otherwise one scan reads both operands.  Partial results of rows
     // scanned in several parts go where the residues will be written.
     uint32_t *clear = h->keep_status ? nullptr : status;
+    // Short rows are scanned and split by one launch (the test hook's exponents come between).
+    const bool in_one = h->mode == OZC_MODE_FAST && !pre && !ins && fault == 0 && prep_in_one(k);
     int abits;
-    if (h->mode == OZC_MODE_FAST) {
+    if (in_one) {
+        abits = th.max_abits_fast;
+    } else if (h->mode == OZC_MODE_FAST) {
         if (pre)
             OZC_TRY(launch_pair_fast_exponents(h->pre.maxA, h->pre.sigA, m, L.m_pad, muA, h->pre.maxB,
                                                h->pre.sigB, n, L.n_pad, nuB, tab, status, s));
@@ -477,8 +481,12 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
 
     // Steps IV, V-i/ii: truncation and residues
     OZC_TRY(pe.mark(1));
-    OZC_TRY(launch_pair_split(vA, vB, ek, muA, nuB, tab, h->nmod, L.planes, abits, resA, L.m_pad, resB,
-                              L.n_pad, L.k_pad, status, s));
+    if (in_one)
+        OZC_TRY(launch_pair_prep(vA, vB, ek, muA, nuB, tab, h->nmod, L.planes, abits, resA, L.m_pad, resB,
+                                 L.n_pad, L.k_pad, clear, s));
+    else
+        OZC_TRY(launch_pair_split(vA, vB, ek, muA, nuB, tab, h->nmod, L.planes, abits, resA, L.m_pad, resB,
+                                  L.n_pad, L.k_pad, status, s));
 
     // Step V-iii/iv: INT8 products and their residues
     OZC_TRY(pe.mark(2));
@@ -513,6 +521,7 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
         ca.ldc = ldc;
         ca.single = ek == kElemC;
         ca.ek = ek;
+        ca.status = in_one ? status : nullptr;
         ca.C_lo = ek == kElemZ ? h->dd_lo : nullptr;
         OZC_TRY(launch_crt_output(ca, s));
     }

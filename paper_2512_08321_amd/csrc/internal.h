@@ -56,6 +56,7 @@ struct NTable {
     int32_t accu_thi;             // largest t with 2 * 4^t <= P - 1
     int32_t max_abits_fast;       // bound on the bit length of |a'| in fast mode
     int32_t max_abits_accu;       // ... in accurate mode
+    double inv_fast_thr0;         // 1 / ((P - 1) 2^(2 kSigmaFracBits - 3 - 2 fast_tmax)), the unfloored fast_thr[0]
     uint64_t fast_thr[kThr];      // sigma <= fast_thr[d]  <=>  t = fast_tmax - d admissible
     uint64_t accu_thr[kThr];      // X <= accu_thr[d]      <=>  t = accu_thi - d admissible
     ModConst mod[kMaxModuli];
@@ -124,6 +125,14 @@ hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int e
                              int8_t *resA, int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad,
                              uint32_t *status, hipStream_t s);
 
+// Scan and split of both operands in one launch, where prep_in_one says so (fast mode).
+// Clears the status word (or null) and leaves setting it to the reconstruction.
+bool prep_in_one(int64_t k);
+hipError_t launch_pair_prep(const OperandView &va, const OperandView &vb, int ek, int16_t *mu, int16_t *nu,
+                            const NTable *tab, int nmod, int nplanes, int abits, int8_t *resA,
+                            int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad, uint32_t *status,
+                            hipStream_t s);
+
 struct GemmArgs {
     const int8_t *A;      // [N][planes][k_pad/64][m_pad][64] (slab-major planes)
     const int8_t *B;      // [N][planes][k_pad/64][n_pad][64]
@@ -190,6 +199,7 @@ struct CrtArgs {
     int64_t ldc;
     bool single;           // batched launches: complex64 (else complex128)
     int ek;                // single launches: ElemKind of C (real: alpha_i = beta_i = 0)
+    uint32_t *status;      // or null: bit 0 is set for operands with inf or NaN
     void *C_lo;            // complex128 only: double-double output, C the high parts and
                            // C_lo the low parts (alpha = 1, beta = 0); null otherwise
 };

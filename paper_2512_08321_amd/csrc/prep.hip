@@ -242,8 +242,14 @@ __device__ __forceinline__ bool exponent_from_squares(uint64_t mb, double S, dou
     const double Sp = __builtin_ldexp(S, 2 * (kSigmaFracBits - e));
     const double hi = Sp * (1.0 + 0x1p-30);
     const double up = (hi + 2.0 * __builtin_sqrt(n * hi) + n) * (1.0 + 0x1p-30) + 1.0;
-    const int dl = fast_index((uint64_t)(Sp * (1.0 - 0x1p-30)), ct);
-    const int du = fast_index((uint64_t)up, ct);
+    // index of x >= 2^39: thresholds are X 4^d, so the smallest d >= 0 with x / X <= 4^d, from the
+    // exponent of x / X.  (At an exact power of four one too many; the factors above make that
+    // right for the lower end, whose true value is larger, and safe for the upper one.)
+    auto index = [&](double x) {
+        const int e2 = __builtin_amdgcn_frexp_exp(x * ct->inv_fast_thr0) - 1;  // floor(log2)
+        return e2 >= 0 ? (e2 + 2) >> 1 : 0;
+    };
+    const int dl = index(Sp * (1.0 - 0x1p-30)), du = index(up);
     mu = ct->fast_tmax - dl - e;
     return dl == du;
 }
@@ -619,55 +625,54 @@ __device__ __forceinline__ float smod_u8(float xs, float p, float ip, float rbia
     return __builtin_fmaf(-__builtin_floorf(__builtin_fmaf(xs, ip, rbias)), p, xs);
 }
 
-// status (may be null): bit 0 is set when a row holds inf or NaN.
-template <int EK, int NPLANES, int W>
-__device__ __forceinline__ void split_body(const OperandView &v, const int16_t *__restrict__ mu,
-                                           const NTable *__restrict__ tab, int nmod,
-                                           int8_t *__restrict__ dst, int64_t rows_pad,
-                                           int64_t k_pad, int64_t bx, int64_t by, uint32_t *status) {
-    const int tid = threadIdx.x;
-    constexpr int TPR = kTileH / kEPT;  // threads per row
-    const int rl = tid / TPR;
-    const int oc = tid % TPR;
-    const int64_t r = by * kDirectRows + rl;
-    const int64_t h0 = bx * kTileH + kEPT * oc;
-    const int64_t plane_pitch = rows_pad * k_pad;
-
-    // Rows past the operand (row padding) are not written: they meet only output rows or
-    // columns past the product, which nothing reads.  Padding along k must be zero.
-    if (r >= v.rows) return;
-    const int ex = global_ptr(mu)[r];
-    const bool live = ex != kExpZero && ex != kExpNonfinite;
-    if (status && ex == kExpNonfinite && h0 == 0) atomicOr(status, 1u);
-    int8_t *out = dst + (bx * rows_pad + r) * kTileH + kEPT * oc;
-    if (!live || h0 >= v.k) {  // k padding, or a row without scaling: every residue is 0
-        const int z[kEPT] = {};
-        for (int q = 0; q < nmod * NPLANES; ++q) store_res(out + (int64_t)q * plane_pitch, z);
-        return;
+// kEPT consecutive elements of row r from h0 on, conjugated where the view says so; zeros past k.
+template <int EK>
+__device__ __forceinline__ void load_quad(const OperandView &v, int64_t r, int64_t h0, double *re, double *im) {
+#pragma unroll
+    for (int j = 0; j < kEPT; ++j) {
+        re[j] = im[j] = 0.0;
+        const int64_t h = h0 + j;
+        if (h < v.k) {
+            load_elem<EK>(v.base, r * v.stride_r + h * v.stride_h, re[j], im[j]);
+            if (v.conj) im[j] = -im[j];
+        }
     }
+}
+
+// The residues of kEPT consecutive elements (exponent ex) to out, one word per plane and
+// modulus; elements past k are zeros, whose residues are 0.
+template <int EK, int NPLANES, int W>
+__device__ __forceinline__ void split_quad(const double *re, const double *im, int ex,
+                                           const NTable *__restrict__ tab, int nmod,
+                                           int8_t *__restrict__ out, int64_t plane_pitch) {
     static_assert(NPLANES != 1 || elem_real(EK), "one residue plane for real operands only");
     static_assert(kEPT == 4, "one 4-byte word of residues per plane and modulus");
-    // elements past k (the ragged last slab) enter as zeros, whose residues are 0
     uint32_t uR[kEPT][W], uI[kEPT][W];
 #pragma unroll
     for (int j = 0; j < kEPT; ++j) {
-        double re = 0.0, im = 0.0;
-        const int64_t h = h0 + j;
-        if (h < v.k) {
-            load_elem<EK>(v.base, r * v.stride_r + h * v.stride_h, re, im);
-            if (v.conj) im = -im;
-        }
-        biased_words<W>(re, ex, uR[j]);
-        if constexpr (NPLANES > 1) biased_words<W>(im, ex, uI[j]);
+        biased_words<W>(re[j], ex, uR[j]);
+        if constexpr (NPLANES > 1) biased_words<W>(im[j], ex, uI[j]);
     }
-
-    for (int l = 0; l < nmod; ++l) {
+    // a modulus' constants are loaded while the one before is worked on: with few waves
+    // (short calls) the scalar loads' latency would show once per modulus
+    struct Rule {
+        float p, ip, rb;
+        uint32_t wb[W], bias;
+    };
+    auto rule_of = [&](int l) {
         const OZC_AS_CONST ModConst &mc = const_ptr(tab)->mod[l];
-        const float p = mc.pf, ip = mc.ipf, rb = mc.rbias;
-        uint32_t wb[W];
+        Rule r{mc.pf, mc.ipf, mc.rbias, {}, mc.wbias[W - 1]};
 #pragma unroll
-        for (int i = 0; i < W; ++i) wb[i] = mc.wbyte[i];
-        const uint32_t bias = mc.wbias[W - 1];
+        for (int i = 0; i < W; ++i) r.wb[i] = mc.wbyte[i];
+        return r;
+    };
+    Rule next = rule_of(0);
+    for (int l = 0; l < nmod; ++l) {
+        const Rule cur = next;
+        next = rule_of(min(l + 1, nmod - 1));
+        const float p = cur.p, ip = cur.ip, rb = cur.rb;
+        const uint32_t(&wb)[W] = cur.wb;
+        const uint32_t bias = cur.bias;
         uint32_t wa = 0, wbi = 0, wc = 0;  // residues + 128 as bytes, k ascending
 #pragma unroll
         for (int j = 0; j < kEPT; ++j) {
@@ -686,6 +691,137 @@ __device__ __forceinline__ void split_body(const OperandView &v, const int16_t *
         store_word(o, wa ^ 0x80808080u);
         if constexpr (NPLANES > 1) store_word(o + plane_pitch, wbi ^ 0x80808080u);
         if constexpr (NPLANES == 3) store_word(o + 2 * plane_pitch, wc ^ 0x80808080u);
+    }
+}
+
+// k padding, or a row without scaling: every residue is 0.
+template <int NPLANES>
+__device__ __forceinline__ void split_zeros(int nmod, int8_t *__restrict__ out, int64_t plane_pitch) {
+    const int z[kEPT] = {};
+    for (int q = 0; q < nmod * NPLANES; ++q) store_res(out + (int64_t)q * plane_pitch, z);
+}
+
+// status (may be null): bit 0 is set when a row holds inf or NaN.
+template <int EK, int NPLANES, int W>
+__device__ __forceinline__ void split_body(const OperandView &v, const int16_t *__restrict__ mu,
+                                           const NTable *__restrict__ tab, int nmod,
+                                           int8_t *__restrict__ dst, int64_t rows_pad,
+                                           int64_t k_pad, int64_t bx, int64_t by, uint32_t *status) {
+    const int tid = threadIdx.x;
+    constexpr int TPR = kTileH / kEPT;  // threads per row
+    const int rl = tid / TPR;
+    const int oc = tid % TPR;
+    const int64_t r = by * kDirectRows + rl;
+    const int64_t h0 = bx * kTileH + kEPT * oc;
+
+    // Rows past the operand (row padding) are not written: they meet only output rows or
+    // columns past the product, which nothing reads.  Padding along k must be zero.
+    if (r >= v.rows) return;
+    const int ex = global_ptr(mu)[r];
+    if (status && ex == kExpNonfinite && h0 == 0) atomicOr(status, 1u);
+    int8_t *out = dst + (bx * rows_pad + r) * kTileH + kEPT * oc;
+    if (ex == kExpZero || ex == kExpNonfinite || h0 >= v.k) {
+        split_zeros<NPLANES>(nmod, out, rows_pad * k_pad);
+        return;
+    }
+    double re[kEPT], im[kEPT];
+    load_quad<EK>(v, r, h0, re, im);
+    split_quad<EK, NPLANES, W>(re, im, ex, tab, nmod, out, rows_pad * k_pad);
+}
+
+// One operand of a single call's split, or of its scan and split in one.
+struct SplitSide {
+    OperandView v;
+    const int16_t *mu;
+    int8_t *dst;
+    int64_t rows_pad;
+    uint32_t blocks;  // split: (k_pad / 64) x (rows_pad / kDirectRows); in one: rows_pad / RB
+    int16_t *mu_out;  // in one: exponents
+};
+
+// ---------------------------------------------------------------- scan and split in one
+// Rows of at most kPrepMaxK elements: a block reads RB rows into registers, decides their
+// exponents and splits them, one launch for both operands.  64 threads per row, each with two
+// runs of 4 consecutive k, one in each half of up to eight 64-wide k-slabs; RB is blockDim / 64.
+// Calls this short are chains of launches that the chip waits for: what bounds them is the
+// latency of each, about 7 us a launch.  ZGEMM 64^3 24.4 -> 20.7 us, 256^3 29.9 -> 26.3 us
+// against the scan and the split in two launches; from 16 rows x 256 blocks on 16 rows share a
+// block (CGEMM 4096 x 4096 x 512 at N = 6: 352 us with 4 rows, 341 with 16, 344 in two launches);
+// longer rows are no faster in one launch (1000^3 113 against 107 us: too few waves per block).
+constexpr int kPrepMaxK = 512;
+template <int EK, int NPLANES, int W>
+__device__ __forceinline__ void prep_rows_body(const SplitSide &w, int64_t r0, int64_t k_pad,
+                                               const NTable *__restrict__ tab, int nmod) {
+    constexpr int kMaxRB = 16;
+    __shared__ uint64_t lm[4][kMaxRB], lx[4][kMaxRB];
+    __shared__ double lq[4][kMaxRB];
+    const OperandView &v = w.v;
+    const int RB = blockDim.x / 64, tid = threadIdx.x;
+    const int oc = tid % 16, rl = tid / 16 % RB, part = tid / 16 / RB;  // part: every fourth slab
+    const int64_t r = r0 + rl;
+    const int slabs = (int)(k_pad / kTileH);
+    const bool inside = r < v.rows;
+    uint64_t m = 0;
+    double q = 0.0;
+    double re[2][kEPT], im[2][kEPT];  // slabs part and part + 4
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int64_t h0 = (int64_t)(part + 4 * t) * kTileH + kEPT * oc;
+        load_quad<EK>(v, r, inside ? h0 : v.k, re[t], im[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int j = 0; j < kEPT; ++j) {
+            m = max(m, max(abs_bits(re[t][j]), abs_bits(im[t][j])));
+            q = fma(re[t][j], re[t][j], q);
+            if constexpr (!elem_real(EK)) q = fma(im[t][j], im[t][j], q);
+        }
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+        m = max(m, __shfl_xor(m, off, 64));
+        q += __shfl_xor(q, off, 64);
+    }
+    if (oc == 0) {
+        lm[part][rl] = m;
+        lq[part][rl] = q;
+    }
+    __syncthreads();
+    m = max(max(lm[0][rl], lm[1][rl]), max(lm[2][rl], lm[3][rl]));
+    q = (lq[0][rl] + lq[1][rl]) + (lq[2][rl] + lq[3][rl]);
+    const OZC_AS_CONST NTable *ct = const_ptr(tab);
+    int ex = kExpZero;
+    bool open = false;
+    if (inside) {
+        if (m >= kInfBits) ex = kExpNonfinite;
+        else if (m != 0)
+            open = !exponent_from_squares(m, q, (double)(elem_real(EK) ? v.k : 2 * v.k), ct, ex);
+    }
+    if (__syncthreads_or(open)) {  // rows that need their integer sum
+        uint64_t x = open ? exact_sigma_part<EK>(v, r, m, part * 16 + oc, 64) : 0;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (oc == 0) lx[part][rl] = x;
+        __syncthreads();
+        if (open) {
+            x = (lx[0][rl] + lx[1][rl]) + (lx[2][rl] + lx[3][rl]);
+            ex = ct->fast_tmax - fast_index(x, ct) - ilogb_bits(m);
+        }
+    }
+    if (r >= w.rows_pad) return;
+    if (oc == 0 && part == 0) w.mu_out[r] = (int16_t)ex;
+    if (!inside) return;
+    const bool live = ex != kExpZero && ex != kExpNonfinite;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int sl = part + 4 * t;
+        if (sl >= slabs) break;
+        int8_t *out = w.dst + (sl * w.rows_pad + r) * kTileH + kEPT * oc;
+        if (live && sl * kTileH + kEPT * oc < v.k)
+            split_quad<EK, NPLANES, W>(re[t], im[t], ex, tab, nmod, out, w.rows_pad * k_pad);
+        else
+            split_zeros<NPLANES>(nmod, out, w.rows_pad * k_pad);
     }
 }
 
@@ -757,13 +893,6 @@ __global__ __launch_bounds__(256) void pair_fast_exponents_kernel(ExpSide a, Exp
     else fast_exponents_body(b.maxbits, b.sigma, b.rows, b.rows_pad, tab, b.mu, status, blk - a.blocks);
 }
 // The residues of both operands of one call in one launch (the blocks of A first).
-struct SplitSide {
-    OperandView v;
-    const int16_t *mu;
-    int8_t *dst;
-    int64_t rows_pad;
-    uint32_t blocks;  // (k_pad / 64) x (rows_pad / kDirectRows)
-};
 template <int EK, int NPLANES, int W>
 __global__ __launch_bounds__(256) void pair_split_kernel(SplitSide a, SplitSide b,
                                                          const NTable *__restrict__ tab, int nmod,
@@ -775,6 +904,17 @@ __global__ __launch_bounds__(256) void pair_split_kernel(SplitSide a, SplitSide 
     const uint32_t gx = (uint32_t)(k_pad / kTileH);
     split_body<EK, NPLANES, W>(w.v, w.mu, tab, nmod, w.dst, w.rows_pad, k_pad, blk % gx, blk / gx,
                                status);
+}
+
+template <int EK, int NPLANES, int W>
+__global__ __launch_bounds__(1024) void pair_prep_kernel(SplitSide a, SplitSide b,
+                                                         const NTable *__restrict__ tab, int nmod,
+                                                         int64_t k_pad, uint32_t *status) {
+    uint32_t blk = blockIdx.x;
+    if (status && blk == 0 && threadIdx.x == 0) *status = 0;  // set again by the reconstruction
+    const bool second = blk >= a.blocks;
+    if (second) blk -= a.blocks;
+    prep_rows_body<EK, NPLANES, W>(second ? b : a, (int64_t)blk * (blockDim.x / 64), k_pad, tab, nmod);
 }
 
 template <int EK, bool CONTIG_H>
@@ -920,14 +1060,19 @@ hipError_t batch_split_w(const BatchOperand *ops, int nops, int64_t blocks, int 
     return hipGetLastError();
 }
 
+// threads: 256 for the split, 64 RB for scan and split in one
 template <int EK, int NPLANES>
-hipError_t pair_split_w(const SplitSide &a, const SplitSide &b, const NTable *tab, int nmod, int nw,
-                        int64_t k_pad, uint32_t *status, hipStream_t s) {
-    dim3 grid(a.blocks + b.blocks);
-#define OZC_SPLIT_CASE(W)                                                                    \
-    case W:                                                                                  \
-        hipLaunchKernelGGL((pair_split_kernel<EK, NPLANES, W>), grid, dim3(256), 0, s, a, b, \
-                           tab, nmod, k_pad, status);                                        \
+hipError_t pair_split_w(const SplitSide &a, const SplitSide &b, bool scan, int threads, const NTable *tab,
+                        int nmod, int nw, int64_t k_pad, uint32_t *status, hipStream_t s) {
+    const dim3 grid(a.blocks + b.blocks), block((unsigned)threads);
+#define OZC_SPLIT_CASE(W)                                                                              \
+    case W:                                                                                            \
+        if (scan)                                                                                      \
+            hipLaunchKernelGGL((pair_prep_kernel<EK, NPLANES, W>), grid, block, 0, s, a, b, tab, nmod, \
+                               k_pad, status);                                                         \
+        else                                                                                           \
+            hipLaunchKernelGGL((pair_split_kernel<EK, NPLANES, W>), grid, block, 0, s, a, b, tab,      \
+                               nmod, k_pad, status);                                                   \
         break;
     switch (nw) {
         OZC_W_CASES(OZC_SPLIT_CASE)
@@ -1091,18 +1236,13 @@ hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int6
     return hipGetLastError();
 }
 
-hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int ek, const int16_t *mu,
-                             const int16_t *nu, const NTable *tab, int nmod, int nplanes, int abits,
-                             int8_t *resA, int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad,
-                             uint32_t *status, hipStream_t s) {
+static hipError_t pair_split_ek(const SplitSide &a, const SplitSide &b, bool scan, int threads, int ek,
+                                const NTable *tab, int nmod, int nplanes, int abits, int64_t k_pad,
+                                uint32_t *status, hipStream_t s) {
     if (abits > kMaxSplitBits) return hipErrorInvalidValue;
     const int nw = split_words(abits);
-    if (m_pad % kDirectRows || n_pad % kDirectRows || k_pad % kTileH) return hipErrorInvalidValue;
     if ((nplanes == 1) != elem_real(ek)) return hipErrorInvalidValue;
-    const int64_t blkA = batch_split_blocks(m_pad, k_pad), blkB = batch_split_blocks(n_pad, k_pad);
-    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
-    const SplitSide a{va, mu, resA, m_pad, (uint32_t)blkA}, b{vb, nu, resB, n_pad, (uint32_t)blkB};
-#define OZC_SPLIT_ARGS a, b, tab, nmod, nw, k_pad, status, s
+#define OZC_SPLIT_ARGS a, b, scan, threads, tab, nmod, nw, k_pad, status, s
     switch (ek) {
         case kElemZ: return nplanes == 3 ? pair_split_w<kElemZ, 3>(OZC_SPLIT_ARGS) : pair_split_w<kElemZ, 2>(OZC_SPLIT_ARGS);
         case kElemC: return nplanes == 3 ? pair_split_w<kElemC, 3>(OZC_SPLIT_ARGS) : pair_split_w<kElemC, 2>(OZC_SPLIT_ARGS);
@@ -1111,6 +1251,33 @@ hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int e
         default: return hipErrorInvalidValue;
     }
 #undef OZC_SPLIT_ARGS
+}
+
+hipError_t launch_pair_split(const OperandView &va, const OperandView &vb, int ek, const int16_t *mu,
+                             const int16_t *nu, const NTable *tab, int nmod, int nplanes, int abits,
+                             int8_t *resA, int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad,
+                             uint32_t *status, hipStream_t s) {
+    if (m_pad % kDirectRows || n_pad % kDirectRows || k_pad % kTileH) return hipErrorInvalidValue;
+    const int64_t blkA = batch_split_blocks(m_pad, k_pad), blkB = batch_split_blocks(n_pad, k_pad);
+    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
+    const SplitSide a{va, mu, resA, m_pad, (uint32_t)blkA, nullptr}, b{vb, nu, resB, n_pad, (uint32_t)blkB, nullptr};
+    return pair_split_ek(a, b, false, 256, ek, tab, nmod, nplanes, abits, k_pad, status, s);
+}
+
+bool prep_in_one(int64_t k) { return k <= kPrepMaxK; }
+hipError_t launch_pair_prep(const OperandView &va, const OperandView &vb, int ek, int16_t *mu, int16_t *nu,
+                            const NTable *tab, int nmod, int nplanes, int abits, int8_t *resA,
+                            int64_t m_pad, int8_t *resB, int64_t n_pad, int64_t k_pad, uint32_t *status,
+                            hipStream_t s) {
+    if (va.rows <= 0 || vb.rows <= 0 || va.k <= 0 || va.k > kPrepMaxK || m_pad % kScanRows ||
+        n_pad % kScanRows || k_pad % kTileH)
+        return hipErrorInvalidValue;
+    // 4 rows per block until 16 fill every CU
+    const int RB = va.rows + vb.rows >= 16 * 256 ? 16 : 4;
+    const int64_t blkA = m_pad / RB, blkB = n_pad / RB;
+    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
+    const SplitSide a{va, mu, resA, m_pad, (uint32_t)blkA, mu}, b{vb, nu, resB, n_pad, (uint32_t)blkB, nu};
+    return pair_split_ek(a, b, true, 64 * RB, ek, tab, nmod, nplanes, abits, k_pad, status, s);
 }
 
 template <int EK>

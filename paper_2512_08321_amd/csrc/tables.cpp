@@ -151,6 +151,7 @@ void build_tables(NTable *tables) {
         const int lb = Pm1.bitlen() - 1;  // floor(log2(P - 1))
         // fast mode: t <= P'_fast - 1 with P'_fast = log2(P-1)/2 - 1.5  <=>  2^(2t+5) <= P - 1
         t.fast_tmax = (int)std::floor((lb - 5) / 2.0);
+        t.inv_fast_thr0 = 1.0 / std::ldexp(Pm1.approx(), 2 * kSigmaFracBits - 3 - 2 * t.fast_tmax);
         // accurate mode: 2 * X * 4^t <= P - 1 with X >= 1
         t.accu_thi = (int)std::floor((lb - 1) / 2.0);
         for (int d = 0; d < kThr; ++d) {
