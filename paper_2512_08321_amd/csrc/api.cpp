@@ -492,7 +492,11 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     OZC_TRY(pe.mark(2));
     int8_t *ep_parts = (int8_t *)(ws + L.total);
     GemmArgs ga{resA, resB, L.m_pad, L.n_pad, L.k_pad, h->nmod, galgo, tab, ep, prods, L.tile,
-                ks.l_split, ks.parts, ep_parts};
+                ks.l_split, ks.parts, ep_parts, 0, 0};
+    if (!ins && ks.parts == 1 && choose_64_tiles(L.tile, h->nmod, m, n, L.k_pad, h->cus)) {
+        ga.rows64 = (m + 63) / 64;
+        ga.cols64 = (n + 63) / 64;
+    }
     OZC_TRY(launch_residue_gemm(ga, s));
     if (fault == 1 && h->attempt == 0) OZC_TRY(launch_debug_xor_byte(ep, s));
     OZC_TRY(pe.mark(3));

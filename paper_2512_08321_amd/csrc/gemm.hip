@@ -2,10 +2,10 @@
 // accumulation (Section III-A; Algorithm 1 Step V-iii/iv).
 //
 // One block computes a TM x TN output tile of one modulus l with WM x WN
-// waves; each wave owns (BM*32) x (BN*32) outputs as BM x BN blocks of
-// v_mfma_i32_32x32x32_i8 (large problems: 256 x 256 tiles, 8 waves of
+// waves; each wave owns (BM*16) x (BN*16) outputs as BM x BN blocks of
+// v_mfma_i32_16x16x64_i8 (large problems: 256 x 256 tiles, 8 waves of
 // 128 x 64, two waves per SIMD; small problems: 128 x 128, 4 waves of
-// 64 x 64).  The products of the chosen algorithm run one after another over
+// 64 x 64; calls that leave CUs idle: 64 x 64, 4 waves of 64 x 16).  The products of the chosen algorithm run one after another over
 // the same tile, each as a k-loop over a ring of LDS buffers that the load
 // units fill straight from global memory a few 64-wide k-slabs ahead of the
 // matrix cores (one barrier per k-slab).  Between products
@@ -26,12 +26,12 @@
 // (modulus, tile) sequence, tiles grouped 4 rows at a time, so that the
 // blocks resident on one XCD share A and B panels in that XCD's L2.
 //
-// MFMA operand layout: lane l of a 32x32x32 instruction supplies 16 bytes of
-// row (l mod 32) of the A block and of column (l mod 32) of the B block, at
-// k-offset 16 * (l / 32); both operands use the same k assignment, so the
-// product does not depend on how the hardware orders k inside the 32-wide
-// step.  Accumulator register r of lane l holds row 8(r/4) + 4(l/32) + (r mod 4),
-// column (l mod 32).
+// MFMA operand layout: lane l of a 16x16x64 instruction supplies 16 bytes of
+// row (l mod 16) of the A block and of column (l mod 16) of the B block, at
+// k-offset 16 * (l / 16); both operands use the same k assignment, so the
+// product does not depend on how the hardware orders k inside the 64-wide
+// step.  Accumulator register r of lane l holds row 4(l/16) + r, column
+// (l mod 16).
 #include <algorithm>
 #include <cmath>
 #include <utility>
@@ -42,7 +42,6 @@ namespace ozc {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 64;
 
@@ -77,7 +76,7 @@ struct Plan {
 // Six instructions per output with the packing of four residues into a word; the epilogue
 // is bound by them where k is short.  The rule before, rint(x (1/p)) in FP64, took five FP64
 // ones and two more to pack, and E' went out in 4-byte stores; products then and now, same
-// box: ZGEMM 4096^3 at N = 14 2505 -> 2377 us, 4096 x 4096 x 128 435 -> 301 us, DGEMM 1536 x
+// card: ZGEMM 4096^3 at N = 14 2505 -> 2377 us, 4096 x 4096 x 128 435 -> 301 us, DGEMM 1536 x
 // 2048 x 1000 75 -> 57 us, SGEMM 3000 x 3000 x 700 at N = 8 102 -> 70 us.
 struct ModRule {
     uint32_t wb, bias;
@@ -95,34 +94,27 @@ __device__ __forceinline__ uint32_t put_residue(uint32_t v, const ModRule &r, ui
     return __builtin_amdgcn_cvt_pk_u8_f32(s, U, w);
 }
 
-// A lane of a 32 x 32 block holds one column: rows 8 g + 4 (lane / 32) + 0..3 in word g.
-// v_permlane32_swap exchanges words with lane +- 32 so that each lane has 16 consecutive
-// rows, 16 (lane / 32) + 0..15, and E' moves in 16-byte accesses; it is its own inverse.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x4 rows16(const uint32_t (&w)[4]) {
-    const auto e = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-    const auto f = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-    return u32x4{e[0], e[1], f[0], f[1]};
-}
-__device__ __forceinline__ void rows4(const u32x4 &r, uint32_t (&w)[4]) {
-    const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[1], false, false);
-    const auto f = __builtin_amdgcn_permlane32_swap(r[2], r[3], false, false);
-    w[0] = e[0];
-    w[2] = e[1];
-    w[1] = f[0];
-    w[3] = f[1];
-}
 
 __device__ __forceinline__ int byte_of(uint32_t w, int u) { return (int)(int8_t)(w >> (8 * u)); }
 
-// LDS tile layout: 64-byte rows of four 16-byte granules; granule g of row r is
-// stored at position g ^ sw(r).  With sw(r) = r2 | (r1 ^ r3) << 1 (ri = bit i of
-// r), 8 and 16 consecutive rows read at one granule position hit distinct bank
-// groups (32- and 64-bank LDS), and so do the row-major 16-byte stores.
+// The 64 rows (or columns) of a group of four 16 x 16 blocks are dealt to the blocks so that a
+// lane ends up with 16 consecutive rows of its column: matrix row x of block t is row
+// 16 (x / 4) + 4 t + x mod 4 of the group.  A lane's accumulators of the four blocks (rows
+// 4 (lane / 16) + 0..3 of each) are then rows 16 (lane / 16) + 0..15, in order, and E' moves in
+// 16-byte accesses without any exchange between lanes.
+__device__ __forceinline__ int group_row(int x) { return 16 * (x >> 2) + (x & 3); }
+
+// LDS tile layout: 64-byte rows of four 16-byte granules; granule g of row r is stored at
+// position g ^ sw(r), sw(r) = r5 | (r4 ^ r5 ^ r1) << 1 (ri = bit i of r).  A fragment read takes
+// granule lane / 16 of row group_row(lane mod 16) + 4 t.  128-bit reads are served sixteen
+// lanes at a time, lanes 0-3, 12-15, 20-23 and 24-27 together, then 4-7, 8-11, 16-19 and 28-31,
+// and the same 32 lanes up: each sixteen hit distinct groups of banks (counters: no conflicts;
+// r4 | (r5 ^ r1) << 1, which only tells consecutive lanes apart, has four cycles per read).
 __device__ __forceinline__ int swz_bits(int row) {
-    return ((row >> 2) & 1) | ((((row >> 1) ^ (row >> 3)) & 1) << 1);
+    const int b = row >> 5;
+    return (b & 1) | (((b ^ (row >> 4) ^ (row >> 1)) & 1) << 1);
 }
-__device__ __forceinline__ int swz(int row, int seg) { return row * 4 + (seg ^ swz_bits(row)); }
 
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0..N-1, so that
 // register arrays are only ever indexed by constants.
@@ -157,7 +149,7 @@ __device__ __forceinline__ void map_tile(uint32_t L, uint32_t TR, uint32_t TC, u
     tj = uniform(col);
 }
 
-// WM x WN waves of BM x BN blocks; KS 64-byte k sub-slabs per pipeline stage.
+// WM x WN waves of BM x BN blocks of 16 x 16 outputs; one 64-wide k-slab per pipeline stage.
 // k-slabs are copied global -> LDS by the load units directly (gfx950
 // global_load_lds_dwordx4) into a ring of NSTAGE buffers, NSTAGE - 1 slabs
 // ahead of the matrix cores.  REG_CARRY: the residue carried between the
@@ -166,25 +158,24 @@ __device__ __forceinline__ void map_tile(uint32_t L, uint32_t TR, uint32_t TC, u
 // queued before the current product's epilogue; otherwise each product
 // starts its own ring after the epilogue.  Both pay where k is short (4096^3:
 // 15% faster products); for long k the plain schedule keeps the tiles of an
-// XCD in step (16384^3: L2 hit rate 84% against 65%, 2.6% faster).
-template <int WM_, int WN_, int BM_, int BN_, int KS_, int NSTAGE_, bool REG_CARRY_, bool PREFETCH_>
+// XCD in step (16384^3: L2 hit rate 84% against 65%, 148 against 152 ms; 8192^3 17.75 against
+// 17.35 ms, 4096^3 2459 against 2360 us).
+template <int WM_, int WN_, int BM_, int BN_, int NSTAGE_, bool REG_CARRY_, bool PREFETCH_>
 struct TileCfg {
-    static constexpr int WM = WM_, WN = WN_, BM = BM_, BN = BN_, KS = KS_;
+    static constexpr int WM = WM_, WN = WN_, BM = BM_, BN = BN_;
     static constexpr int NSTAGE = NSTAGE_;
     static constexpr bool REG_CARRY = REG_CARRY_, PREFETCH = PREFETCH_;
-    static constexpr int TM = WM * BM * 32, TN = WN * BN * 32;
+    static constexpr int TM = WM * BM * 16, TN = WN * BN * 16;
     static constexpr int THREADS = 64 * WM * WN;
-    static constexpr int STAGE = (TM + TN) * 4;   // uint4 per sub-slab in LDS
-    static constexpr int KSTEP = BK * KS;
+    static constexpr int STAGE = (TM + TN) * 4;   // uint4 per k-slab in LDS
 };
-using CfgLarge = TileCfg<2, 4, 4, 2, 1, 4, false, false>;  // 256 x 256 output tiles, 512 threads, 128 KB LDS
-using CfgSmall = TileCfg<2, 2, 2, 2, 1, 4, true, true>;    // 128 x 128, 256 threads, 64 KB LDS
+using CfgLarge = TileCfg<2, 4, 8, 4, 4, false, false>;  // 256 x 256 output tiles, 512 threads, 128 KB LDS
+using CfgSmall = TileCfg<2, 2, 4, 4, 4, true, true>;    // 128 x 128, 256 threads, 64 KB LDS
 // 256 x 256 tiles with the short-k schedule: single calls with k_pad < kLongK and batches.
-using CfgLargeShortK = TileCfg<2, 4, 4, 2, 1, 4, true, true>;
-static_assert(CfgLargeShortK::TM == CfgLarge::TM && CfgLargeShortK::TN == CfgLarge::TN &&
-                  CfgLargeShortK::KSTEP == CfgLarge::KSTEP,
+using CfgLargeShortK = TileCfg<2, 4, 8, 4, 4, true, true>;
+static_assert(CfgLargeShortK::TM == CfgLarge::TM && CfgLargeShortK::TN == CfgLarge::TN,
               "both large-tile schedules share the operand padding");
-constexpr int64_t kLongK = 16384;  // measured: short-k faster up to 12288^3, plain at 16384^3
+constexpr int64_t kLongK = 16384;  // short-k faster up to 8192^3, plain at 16384^3 (above)
 
 // One wave copies 64 x 16 bytes from global memory straight into 1 KB of LDS:
 // lane i reads sbase + voff_i + OFF and writes lds_base + OFF + 16 i (the
@@ -218,6 +209,105 @@ __device__ __forceinline__ void vmcnt_wait() {
 }
 __device__ __forceinline__ void block_barrier() { __builtin_amdgcn_s_barrier(); }
 
+// Copies of one k-slab into a ring stage: each wave fills whole 1 KB chunks (16 rows) of the
+// A and B parts.  Lane i of a chunk writes LDS granule i, i.e. row 16 c + i / 4 at position
+// i mod 4, which holds the swizzled global granule (i mod 4) ^ swz_bits(row).
+template <int TM, int TN, int NW>
+struct SlabCopy {
+    static constexpr int QA = TM / 16 / NW, QB = TN / 16 / NW, NLOAD = QA + QB;  // loads per wave
+    static_assert(TM / 16 % NW == 0 && TN / 16 % NW == 0 && QA <= 4 && QB <= 4, "chunks per wave");
+    uint32_t va[QA], vb[QB];  // per-lane global offsets (without the instruction offset), fixed
+    uint32_t la, lb;          // the wave's first chunk in a stage
+    __device__ __forceinline__ SlabCopy(int wv, int lane) {
+        const int crow = lane >> 2;
+        static_for<QA>([&](auto q) {
+            const int row = (wv * QA + q) * 16 + crow;
+            va[q] = (uint32_t)(wv * QA * 1024 + crow * BK + ((lane & 3) ^ swz_bits(row)) * 16);
+        });
+        static_for<QB>([&](auto q) {
+            const int row = (wv * QB + q) * 16 + crow;
+            vb[q] = (uint32_t)(wv * QB * 1024 + crow * BK + ((lane & 3) ^ swz_bits(row)) * 16);
+        });
+        la = (uint32_t)(wv * QA * 1024);
+        lb = (uint32_t)(TM * 64 + wv * QB * 1024);
+    }
+    __device__ __forceinline__ void issue(const int8_t *sa, const int8_t *sb, uint32_t stage) const {
+        static_for<QA>([&](auto q) { dma16<q * 1024>(sa, va[q], stage + la); });
+        static_for<QB>([&](auto q) { dma16<q * 1024>(sb, vb[q], stage + lb); });
+    }
+};
+
+// A wave's share of a product, BM x BN blocks of v_mfma_i32_16x16x64_i8 per k-slab, one
+// instruction's k.  That instruction at random operands reaches 4060 TOP/s on registers where
+// the 32 x 32 x 32 one reaches 3460 (both 4.85 POP/s on zeros): the chip runs at its power limit
+// here, and half as many accumulator updates per multiply-add toggle less.
+// Fragments are single-buffered: a block row's A fragment is read again, for the next slab,
+// right behind its last use, and the B fragments behind theirs in the last two block rows,
+// so each has most of a slab to arrive and no copy of it is held.
+// Against 32 x 32 x 32 instructions on the same tiles (fragments of half slabs in two sets,
+// the barrier between the halves), products, same card: ZGEMM N = 14 2048^3 361 -> 348 us, 4096^3
+// 2430 -> 2310 us, 8192^3 19260 -> 17780 us, 16384^3 151.0 -> 138.8 ms (2660 TOP/s); N = 13
+// 2048^3 336 -> 320 us; 128 x 128 tiles, 1000 x 900 x 1100 65.7 -> 62.0 us, DGEMM 900 x 900 x 4096
+// 70.6 -> 66.2 us.  With the barrier ahead of the slab's first matrix instruction 16384^3 takes
+// 148 ms, with a fifth buffer 140 ms (4096^3 2410 us).
+template <int BM, int BN>
+struct WaveTile {
+    static_assert(BM % 4 == 0 && BM >= 4 && (BN == 4 || BN == 1), "groups of four blocks");
+    v4i fa[BM], fb[BN];
+    const int loff;  // the lane's granule of block 0: the others are at fixed distances, since
+                     // their rows differ in bits that the swizzle does not use
+    __device__ __forceinline__ explicit WaveTile(int lane)
+        : loff(group_row(lane & 15) * 4 + ((lane >> 4) ^ swz_bits(group_row(lane & 15)))) {}
+    // fragment b of the wave's rows (columns) in the stage part at `base`
+    __device__ __forceinline__ v4i frag(const uint4 *base, int b) const {
+        const uint4 t = base[loff + (64 * (b >> 2) + 4 * (b & 3)) * 4];
+        return v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+    }
+    __device__ __forceinline__ void read_all(const uint4 *A, const uint4 *B) {
+        static_for<BN>([&](auto j) { fb[j] = frag(B, j); });
+        static_for<BM>([&](auto i) { fa[i] = frag(A, i); });
+    }
+    // acc += this slab; the fragments of the next slab from A, B (behind the last slab the
+    // ring's next buffer: unused).  meet() waits until that
+    // slab is there for all waves: behind the first block row, so that the waves meet with
+    // matrix instructions queued.
+    template <typename Meet>
+    __device__ __forceinline__ void slab(v4i (&acc)[BM][BN], const uint4 *A, const uint4 *B, Meet meet) {
+        auto mfma = [&](auto i, auto j) {
+            acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        };
+        static_for<BM - 2>([&](auto i) {
+            static_for<BN>([&](auto j0) {
+                constexpr int j = (i & 1) ? BN - 1 - j0 : (int)j0;
+                mfma(i, std::integral_constant<int, j>{});
+            });
+            if constexpr (i == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                meet();
+            }
+            fa[i] = frag(A, i);
+        });
+        static_for<BN>([&](auto j) {
+            mfma(std::integral_constant<int, BM - 2>{}, j);
+            mfma(std::integral_constant<int, BM - 1>{}, j);
+            fb[j] = frag(B, j);
+        });
+        fa[BM - 2] = frag(A, BM - 2);
+        fa[BM - 1] = frag(A, BM - 1);
+        // the order written above: the scheduler would gather the reads
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        static_for<BM - 3>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x008, BN, 0);  // matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
+        });
+        static_for<BN>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        });
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+};
+
 // One output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + nk - 1: all products of
 // the plan and their epilogues, E' to the modulus' planes at ep.
 // Ends with a block barrier, so a caller may run the next tile right away.
@@ -225,12 +315,13 @@ template <int KIND, typename C, bool DUMP>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b, int8_t *ep, int l,
                                           int64_t ti, int64_t tj, int s0, int nk) {
     using P = Plan<KIND>;
-    constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN, KS = C::KS;
-    constexpr int WTM = BM * 32, WTN = BN * 32;  // wave tile
-    __shared__ uint4 lds[C::NSTAGE][KS * C::STAGE];  // [buffer][sub-slab][A rows, B rows]
+    constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN;
+    constexpr int WTM = BM * 16, WTN = BN * 16;  // wave tile
+    __shared__ uint4 lds[C::NSTAGE][C::STAGE];   // [buffer][A rows, B rows]
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % C::WM, wn = wave / C::WM;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wv % C::WM, wn = wv / C::WM;
 
     constexpr bool bound = P::bound;
     const int64_t m_pad = bound ? b.m_pad : a.m_pad;
@@ -241,48 +332,31 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
     // planes are slab-major: k-slab s (64 wide) of a plane is m_pad x 64 bytes at s * slabA
     const int64_t planeA = m_pad * k_pad, planeB = n_pad * k_pad;
     const int64_t slabA = m_pad * BK, slabB = n_pad * BK;
-    static_assert(C::KS == 1, "one k-slab per ring stage");
-    const int8_t *baseA = (bound ? b.A : a.A) + (int64_t)l * P::nplanes * planeA + i0 * BK + s0 * slabA;
-    const int8_t *baseB = (bound ? b.B : a.B) + (int64_t)l * P::nplanes * planeB + j0 * BK + s0 * slabB;
+    const int8_t *baseA =
+        uniform_ptr((bound ? b.A : a.A) + (int64_t)l * P::nplanes * planeA + i0 * BK + s0 * slabA);
+    const int8_t *baseB =
+        uniform_ptr((bound ? b.B : a.B) + (int64_t)l * P::nplanes * planeB + j0 * BK + s0 * slabB);
 
     ModRule rule{};
     if constexpr (!bound) rule = mod_rule(a.tab, l);
     constexpr int bias = bound || DUMP ? 0 : kAccBias;  // accumulators' start
     const int64_t planeC = bound ? 0 : a.n_pad * a.m_pad;
 
-    // Each wave fills whole 1 KB chunks (16 rows) of the A and B slabs: lane i of a
-    // chunk writes LDS granule i, i.e. row 16c + i/4 at position i mod 4, which holds
-    // the swizzled global granule (i mod 4) ^ swz_bits(row).  A ring stage holds KS
-    // consecutive 64-wide k-slabs.
-    constexpr int CA = TM / 16, CB = TN / 16, NW = C::WM * C::WN;
-    static_assert(CA % NW == 0 && CB % NW == 0, "chunks per wave");
-    // a stage is waited for one stage before it is consumed and issued AHEAD >= 2
-    // stages ahead, so its buffer was released by the barrier of the stage before
+    using Copy = SlabCopy<TM, TN, C::WM * C::WN>;
+    const Copy copy(wv, lane);
+    constexpr int NLOAD = Copy::NLOAD;
+    // a slab is waited for one slab before it is used, while the one before it is computed and
+    // its fragments are read, and queued AHEAD slabs ahead of its use
     static_assert(C::NSTAGE >= 3, "DMA ring needs at least three buffers");
-    constexpr int QA = CA / NW, QB = CB / NW, NLOAD = KS * (QA + QB);  // loads per wave per stage
-    static_assert(QA <= 4 && QB <= 4, "chunk offsets must fit the instruction offset");
-    constexpr int AHEAD = C::NSTAGE - 1, NH = 2 * KS;
-    const int crow = lane >> 2;
-    const int cg = (lane & 3) ^ swz_bits(crow);  // chunk rows start at multiples of 16
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    // per-lane offsets inside the wave's first chunk (same for every stage and product)
-    const uint32_t voffA = (uint32_t)(wv * QA * 1024 + crow * BK + cg * 16);
-    const uint32_t voffB = (uint32_t)(wv * QB * 1024 + crow * BK + cg * 16);
+    constexpr int AHEAD = C::NSTAGE - 1;
     const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)(&lds[0][0]);
     // plane bases of product g (wave-uniform)
     auto pa_of = [&](int g) { return uniform_ptr(baseA + (int64_t)P::pa(g) * planeA); };
     auto pb_of = [&](int g) { return uniform_ptr(baseB + (int64_t)P::pb(g) * planeB); };
-    auto issue_from = [&](const int8_t *sa, const int8_t *sb_, int st) {  // stage st -> buffer st % NSTAGE
-        const uint32_t buf = lbase + (uint32_t)((st % C::NSTAGE) * KS * C::STAGE * 16);
-        static_for<KS>([&](auto ks) {
-            const int64_t ks_idx = (int64_t)st * KS + ks;
-            const uint32_t la = buf + (uint32_t)(ks * C::STAGE * 16 + wv * QA * 1024);
-            const uint32_t lb = buf + (uint32_t)(ks * C::STAGE * 16 + TM * 64 + wv * QB * 1024);
-            static_for<QA>([&](auto q) { dma16<q * 1024>(sa + ks_idx * slabA, voffA, la); });
-            static_for<QB>([&](auto q) { dma16<q * 1024>(sb_ + ks_idx * slabB, voffB, lb); });
-        });
+    auto issue_from = [&](const int8_t *sa, const int8_t *sb_, int st) {  // slab st -> buffer st % NSTAGE
+        copy.issue(sa + st * slabA, sb_ + st * slabB, lbase + (uint32_t)((st % C::NSTAGE) * C::STAGE * 16));
     };
-    // The first AHEAD stages of a product.  Those of product g + 1 are issued right
+    // The first AHEAD slabs of a product.  Those of product g + 1 are issued right
     // after product g's last barrier, so they load while g's epilogue runs.
     auto issue_first = [&](int g) {
         const int8_t *sa = pa_of(g), *sb_ = pb_of(g);
@@ -290,108 +364,49 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             if (st < nk) issue_from(sa, sb_, st);
         });
     };
+    auto partA = [&](int st) { return lds[st % C::NSTAGE] + wm * WTM * 4; };
+    auto partB = [&](int st) { return lds[st % C::NSTAGE] + (TM + wn * WTN) * 4; };
 
-    v16i acc[BM][BN];
-    uint32_t cw[BM][BN][4];  // packed carry residues (kept here, or reloaded from E'_I)
+    v4i acc[BM][BN];
+    uint32_t cw[BM][BN];  // packed carry residues (kept here, or reloaded from E'_I)
     if constexpr (C::PREFETCH) issue_first(0);
 
 #pragma unroll 1
     for (int sgi = 0; sgi < P::nseg; ++sgi) {
         if (!bound || sgi == 0) {
-            static_for<BM>([&](auto bi) { static_for<BN>([&](auto bj) { acc[bi][bj] = (v16i)bias; }); });
+            static_for<BM>([&](auto bi) { static_for<BN>([&](auto bj) { acc[bi][bj] = (v4i)bias; }); });
         }
-        // Fragments of one 32-wide half (kk) of a 64-wide k-slab held in LDS buffer Lbuf.
-        auto read_frags = [&](const uint4 *Lbuf, int kk, v4i (&fa)[BM], v4i (&fb)[BN]) {
-            // fragment rows are (multiple of 32) + (lane mod 32): the swizzle depends on the lane only
-            const int g = (kk * 2 + (lane >> 5)) ^ swz_bits(lane & 31);
-            const uint4 *FA = Lbuf + (wm * WTM + (lane & 31)) * 4 + g;
-            const uint4 *FB = Lbuf + TM * 4 + (wn * WTN + (lane & 31)) * 4 + g;
-            // issue order B0 A0 B1 A1 A2 ...: the MFMAs (A-block outer, B-block inner) can
-            // start after the first two reads and consume the rest as they arrive
-            constexpr int NR = BM > BN ? BM : BN;
-            static_for<NR>([&](auto i) {
-                if constexpr (i < BN) {
-                    const uint4 t = FB[i * 32 * 4];
-                    fb[i] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
-                }
-                if constexpr (i < BM) {
-                    const uint4 t = FA[i * 32 * 4];
-                    fa[i] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
-                }
-            });
-        };
-        auto mfmas = [&](const v4i (&fa)[BM], const v4i (&fb)[BN]) {
-            static_for<BM>([&](auto bi) {
-                static_for<BN>([&](auto bj) {
-                    acc[bi][bj] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[bi], fb[bj], acc[bi][bj], 0, 0, 0);
-                });
-            });
-        };
         {
             const int8_t *sa = pa_of(sgi), *sb_ = pb_of(sgi);
-            auto issue = [&](int st) { issue_from(sa, sb_, st); };
-            // Software pipeline over half-slabs (32-wide k): the fragments of the next half
-            // are read while the current half's matrix instructions run.  The one barrier
-            // per stage sits before the last half's MFMAs, after the wait for the next
-            // stage, so queued MFMAs keep the matrix pipe busy while the waves meet; after
-            // it the oldest buffer is free and receives the stage AHEAD steps ahead.
-            // stages 1 .. AHEAD-1 may stay in flight, except when this product's first
-            // stages were queued before the previous epilogue's stores: then wait for all
+            // slabs 1 .. AHEAD-1 may stay in flight, except when this product's first
+            // slabs were queued before the previous epilogue's stores: then wait for all
             if constexpr (!C::PREFETCH) issue_first(sgi);
             const bool fresh = !C::PREFETCH || sgi == 0;
             if (fresh && nk > 2 && AHEAD >= 3) vmcnt_wait<2 * NLOAD>();
             else if (fresh && nk > 1 && AHEAD >= 2) vmcnt_wait<NLOAD>();
             else vmcnt_wait<0>();
             block_barrier();
-            v4i fa[2][BM], fb[2][BN];
-            read_frags(lds[0], 0, fa[0], fb[0]);
-            // The fragment reads of the next half are interleaved with this half's matrix
-            // instructions (MFMA, read, MFMA, read, ...) so that they are all in flight
-            // early; otherwise the scheduler tends to sink them behind the MFMAs and the
-            // LDS latency shows at the start of the next half.
-            auto interleave = [&]() {
-                static_for<BM + BN>([&](auto) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-                });
-                __builtin_amdgcn_sched_group_barrier(0x008, BM * BN - (BM + BN), 0);
-            };
-            static_assert(BM * BN >= BM + BN, "interleave needs an MFMA per fragment read");
-            // HANDOVER: wait for stage s+1 (WAIT loads of later stages may stay in flight),
-            // then ISSUE stage s + AHEAD into the buffer released by the barrier.
-            auto stage = [&](int s, auto handover_tag, auto issue_tag, auto wait_tag) {
-                constexpr bool HANDOVER = decltype(handover_tag)::value;
-                constexpr bool ISSUE = decltype(issue_tag)::value;
-                const uint4 *cur = lds[s % C::NSTAGE];
-                static_for<NH>([&](auto h) {
-                    constexpr int nb = (h + 1) & 1;
-                    if constexpr (h + 1 < NH) {
-                        read_frags(cur + ((h + 1) / 2) * C::STAGE, (h + 1) & 1, fa[nb], fb[nb]);
-                        mfmas(fa[h & 1], fb[h & 1]);
-                        interleave();
-                    } else if constexpr (HANDOVER) {
-                        vmcnt_wait<decltype(wait_tag)::value>();
-                        block_barrier();  // stage s+1 visible; stage s-1's buffer free
-                        if constexpr (ISSUE) issue(s + AHEAD);
-                        read_frags(lds[(s + 1) % C::NSTAGE], 0, fa[0], fb[0]);
-                        mfmas(fa[h & 1], fb[h & 1]);
-                        interleave();
-                    } else {
-                        mfmas(fa[h & 1], fb[h & 1]);
-                    }
-                });
-            };
-            using T = std::true_type;
-            using F = std::false_type;
-            // stages issued after stage s+1 when it is awaited: min(AHEAD - 2, nk - 2 - s)
+            WaveTile<BM, BN> wt(lane);
+            wt.read_all(partA(0), partB(0));
+            // At the last slab the fragments read ahead are not used.
             constexpr int LATER = AHEAD >= 2 ? AHEAD - 2 : 0;
-            using WL = std::integral_constant<int, LATER * NLOAD>;
-            using W0 = std::integral_constant<int, 0>;
-            int s = 0;
-            for (; s + AHEAD < nk; ++s) stage(s, T{}, T{}, WL{});
-            for (; s + 1 + LATER < nk; ++s) stage(s, T{}, F{}, WL{});
-            for (; s + 1 < nk; ++s) stage(s, T{}, F{}, W0{});
-            stage(s, F{}, F{}, W0{});
+            const int main_end = max(nk - AHEAD, 0);
+#pragma unroll 1
+            for (int s = 0; s < main_end; ++s) {
+                wt.slab(acc, partA(s + 1), partB(s + 1), [&]() {
+                    vmcnt_wait<LATER * NLOAD>();
+                    block_barrier();  // slab s+1 visible; slab s-1's buffer free
+                    issue_from(sa, sb_, s + AHEAD);
+                });
+            }
+#pragma unroll 1
+            for (int s = main_end; s < nk; ++s) {
+                wt.slab(acc, partA(s + 1), partB(s + 1), [&]() {
+                    if (s + 1 + LATER < nk) vmcnt_wait<LATER * NLOAD>();
+                    else vmcnt_wait<0>();
+                    block_barrier();
+                });
+            }
             block_barrier();  // all waves done with the ring before it is refilled
         }
 
@@ -404,21 +419,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
         // Parked carries are loaded and awaited first; then the next product's first
         // stages are queued, so that their copies overlap the rest of this epilogue.
         constexpr bool karatsuba = KIND == KIND_KARATSUBA;
-        auto e16 = [&](int8_t *E, int bi, int bj) {
-            const int64_t i = i0 + wm * WTM + bi * 32 + 16 * (lane >> 5);
-            const int64_t j = j0 + wn * WTN + bj * 32 + (lane & 31);
-            return reinterpret_cast<u32x4 *>(E + j * a.m_pad + i);
+        // 16 rows of a column: the lane's outputs of group q's four blocks in block column bj
+        int el = lane;  // not hoisted: the addresses would live (in scratch) through the k-loops
+        asm volatile("" : "+v"(el));
+        const int64_t col0 = j0 + wn * WTN + group_row(el & 15);
+        const int64_t row0 = i0 + wm * WTM + 16 * (el >> 4);
+        auto e16 = [&](int8_t *E, int q, int bj) {
+            return reinterpret_cast<u32x4 *>(E + (col0 + 4 * bj) * a.m_pad + row0 + 64 * q);
         };
-        // four residues per word of value(0..15), the lane's accumulator-order rows
-        auto residues = [&](auto value, uint32_t (&w)[4]) {
-            static_for<4>([&](auto g) {
-                w[g] = 0;
+        // the group's residues, four to a word: value(block, accumulator register)
+        auto residues = [&](auto value) {
+            u32x4 w;
+            static_for<4>([&](auto t) {
+                uint32_t x = 0;
                 static_for<4>([&](auto u) {
-                    w[g] = put_residue<u>((uint32_t)value(4 * (int)g + u) ^ (DUMP ? (uint32_t)kAccBias : 0u),
-                                          rule, w[g]);
+                    x = put_residue<u>((uint32_t)value(t, (int)u) ^ (DUMP ? (uint32_t)kAccBias : 0u), rule, x);
                 });
-                w[g] ^= 0x80808080u;
+                w[(int)t] = x ^ 0x80808080u;
             });
+            return w;
         };
         int8_t *ER = ep, *EI = ep + planeC;  // EI: not used by real products
         if constexpr (C::PREFETCH) {
@@ -428,10 +447,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             int32_t *D = a.prods + ((int64_t)l * P::nseg + sgi) * planeC;
             static_for<BM>([&](auto bi) {
                 static_for<BN>([&](auto bj) {
-                    static_for<16>([&](auto r) {
-                        const int64_t i = i0 + wm * WTM + bi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        const int64_t j = j0 + wn * WTN + bj * 32 + (lane & 31);
-                        D[j * a.m_pad + i] = acc[bi][bj][(int)r];
+                    static_for<4>([&](auto r) {
+                        D[(col0 + 4 * bj) * a.m_pad + row0 + 64 * (bi / 4) + 4 * (bi % 4) + r] = acc[bi][bj][(int)r];
                     });
                 });
             });
@@ -441,71 +458,63 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             // real: Abar Bbar after the one product
             if (P::real || sgi >= 1) {
                 static_for<BM>([&](auto bi) {
-                    static_for<16>([&](auto r) {
+                    static_for<4>([&](auto r) {
                         int x = acc[bi][0][(int)r];
                         static_for<BN>([&](auto bj) { x = max(x, acc[bi][bj][(int)r]); });
 #pragma unroll
-                        for (int off = 16; off >= 1; off >>= 1) x = max(x, __shfl_xor(x, off, 64));
-                        if ((lane & 31) == 0 && x > 0) {
-                            const int64_t i = i0 + wm * WTM + bi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                            atomicMax(&b.X[i], x);
-                        }
+                        for (int off = 8; off >= 1; off >>= 1) x = max(x, __shfl_xor(x, off, 64));
+                        if ((lane & 15) == 0 && x > 0)
+                            atomicMax(&b.X[row0 + 64 * (bi / 4) + 4 * (bi % 4) + r], x);
                     });
                 });
                 static_for<BN>([&](auto bj) {
                     int y = 0;
-                    static_for<BM>([&](auto bi) { static_for<16>([&](auto r) { y = max(y, acc[bi][bj][(int)r]); }); });
+                    static_for<BM>([&](auto bi) { static_for<4>([&](auto r) { y = max(y, acc[bi][bj][(int)r]); }); });
+                    y = max(y, __shfl_xor(y, 16, 64));
                     y = max(y, __shfl_xor(y, 32, 64));
-                    if (lane < 32 && y > 0) atomicMax(&b.Y[j0 + wn * WTN + bj * 32 + lane], y);
+                    if (lane < 16 && y > 0) atomicMax(&b.Y[col0 + 4 * bj], y);
                 });
             }
         } else if constexpr (P::real) {
             // E' = mod(A'_l B'_l): one reduction per output (Algorithm 1 Step V-iv)
-            static_for<BM>([&](auto bi) {
+            static_for<BM / 4>([&](auto q) {
                 static_for<BN>([&](auto bj) {
-                    uint32_t o[4];
-                    residues([&](int r) { return acc[bi][bj][r]; }, o);
-                    *e16(ER, bi, bj) = rows16(o);
+                    *e16(ER, q, bj) = residues([&](int t, int r) { return acc[4 * (int)q + t][bj][r]; });
                 });
             });
         } else {
-            static_for<BM>([&](auto bi) {
-                // A parked carry is read back one row of blocks at a time (BN * 4 words in one
-                // burst of loads) before that row's stores: a load after a store is not moved
-                // above it (they might alias), so word-by-word read-back waited for a memory
-                // round trip per word.  Reading all BM rows before any store was no faster
-                // overall (fewer E' write-backs, but more operand misses in L2).
+            static_for<BM / 4>([&](auto q) {
+                // A parked carry is read back one row of blocks at a time before that row's
+                // stores: a load after a store is not moved above it (they might alias), so
+                // word-by-word read-back waited for a memory round trip per word.
                 if (!C::REG_CARRY && sgi >= 1 && (karatsuba || sgi != 2)) {
                     u32x4 back[BN];
-                    static_for<BN>([&](auto bj) { back[bj] = *e16(EI, bi, bj); });
-                    static_for<BN>([&](auto bj) { rows4(back[bj], cw[bi][bj]); });
+                    static_for<BN>([&](auto bj) { back[bj] = *e16(EI, q, bj); });
+                    static_for<BN>([&](auto bj) {
+                        static_for<4>([&](auto t) { cw[4 * q + t][bj] = back[bj][(int)t]; });
+                    });
                 }
                 static_for<BN>([&](auto bj) {
-                    u32x4 *er = e16(ER, bi, bj), *ei = e16(EI, bi, bj);
+                    u32x4 *er = e16(ER, q, bj), *ei = e16(EI, q, bj);
                     // The first product of a pair is reduced and carried; the second
                     // enters the reduction unreduced (accumulator +- carried residue
                     // stays in range, see put_residue): 4 reductions per output and
                     // modulus in both forms.
-                    uint32_t o[4];
-                    auto x = [&](int r) { return acc[bi][bj][r]; };
-                    auto d = [&](int r) { return byte_of(cw[bi][bj][r >> 2], r & 3); };
+                    auto x = [&](int t, int r) { return acc[4 * (int)q + t][bj][r]; };
+                    auto d = [&](int t, int r) { return byte_of(cw[4 * (int)q + t][bj], r); };
+                    auto carry = [&](const u32x4 &o) {
+                        if constexpr (C::REG_CARRY) static_for<4>([&](auto t) { cw[4 * q + t][bj] = o[(int)t]; });
+                        else *ei = o;
+                    };
                     if (sgi == 0 || (!karatsuba && sgi == 2)) {
-                        residues(x, o);
-                        if constexpr (C::REG_CARRY) static_for<4>([&](auto g) { cw[bi][bj][g] = o[g]; });
-                        else *ei = rows16(o);
+                        carry(residues(x));
                     } else if (sgi == 1) {
                         // Karatsuba: E'_R = mod(D - E), carry mod(D + E); expanded: E'_R = mod(RR - II)
-                        residues([&](int r) { return d(r) - x(r); }, o);
-                        *er = rows16(o);
-                        if constexpr (karatsuba) {
-                            residues([&](int r) { return d(r) + x(r); }, o);
-                            if constexpr (C::REG_CARRY) static_for<4>([&](auto g) { cw[bi][bj][g] = o[g]; });
-                            else *ei = rows16(o);
-                        }
+                        *er = residues([&](int t, int r) { return d(t, r) - x(t, r); });
+                        if constexpr (karatsuba) carry(residues([&](int t, int r) { return d(t, r) + x(t, r); }));
                     } else {
                         // Karatsuba: E'_I = mod(F - mod(D + E)); expanded: E'_I = mod(RI + IR)
-                        residues([&](int r) { return karatsuba ? x(r) - d(r) : d(r) + x(r); }, o);
-                        *ei = rows16(o);
+                        *ei = residues([&](int t, int r) { return karatsuba ? x(t, r) - d(t, r) : d(t, r) + x(t, r); });
                     }
                 });
             });
@@ -525,16 +534,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
 // symmetric residues in between.
 // The first accumulator starts at the bias 2^31 that put_residue expects: it carries over
 // to both results (X - Y and Z - X - Y modulo 2^32).
-// Against the 128 x 128 tiles with carried residues, same box, products: ZGEMM 64^3 10.8 ->
-// 8.5 us, 256^3 expanded 15.5 -> 12.4 us, 1000 x 900 x 1100 70 -> 65 us.  On 256 x 256-tile
-// shapes it loses from k = 1024 on (2048^3 at N = 13: 390 against 354 us, 4096^3 3200 against
-// 2377 us): a 64 x 64 wave reads a third more LDS per matrix instruction and a 128 x 128
-// block copies twice the bytes into it.
+// Against the 128 x 128 tiles with carried residues, same card, products (32 x 32 x 32
+// instructions): ZGEMM 64^3 10.8 -> 8.5 us, 256^3 expanded 15.5 -> 12.4 us, 1000 x 900 x 1100
+// 70 -> 65 us.  On 256 x 256-tile shapes it loses from k = 1024 on (2048^3 at N = 13: 390
+// against 354 us, 4096^3 3200 against 2377 us): a 64 x 64 wave reads a third more LDS per
+// matrix instruction and a 128 x 128 block copies twice the bytes into it.
+// Waves of 64 x 16 (BN = 1, four to a 64 x 64 tile): see choose_64_tiles.
 constexpr int kOnceChunk = 32768 / BK;  // k-slabs
-template <int WM_, int WN_, int NSTAGE_, int NACC_>
+template <int WM_, int WN_, int BN_, int NSTAGE_, int NACC_, int WAVES_>
 struct OnceCfg {
-    static constexpr int WM = WM_, WN = WN_, BM = 2, BN = 2, NSTAGE = NSTAGE_, NACC = NACC_;
-    static constexpr int TM = WM * 64, TN = WN * 64, THREADS = 64 * WM * WN;
+    static constexpr int WM = WM_, WN = WN_, BM = 4, BN = BN_, NSTAGE = NSTAGE_, NACC = NACC_;
+    static constexpr int TM = WM * 64, TN = WN * BN * 16, THREADS = 64 * WM * WN;
+    static constexpr int WAVES = WAVES_;         // per SIMD: bounds the registers
     static constexpr int STAGE = (TM + TN) * 4;  // uint4 per 64-wide k-slab in LDS
 };
 
@@ -560,45 +571,27 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
     const ModRule rule = mod_rule(a.tab, l);
 
     // ring of NSTAGE one-slab buffers, filled AHEAD slabs ahead (see gemm_tile)
-    constexpr int NW = C::WM * C::WN, QA = TM / 16 / NW, QB = TN / 16 / NW, NLOAD = QA + QB;
-    static_assert(TM / 16 % NW == 0 && TN / 16 % NW == 0 && QA <= 4 && QB <= 4, "chunks per wave");
+    using Copy = SlabCopy<TM, TN, C::WM * C::WN>;
+    const Copy copy(wv, lane);
+    constexpr int NLOAD = Copy::NLOAD;
     static_assert(NSTAGE >= 3, "DMA ring needs at least three buffers");
     constexpr int AHEAD = NSTAGE - 1, LATER = AHEAD - 2 > 0 ? AHEAD - 2 : 0;
-    const int crow = lane >> 2, cg = (lane & 3) ^ swz_bits(crow);
-    const uint32_t voffA = (uint32_t)(wv * QA * 1024 + crow * BK + cg * 16);
-    const uint32_t voffB = (uint32_t)(wv * QB * 1024 + crow * BK + cg * 16);
     const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)(&lds[0][0]);
-    v16i acc[NACC][BM][BN];
+    v4i acc[NACC][BM][BN];
     static_for<NACC>([&](auto z) {
         static_for<BM>([&](auto bi) {
-            static_for<BN>([&](auto bj) { acc[z][bi][bj] = (v16i)(z == 0 ? kAccBias : 0); });
+            static_for<BN>([&](auto bj) { acc[z][bi][bj] = (v4i)(z == 0 ? kAccBias : 0); });
         });
     });
-    const uint32_t frow = (uint32_t)(lane & 31), fsw = (uint32_t)swz_bits(lane & 31);
-    auto read_frags = [&](int buf, int kk, v4i (&fa)[BM], v4i (&fb)[BN]) {
-        const uint32_t g = (uint32_t)(kk * 2 + (lane >> 5)) ^ fsw;
-        const uint4 *FA = lds[buf] + (wm * 64 + frow) * 4 + g;
-        const uint4 *FB = lds[buf] + TM * 4 + (wn * 64 + frow) * 4 + g;
-        static_for<2>([&](auto i) {
-            const uint4 t = FB[i * 32 * 4], u = FA[i * 32 * 4];
-            fb[i] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
-            fa[i] = v4i{(int)u.x, (int)u.y, (int)u.z, (int)u.w};
-        });
-    };
-    auto interleave = [&]() {  // one LDS read per matrix instruction
-        static_for<BM * BN>([&](auto) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        });
-    };
+    auto partA = [&](int buf) { return lds[buf] + wm * 64 * 4; };
+    const int wcol = wn * BN / 4 * 64 + wn * BN % 4 * 4;  // the wave's first column
+    auto partB = [&](int buf) { return lds[buf] + (TM + wcol) * 4; };
     for (int c0 = 0;;) {
         const int nk = min(slabs - c0, kOnceChunk);
         const int8_t *sa = baseA, *sb = baseB;  // the next slab to queue
         int iseg = 0, ist = 0, ibuf = 0;        // its product, slab and buffer
         auto issue = [&]() {
-            const uint32_t buf = lbase + (uint32_t)(ibuf * C::STAGE * 16);
-            static_for<QA>([&](auto q) { dma16<q * 1024>(sa, voffA, buf + (uint32_t)(wv * QA * 1024)); });
-            static_for<QB>([&](auto q) { dma16<q * 1024>(sb, voffB, buf + (uint32_t)(TM * 64 + wv * QB * 1024)); });
+            copy.issue(sa, sb, lbase + (uint32_t)(ibuf * C::STAGE * 16));
             ibuf = ibuf + 1 == NSTAGE ? 0 : ibuf + 1;
             sa += slabA;
             sb += slabB;
@@ -616,50 +609,38 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
             if (t < T) issue();
         });
 
-        v4i fa[2][BM], fb[2][BN];
         if (T > 2 && AHEAD >= 3) vmcnt_wait<2 * NLOAD>();
         else if (T > 1) vmcnt_wait<NLOAD>();
         else vmcnt_wait<0>();
         block_barrier();
-        read_frags(0, 0, fa[0], fb[0]);
+        WaveTile<BM, BN> wt(lane);
+        wt.read_all(partA(0), partB(0));
         int t = 0, cur = 0;
         static_for<P::nseg>([&](auto seg) {
             constexpr int z = seg < NACC ? (int)seg : NACC - 1;
-            auto mfmas = [&](const v4i (&xa)[BM], const v4i (&xb)[BN]) {
-                static_for<BM>([&](auto bi) {
-                    static_for<BN>([&](auto bj) {
-                        acc[z][bi][bj] =
-                            __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[bi], xb[bj], acc[z][bi][bj], 0, 0, 0);
-                    });
-                });
-            };
 #pragma unroll 1
             for (int s = 0; s < nk; ++s, ++t) {
-                read_frags(cur, 1, fa[1], fb[1]);
-                mfmas(fa[0], fb[0]);
-                interleave();
-                // after the last slab of all the wait and the barrier close the ring, and the
-                // fragments read ahead are not used: one path, so that the accumulators of both
-                // halves stay in place
-                if (t + 1 + LATER < T) vmcnt_wait<LATER * NLOAD>();
-                else vmcnt_wait<0>();
-                block_barrier();  // slab t+1 visible; slab t-1's buffer free
-                if (t + AHEAD < T) issue();
+                // at the last slab of all the wait and the barrier close the ring, and the
+                // fragments read ahead are not used: one path, so that the accumulators
+                // stay in place
                 cur = cur + 1 == NSTAGE ? 0 : cur + 1;
-                read_frags(cur, 0, fa[0], fb[0]);
-                mfmas(fa[1], fb[1]);
-                interleave();
+                wt.slab(acc[z], partA(cur), partB(cur), [&]() {
+                    if (t + 1 + LATER < T) vmcnt_wait<LATER * NLOAD>();
+                    else vmcnt_wait<0>();
+                    block_barrier();  // slab t+1 visible; slab t-1's buffer free
+                    if (t + AHEAD < T) issue();
+                });
             }
         });
-        block_barrier();  // all waves done with the ring before it is refilled
         c0 += nk;
         if (c0 >= slabs) break;
+        block_barrier();  // all waves done with the ring before it is refilled
         baseA += nk * slabA;
         baseB += nk * slabB;
         static_for<NACC>([&](auto z) {
             static_for<BM>([&](auto bi) {
                 static_for<BN>([&](auto bj) {
-                    static_for<16>([&](auto r) {
+                    static_for<4>([&](auto r) {
                         const int v = acc[z][bi][bj][(int)r];
                         const uint32_t u = put_residue<0>((uint32_t)(z == 0 ? v : v ^ kAccBias), rule, 0u);
                         acc[z][bi][bj][(int)r] = (int)u - 128 + (z == 0 ? kAccBias : 0);
@@ -670,31 +651,27 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
     }
 
     const int64_t planeC = a.n_pad * a.m_pad;
-    int8_t *E = ep + i0 + wm * 64 + 16 * (lane >> 5);
-    auto store = [&](auto bi, auto bj, int plane, auto value) {
-        uint32_t w[4];
-        static_for<4>([&](auto g) {
-            w[g] = 0;
-            static_for<4>([&](auto u) {
-                w[g] = put_residue<u>((uint32_t)value(4 * (int)g + u), rule, w[g]);
-            });
-            w[g] ^= 0x80808080u;
+    const int64_t col0 = j0 + wcol + group_row(lane & 15);
+    int8_t *E = ep + i0 + wm * 64 + 16 * (lane >> 4);
+    auto store = [&](auto bj, int plane, auto value) {
+        u32x4 w;
+        static_for<4>([&](auto t) {
+            uint32_t x = 0;
+            static_for<4>([&](auto u) { x = put_residue<u>((uint32_t)value(t, (int)u), rule, x); });
+            w[(int)t] = x ^ 0x80808080u;
         });
-        const int64_t j = j0 + wn * 64 + bj * 32 + (lane & 31);
-        *global_ptr(reinterpret_cast<u32x4 *>(E + plane * planeC + j * a.m_pad + bi * 32)) = rows16(w);
+        *global_ptr(reinterpret_cast<u32x4 *>(E + plane * planeC + (col0 + 4 * bj) * a.m_pad)) = w;
     };
-    static_for<BM>([&](auto bi) {
-        static_for<BN>([&](auto bj) {
-            if constexpr (P::real) {
-                store(bi, bj, 0, [&](int r) { return acc[0][bi][bj][r]; });
-            } else {
-                store(bi, bj, 0, [&](int r) { return acc[0][bi][bj][r] - acc[1][bi][bj][r]; });
-                store(bi, bj, 1, [&](int r) {
-                    if constexpr (KIND == KIND_4M) return acc[2][bi][bj][r] ^ kAccBias;
-                    else return acc[2][bi][bj][r] - acc[0][bi][bj][r] - acc[1][bi][bj][r];
-                });
-            }
-        });
+    static_for<BN>([&](auto bj) {
+        if constexpr (P::real) {
+            store(bj, 0, [&](int t, int r) { return acc[0][t][bj][r]; });
+        } else {
+            store(bj, 0, [&](int t, int r) { return acc[0][t][bj][r] - acc[1][t][bj][r]; });
+            store(bj, 1, [&](int t, int r) {
+                if constexpr (KIND == KIND_4M) return acc[2][t][bj][r] ^ kAccBias;
+                else return acc[2][t][bj][r] - acc[0][t][bj][r] - acc[1][t][bj][r];
+            });
+        }
     });
 }
 
@@ -715,7 +692,8 @@ struct BlockWork {
 };
 template <int KIND, typename C>
 __device__ __forceinline__ BlockWork block_work(const GemmArgs &a, uint32_t blk) {
-    const uint32_t TR = (uint32_t)(a.m_pad / C::TM), TC = (uint32_t)(a.n_pad / C::TN);
+    const uint32_t TR = C::TM == 64 ? (uint32_t)a.rows64 : (uint32_t)(a.m_pad / C::TM);
+    const uint32_t TC = C::TN == 64 ? (uint32_t)a.cols64 : (uint32_t)(a.n_pad / C::TN);
     const uint32_t whole = (uint32_t)a.l_split * TR * TC;
     const int slabs = (int)(a.k_pad / BK);
     BlockWork w;
@@ -738,20 +716,23 @@ __device__ __forceinline__ BlockWork block_work(const GemmArgs &a, uint32_t blk)
     return w;
 }
 
+// Two waves per SIMD at least: with 512 registers allowed the compiler keeps accumulators in
+// the accumulation half and copies them from slab to slab (real bound of 576 x 960 x 23655:
+// 328 against 294 us with the scan).
 template <int KIND, typename C, bool DUMP>
-__global__ __launch_bounds__(C::THREADS) void residue_gemm_kernel(GemmArgs a) {
+__global__ __launch_bounds__(C::THREADS, 2) void residue_gemm_kernel(GemmArgs a) {
     const BlockWork w = block_work<KIND, C>(a, blockIdx.x);
     gemm_tile<KIND, C, DUMP>(a, BoundArgs{}, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
 }
 
 template <int KIND, typename C>
-__global__ __launch_bounds__(C::THREADS, 2) void once_gemm_kernel(GemmArgs a) {
+__global__ __launch_bounds__(C::THREADS, C::WAVES) void once_gemm_kernel(GemmArgs a) {
     const BlockWork w = block_work<KIND, C>(a, blockIdx.x);
     once_tile<KIND, C>(a, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
 }
 
 template <int KIND, typename C>
-__global__ __launch_bounds__(C::THREADS) void bound_gemm_kernel(BoundArgs b) {
+__global__ __launch_bounds__(C::THREADS, 2) void bound_gemm_kernel(BoundArgs b) {
     const uint32_t TR = (uint32_t)(b.m_pad / C::TM), TC = (uint32_t)(b.n_pad / C::TN);
     int l;
     int64_t ti, tj;
@@ -766,11 +747,11 @@ struct BatchTile {
         gemm_tile<KIND, C, false>(a, BoundArgs{}, eprime_of<KIND>(a, l), l, ti, tj, 0, (int)(a.k_pad / BK));
     }
 };
-template <int KIND, int WM, int WN, int NSTAGE, int NACC>
-struct BatchTile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>> {
+template <int KIND, int WM, int WN, int BN, int NSTAGE, int NACC, int WAVES>
+struct BatchTile<KIND, OnceCfg<WM, WN, BN, NSTAGE, NACC, WAVES>> {
     __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
-        once_tile<KIND, OnceCfg<WM, WN, NSTAGE, NACC>>(a, eprime_of<KIND>(a, l), l, ti, tj, 0,
-                                                     (int)(a.k_pad / BK));
+        once_tile<KIND, OnceCfg<WM, WN, BN, NSTAGE, NACC, WAVES>>(a, eprime_of<KIND>(a, l), l, ti, tj, 0,
+                                                                 (int)(a.k_pad / BK));
     }
 };
 
@@ -848,7 +829,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void batch_gemm_kernel(const BatchGe
 
 // Persistent kernel over the tiles of a batch's bound products (accurate mode).
 template <typename C>
-__global__ __launch_bounds__(C::THREADS) void batch_bound_kernel(const BatchBound *probs, int nprob,
+__global__ __launch_bounds__(C::THREADS, 2) void batch_bound_kernel(const BatchBound *probs, int nprob,
                                                                 int64_t items, uint32_t *counter) {
     __shared__ int64_t item_s;
     for (;;) {
@@ -894,8 +875,10 @@ void launch_kind(const GemmArgs &a, bool dump, int64_t blocks, hipStream_t s) {
 }
 
 // 128 x 128 output tiles, 256 threads, 64 KB LDS: two blocks per CU, two waves per SIMD
-using Once128 = OnceCfg<2, 2, 4, 3>;
-using Once128Real = OnceCfg<2, 2, 4, 1>;
+using Once128 = OnceCfg<2, 2, 4, 4, 3, 2>;
+using Once128Real = OnceCfg<2, 2, 4, 4, 1, 2>;
+using Once64 = OnceCfg<1, 4, 1, 4, 3, 4>;
+using Once64Real = OnceCfg<1, 4, 1, 4, 1, 4>;
 
 template <int KIND, typename C>
 hipError_t launch_once(const GemmArgs &a, int64_t blocks, hipStream_t s) {
@@ -912,7 +895,7 @@ void launch_dump(const GemmArgs &a, int64_t blocks, hipStream_t s) {
 }  // namespace
 
 int gemm_tile_for(int64_t m, int64_t n) { return (m >= 1024 && n >= 1024) ? 256 : 128; }
-int gemm_kstep_for(int tile) { return tile == 256 ? CfgLarge::KSTEP : CfgSmall::KSTEP; }
+int gemm_kstep_for(int) { return BK; }
 int gemm_tile_rows(int tile) { return tile == 256 ? CfgLarge::TM : CfgSmall::TM; }
 int gemm_tile_cols(int tile) { return tile == 256 ? CfgLarge::TN : CfgSmall::TN; }
 
@@ -962,6 +945,27 @@ KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad
     return best;
 }
 
+// Whether a single call's products run on 64 x 64 tiles.  Where a call's 128 x 128 tiles leave
+// CUs idle, its time is one block's: the reductions of 64 x 64 outputs per wave (some 320 x 8
+// vector instructions, 4 us for complex products) behind a chain of slabs.  A quarter of that
+// on four times the CUs is shorter; once the CUs are full, the smaller tile's operand reads
+// (five LDS reads per four matrix instructions, against two per four) cost more than that.
+// Products in us, 128 x 128 against 64 x 64, blocks of the latter on 256 CUs:
+//   ZGEMM N = 14, 64 x 64 (14 blocks)   k = 64   8.5 -> 6.8,  k = 256  11.0 -> 8.2
+//   ZGEMM N = 14, 256 x 256 (224)       k = 64   9.0 -> 7.2,  k = 512  14.4 -> 11.0
+//   DGEMM N = 14, 256 x 256 (224)       k = 64   7.5 -> 6.8,  k = 1000 10.8 -> 8.8
+//   ZGEMM N = 14, 256 x 512 (448)       k = 512  15.1 -> 12.6, k = 2048 22.8 -> 25.2
+//   CGEMM N = 8, 333 x 777 (624)        k = 64   10.4 -> 9.4, k = 1000 21.0 -> 20.8
+//   ZGEMM N = 14, 512 x 512 (896)       k = 64   12.1 -> 12.0, k = 512  15.6 -> 16.7
+//   DGEMM N = 14, 512 x 512 (896)       k = 64   8.2 -> 8.6,  k = 1000 12.0 -> 13.0
+// Products that are cut along k keep 128 x 128 tiles (as fast there, and the cut's parts are
+// sized for them).
+bool choose_64_tiles(int tile, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus) {
+    if (tile != 128 || m > (int64_t)64 * 1024 || n > (int64_t)64 * 1024) return false;
+    const int64_t blocks = (int64_t)nmod * ((m + 63) / 64) * ((n + 63) / 64);
+    return blocks <= cus || (2 * blocks <= 5 * (int64_t)cus && k_pad <= 1024);
+}
+
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {
     const int tile = a.tile;
     if (tile != 128 && tile != 256) return hipErrorInvalidValue;
@@ -975,6 +979,15 @@ hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const bool dump = a.prods != nullptr;
     if (a.algo < 0 || a.algo > 2) return hipErrorInvalidValue;
+    if (a.rows64 > 0) {
+        if (tile != 128 || dump || a.l_split < a.nmod || a.rows64 * 64 > a.m_pad || a.cols64 < 1 || a.cols64 * 64 > a.n_pad)
+            return hipErrorInvalidValue;
+        const int64_t small = (int64_t)a.nmod * a.rows64 * a.cols64;
+        if (small >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+        if (a.algo == 2) return launch_once<KIND_REAL, Once64Real>(a, small, s);
+        if (a.algo == 1) return launch_once<KIND_4M, Once64>(a, small, s);
+        return launch_once<KIND_KARATSUBA, Once64>(a, small, s);
+    }
     if (tile == 128 && !dump) {
         if (a.algo == 2) return launch_once<KIND_REAL, Once128Real>(a, blocks, s);
         if (a.algo == 1) return launch_once<KIND_4M, Once128>(a, blocks, s);

@@ -146,6 +146,8 @@ struct GemmArgs {
     int l_split, parts;   // moduli from l_split on cut k into `parts` parts (1 .. k_pad / 64), ...
     int8_t *eprime_parts; // ... parts 1 .. parts - 1 with E' planes here: [part - 1][l - l_split]
                           // [2][n_pad][m_pad]; every part's E' is a residue of its share
+    int64_t rows64, cols64;  // > 0: 64 x 64 tiles, this many, over the outputs alone (tile 128,
+                             // one part, no dump); the padding of E' is not written
 };
 // Sum over the moduli of their parts, at most: 128 kMaxPartSum 2^38 stays below 2^52 in the
 // reconstruction's FP64 chunks, and so does the quotient times a chunk of P.
@@ -155,6 +157,7 @@ struct KSplit {
     int l_split, parts;
 };
 KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad, int64_t k_pad, int cus);
+bool choose_64_tiles(int tile, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus);
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s);
 // Output tile edge used for an m x n product (the padding of every buffer follows it).
 int gemm_tile_for(int64_t m, int64_t n);
