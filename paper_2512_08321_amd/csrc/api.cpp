@@ -270,11 +270,10 @@ ozc_status_t enqueue_check_result(ozc_context *h, bool single, int64_t m, int64_
     double rel, gam;
     check_tolerances(h, single, n, k, &rel, &gam);
     const bool beta_zero = beta[0] == 0.0 && beta[1] == 0.0;
-    // w = C x (m), then the row test against alpha z + beta v
-    OZC_TRY(launch_gemv(C, single, 0, m, n, ldc, nullptr, nullptr, nullptr, h->verify_seed, b.w, b.wl,
-                        b.wa, b.scratch, s));
-    OZC_TRY(launch_freivalds_rows(b.w, b.wl, b.wa, b.z, b.zl, b.za, beta_zero ? nullptr : b.v, b.vl,
-                                  b.va, m, alpha, beta, rel, gam, word, s));
+    // w = C x (m) and the row test against alpha z + beta v
+    OZC_TRY(launch_check_rows(C, single, m, n, ldc, h->verify_seed, b.z, b.zl, b.za,
+                              beta_zero ? nullptr : b.v, b.vl, b.va, alpha, beta, rel, gam, word,
+                              b.scratch, s));
     return OZC_STATUS_SUCCESS;
 }
 

@@ -350,11 +350,11 @@ hipError_t launch_gemv(const void *M, bool single, int op, int64_t rows, int64_t
                        const double2 *xv, const double2 *xlo, const double *xa, uint64_t seed,
                        double2 *y, double2 *ylo, double *ya, void *scratch, hipStream_t s);
 size_t gemv_scratch_bytes(int64_t rows, int64_t cols);
-hipError_t launch_freivalds_rows(const double2 *w, const double2 *wl, const double *wa,
-                                 const double2 *z, const double2 *zl, const double *za,
-                                 const double2 *v, const double2 *vl, const double *va, int64_t m,
-                                 const double alpha[2], const double beta[2], double rel,
-                                 double gam, unsigned long long *worst, hipStream_t s);
+hipError_t launch_check_rows(const void *C, bool single, int64_t m, int64_t n, int64_t ldc, uint64_t seed,
+                             const double2 *z, const double2 *zl, const double *za, const double2 *v,
+                             const double2 *vl, const double *va, const double alpha[2],
+                             const double beta[2], double rel, double gam, unsigned long long *worst,
+                             void *scratch, hipStream_t s);
 
 // One matrix-vector product of a batched check: y = op(M) x as in launch_gemv, with
 // x the sign vector of seed (xv == nullptr) or a double-double vector.  make_gemv_task
@@ -381,7 +381,7 @@ GemvTask make_gemv_task(const void *M, int op, int64_t rows, int64_t cols, int64
 hipError_t launch_batch_gemv(const GemvTask *tasks, int n, const int64_t nb[3], bool single,
                              hipStream_t s);
 
-// The per-row test of one problem of a batched check (as launch_freivalds_rows; v may
+// The per-row test of one problem of a batched check (as launch_check_rows; v may
 // be null); b0: first block of the problem in the launch.
 struct RowsTask {
     const double2 *w, *wl, *z, *zl, *v, *vl;
