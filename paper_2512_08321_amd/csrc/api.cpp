@@ -467,12 +467,11 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
         if (pre) OZC_TRY(launch_fill_u64((uint64_t *)XA, (int64_t)(L.muA - L.XA) / 8, 0, s));
         else
             OZC_TRY(launch_row_maxima(vA, vB, ek, L.m_pad, L.n_pad, maxA, maxB, XA, YB, resA, resB, clear, s));
-        OZC_TRY(launch_ceil7(vA, ek, cmaxA, barA, L.m_pad, L.k_pad, s));
-        OZC_TRY(launch_ceil7(vB, ek, cmaxB, barB, L.n_pad, L.k_pad, s));
+        const AccuSide sA{vA, cmaxA, barA, XA, muA, L.m_pad}, sB{vB, cmaxB, barB, YB, nuB, L.n_pad};
+        OZC_TRY(launch_pair_ceil7(sA, sB, ek, L.k_pad, s));
         BoundArgs ba{barA, barB, L.m_pad, L.n_pad, L.k_pad, XA, YB, L.tile, real ? 1 : 0};
         OZC_TRY(launch_bound_gemm(ba, s));
-        OZC_TRY(launch_accu_exponents(cmaxA, XA, m, L.m_pad, tab, muA, status, s));
-        OZC_TRY(launch_accu_exponents(cmaxB, YB, n, L.n_pad, tab, nuB, status, s));
+        OZC_TRY(launch_pair_accu_exponents(sA, sB, tab, status, s));
         abits = th.max_abits_accu;
     }
     if (fault == 2) OZC_TRY(launch_debug_add_exp(muA, 12, s));

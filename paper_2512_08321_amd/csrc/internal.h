@@ -111,12 +111,19 @@ hipError_t launch_pair_fast_exponents(const uint64_t *maxA, const uint64_t *sigA
                                       int64_t m_pad, int16_t *mu, const uint64_t *maxB,
                                       const uint64_t *sigB, int64_t n, int64_t n_pad, int16_t *nu,
                                       const NTable *tab, uint32_t *status, hipStream_t s);
-// complex: planes Abar_R, Abar_I, Abar_R - Abar_I; real: the plane Abar
-hipError_t launch_ceil7(const OperandView &v, int ek, const uint64_t *maxbits,
-                        int8_t *dst, int64_t rows_pad, int64_t k_pad, hipStream_t s);
-hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int64_t rows,
-                                 int64_t rows_pad, const NTable *tab, int16_t *mu,
-                                 uint32_t *status, hipStream_t s);
+// One operand of an accurate-mode call: magnitudes' planes `bar` (complex: Abar_R, Abar_I,
+// Abar_R - Abar_I; real: Abar) from the rows' maxima, exponents from them and the bound X.
+struct AccuSide {
+    OperandView v;
+    const uint64_t *maxbits;
+    int8_t *bar;
+    const int32_t *X;
+    int16_t *mu;
+    int64_t rows_pad;
+};
+hipError_t launch_pair_ceil7(const AccuSide &a, const AccuSide &b, int ek, int64_t k_pad, hipStream_t s);
+hipError_t launch_pair_accu_exponents(const AccuSide &a, const AccuSide &b, const NTable *tab,
+                                      uint32_t *status, hipStream_t s);
 // Residues of both operands.  abits bounds the bit length of |a'| (at most
 // 32 * kMaxSplitWords - 1).  nplanes: 3 (Karatsuba: R, I, reduced R + I) or 2 (R, I) for
 // complex operands, 1 (R) for real ones.

@@ -297,11 +297,13 @@ __device__ __forceinline__ void accu_exponents_body(const uint64_t *maxbits, con
     mu[r] = out;
 }
 
-__global__ __launch_bounds__(256) void accu_exponents_kernel(const uint64_t *maxbits,
-                                                             const int32_t *X, int64_t rows,
-                                                             int64_t rows_pad, const NTable *tab,
-                                                             int16_t *mu, uint32_t *status) {
-    accu_exponents_body(maxbits, X, rows, rows_pad, tab, mu, status, blockIdx.x);
+// Both operands of a single call: A's blocks, then B's.
+__global__ __launch_bounds__(256) void pair_accu_exponents_kernel(AccuSide a, AccuSide b, uint32_t blocks_a,
+                                                                  const NTable *tab, uint32_t *status) {
+    const bool second = blockIdx.x >= blocks_a;
+    const AccuSide &o = second ? b : a;
+    accu_exponents_body(o.maxbits, o.X, o.v.rows, o.rows_pad, tab, o.mu, status,
+                        second ? blockIdx.x - blocks_a : blockIdx.x);
 }
 
 // ---------------------------------------------------------------- one-read scaling scan
@@ -917,10 +919,19 @@ __global__ __launch_bounds__(1024) void pair_prep_kernel(SplitSide a, SplitSide 
     prep_rows_body<EK, NPLANES, W>(second ? b : a, (int64_t)blk * (blockDim.x / 64), k_pad, tab, nmod);
 }
 
-template <int EK, bool CONTIG_H>
-__global__ __launch_bounds__(256) void ceil7_kernel(OperandView v, const uint64_t *maxbits,
-                                                    int8_t *dst, int64_t rows_pad, int64_t k_pad) {
-    ceil7_body<EK, CONTIG_H>(v, maxbits, dst, rows_pad, k_pad, blockIdx.x, blockIdx.y);
+// Both operands of a single call: A's blocks, then B's.  Small accurate calls are chains of
+// launches: this one and the exponents' one took two each (scaling with the bound product,
+// ZGEMM 100 x 100 x 300 37.5 -> 30.8 us, CGEMM 500 x 700 x 1000 50.5 -> 39.9 us, ZGEMM 2048^3 113.1 ->
+// 111.3 us).
+template <int EK>
+__global__ __launch_bounds__(256) void pair_ceil7_kernel(AccuSide a, AccuSide b, uint32_t blocks_a,
+                                                         int64_t k_pad) {
+    const bool second = blockIdx.x >= blocks_a;
+    const AccuSide &o = second ? b : a;
+    const uint32_t lb = second ? blockIdx.x - blocks_a : blockIdx.x, gx = (uint32_t)(k_pad / kTileH);
+    const uint32_t by = lb / gx, bx = lb - by * gx;
+    if (o.v.contig_h) ceil7_body<EK, true>(o.v, o.maxbits, o.bar, o.rows_pad, k_pad, bx, by);
+    else ceil7_body<EK, false>(o.v, o.maxbits, o.bar, o.rows_pad, k_pad, bx, by);
 }
 
 // ---------------------------------------------------------------- kernels (batched)
@@ -1227,12 +1238,13 @@ hipError_t launch_pair_fast_exponents(const uint64_t *maxA, const uint64_t *sigA
     return hipGetLastError();
 }
 
-hipError_t launch_accu_exponents(const uint64_t *maxbits, const int32_t *X, int64_t rows,
-                                 int64_t rows_pad, const NTable *tab, int16_t *mu,
-                                 uint32_t *status, hipStream_t s) {
-    if (rows_pad <= 0) return hipSuccess;
-    hipLaunchKernelGGL(accu_exponents_kernel, dim3((unsigned)((rows_pad + 255) / 256)), dim3(256),
-                       0, s, maxbits, X, rows, rows_pad, tab, mu, status);
+hipError_t launch_pair_accu_exponents(const AccuSide &a, const AccuSide &b, const NTable *tab,
+                                      uint32_t *status, hipStream_t s) {
+    const int64_t blkA = (a.rows_pad + 255) / 256, blkB = (b.rows_pad + 255) / 256;
+    if (blkA + blkB <= 0) return hipSuccess;
+    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(pair_accu_exponents_kernel, dim3((unsigned)(blkA + blkB)), dim3(256), 0, s, a, b,
+                       (uint32_t)blkA, tab, status);
     return hipGetLastError();
 }
 
@@ -1280,25 +1292,20 @@ hipError_t launch_pair_prep(const OperandView &va, const OperandView &vb, int ek
     return pair_split_ek(a, b, true, 64 * RB, ek, tab, nmod, nplanes, abits, k_pad, status, s);
 }
 
-template <int EK>
-hipError_t ceil7_ek(const OperandView &v, const uint64_t *maxbits, int8_t *dst, int64_t rows_pad,
-                    int64_t k_pad, hipStream_t s) {
-    dim3 grid((unsigned)(k_pad / kTileH), (unsigned)(rows_pad / kTileR));
-    if (v.contig_h) hipLaunchKernelGGL((ceil7_kernel<EK, true>), grid, dim3(256), 0, s, v, maxbits, dst, rows_pad, k_pad);
-    else hipLaunchKernelGGL((ceil7_kernel<EK, false>), grid, dim3(256), 0, s, v, maxbits, dst, rows_pad, k_pad);
-    return hipGetLastError();
-}
-
-hipError_t launch_ceil7(const OperandView &v, int ek, const uint64_t *maxbits, int8_t *dst,
-                        int64_t rows_pad, int64_t k_pad, hipStream_t s) {
-    if (rows_pad % kTileR || k_pad % kTileH) return hipErrorInvalidValue;
+hipError_t launch_pair_ceil7(const AccuSide &a, const AccuSide &b, int ek, int64_t k_pad, hipStream_t s) {
+    if (a.rows_pad % kTileR || b.rows_pad % kTileR || k_pad % kTileH) return hipErrorInvalidValue;
+    const int64_t blkA = batch_ceil7_blocks(a.rows_pad, k_pad), blkB = batch_ceil7_blocks(b.rows_pad, k_pad);
+    if (blkA + blkB <= 0) return hipSuccess;
+    if (blkA + blkB > INT32_MAX) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)(blkA + blkB));
     switch (ek) {
-        case kElemZ: return ceil7_ek<kElemZ>(v, maxbits, dst, rows_pad, k_pad, s);
-        case kElemC: return ceil7_ek<kElemC>(v, maxbits, dst, rows_pad, k_pad, s);
-        case kElemD: return ceil7_ek<kElemD>(v, maxbits, dst, rows_pad, k_pad, s);
-        case kElemS: return ceil7_ek<kElemS>(v, maxbits, dst, rows_pad, k_pad, s);
+        case kElemZ: hipLaunchKernelGGL(pair_ceil7_kernel<kElemZ>, grid, dim3(256), 0, s, a, b, (uint32_t)blkA, k_pad); break;
+        case kElemC: hipLaunchKernelGGL(pair_ceil7_kernel<kElemC>, grid, dim3(256), 0, s, a, b, (uint32_t)blkA, k_pad); break;
+        case kElemD: hipLaunchKernelGGL(pair_ceil7_kernel<kElemD>, grid, dim3(256), 0, s, a, b, (uint32_t)blkA, k_pad); break;
+        case kElemS: hipLaunchKernelGGL(pair_ceil7_kernel<kElemS>, grid, dim3(256), 0, s, a, b, (uint32_t)blkA, k_pad); break;
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 int64_t batch_scan_blocks(const OperandView &v) {
