@@ -91,31 +91,48 @@ Layout make_layout(const ozc_context *h, int64_t m, int64_t n, int64_t k, bool w
 }
 
 
-// The call's workspace: at least `bytes`, and up to *extra more where they can be had (the
-// handle's own memory grows; a caller's or the fixed workspace may be too small).  *extra
-// receives what there is of them, all or nothing.
-ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t *extra, char **ws) {
-    if (*extra) {
-        const size_t want = bytes + *extra;
-        const size_t have = h->use_fixed ? (size_t)OZC_NOALLOC_WORKSPACE
-                                         : (h->ws_user ? h->ws_user_bytes : SIZE_MAX);
-        if (want > have) *extra = 0;
-        else if (!h->use_fixed && !h->ws_user && want > h->ws_own_bytes) {
-            size_t none = 0;
-            const ozc_status_t st = ensure_workspace(h, want, &none, ws);
-            if (st != OZC_STATUS_ALLOC_FAILED) return st;
-            *extra = 0;  // as much as the call cannot do without
+// Memory of the handle's own for `bytes` of E' parts, or null.  Nothing is allocated while the
+// stream is being captured, and a capture elsewhere in the process is left alone (hipMalloc
+// would end it otherwise).
+void *own_parts(ozc_context *h, size_t bytes) {
+    if (!h->parts.covers(bytes)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
         }
+        if (cap != hipStreamCaptureStatusNone) return nullptr;
     }
+    return h->parts.get(bytes, [](size_t size) -> void * {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        void *p = nullptr;
+        if (hipMalloc(&p, size) != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return p;
+    });
+}
 
+// The call's workspace of `bytes`, and `extra` bytes more at *more where they can be had
+// without a change to the workspace (null where not).
+ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t extra, char **ws, char **more) {
+    *more = nullptr;
     if (h->use_fixed) {  // checked against the size before any work was enqueued
         if (!h->ws_fixed || bytes > (size_t)OZC_NOALLOC_WORKSPACE) return OZC_STATUS_NOT_SUPPORTED;
         *ws = (char *)h->ws_fixed;
+        if (extra && extra <= (size_t)OZC_NOALLOC_WORKSPACE - bytes) *more = *ws + bytes;
         return OZC_STATUS_SUCCESS;
     }
     if (h->ws_user) {
         if (bytes > h->ws_user_bytes) return OZC_STATUS_ALLOC_FAILED;
         *ws = (char *)h->ws_user;
+        if (extra && extra <= h->ws_user_bytes - bytes) *more = *ws + bytes;
         return OZC_STATUS_SUCCESS;
     }
     if (bytes > h->ws_own_bytes) {
@@ -124,6 +141,7 @@ ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t *extra, char 
             OZC_TRY(hipFree(h->ws_own));
             h->ws_own = nullptr;
             h->ws_own_bytes = 0;
+            h->parts.release([](void *p) { (void)hipFree(p); });
         }
         if (hipMalloc(&h->ws_own, bytes) != hipSuccess) {
             h->ws_own = nullptr;
@@ -133,6 +151,8 @@ ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t *extra, char 
         h->ws_own_bytes = bytes;
     }
     *ws = (char *)h->ws_own;
+    if (extra)
+        *more = extra <= h->ws_own_bytes - bytes ? *ws + bytes : (char *)own_parts(h, extra);
     return OZC_STATUS_SUCCESS;
 }
 
@@ -417,9 +437,13 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     const int galgo = real ? 2 : (h->algo == OZC_ALGO_KARATSUBA ? 0 : 1);
     KSplit ks{h->nmod, 1};
     if (!ins && !h->dd_lo) ks = choose_k_split(L.tile, galgo, h->nmod, L.m_pad, L.n_pad, L.k_pad, h->cus);
+    char *ep_parts = nullptr;
     size_t extra = (size_t)(h->nmod - ks.l_split) * (ks.parts - 1) * L.eplanes * (size_t)L.m_pad * L.n_pad;
-    st = ensure_workspace(h, L.total, &extra, &ws);
-    if (extra == 0) ks = KSplit{h->nmod, 1};
+    st = ensure_workspace(h, L.total, extra, &ws, &ep_parts);
+    if (!ep_parts) {
+        extra = 0;
+        ks = KSplit{h->nmod, 1};
+    }
     if (st != OZC_STATUS_SUCCESS) {  // no scan will clear the flag
         if (!h->keep_status) OZC_TRY(launch_fill_u64(h->status_dev, 1, 0, s));
         return st;
@@ -488,9 +512,8 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
 
     // Step V-iii/iv: INT8 products and their residues
     OZC_TRY(pe.mark(2));
-    int8_t *ep_parts = (int8_t *)(ws + L.total);
     GemmArgs ga{resA, resB, L.m_pad, L.n_pad, L.k_pad, h->nmod, galgo, tab, ep, prods, L.tile,
-                ks.l_split, ks.parts, ep_parts, 0, 0};
+                ks.l_split, ks.parts, (int8_t *)ep_parts, 0, 0};
     if (!ins && ks.parts == 1 && choose_64_tiles(L.tile, h->nmod, m, n, L.k_pad, h->cus)) {
         ga.rows64 = (m + 63) / 64;
         ga.cols64 = (n + 63) / 64;
@@ -503,7 +526,7 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     if (C) {
         CrtArgs ca{};
         ca.eprime = ep;
-        ca.eprime_parts = ep_parts;
+        ca.eprime_parts = (const int8_t *)ep_parts;
         ca.l_split = ks.l_split;
         ca.parts = ks.parts;
         ca.m = m;
@@ -743,6 +766,7 @@ ozc_status_t ozc_destroy(ozc_handle_t h) {
         for (auto e : ev) (void)hipEventDestroy(e);
     for (auto e : h->event_pool) (void)hipEventDestroy(e);
     if (h->ws_own) (void)hipFree(h->ws_own);
+    h->parts.release([](void *p) { (void)hipFree(p); });
     if (h->vws) (void)hipFree(h->vws);
     batch_release(h);
     mlp_release(h);

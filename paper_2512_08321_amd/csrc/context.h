@@ -6,6 +6,7 @@
 
 #include "../../include/ozc.h"
 #include "internal.h"
+#include "parts_buffer.h"
 
 namespace ozc {
 struct BatchState;  // batched-call plans and tuning (batched.cpp)
@@ -26,6 +27,7 @@ struct ozc_context {
     ozc_algo_t algo = OZC_ALGO_KARATSUBA;
     void *ws_own = nullptr;
     size_t ws_own_bytes = 0;
+    ozc::PartsBuffer parts;             // E' planes beyond ws_own of products cut along k
     void *ws_user = nullptr;
     size_t ws_user_bytes = 0;
     void *ws_fixed = nullptr;           // this device's fixed workspace array (ozc_zgemm_noalloc)
