@@ -550,8 +550,11 @@ struct OnceCfg {
 };
 
 // As gemm_tile: one output tile (ti, tj) of modulus l over the k-slabs s0 .. s0 + slabs - 1,
-// E' to the modulus' planes at ep.  Ends with a block barrier.
-template <int KIND, typename C>
+// E' to the modulus' planes at ep.  AGAIN: a block barrier stands behind the last slab, so that
+// the caller may run the next tile right away: the last barrier of the slabs themselves does not
+// wait for the other waves' reads of the slab behind it, and the next tile's copies go to
+// the same buffers.
+template <int KIND, typename C, bool AGAIN>
 __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, int64_t ti, int64_t tj,
                                           int s0, int slabs) {
     using P = Plan<KIND>;
@@ -633,8 +636,8 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
             }
         });
         c0 += nk;
+        if (AGAIN || c0 < slabs) block_barrier();  // all waves done with the ring before it is refilled
         if (c0 >= slabs) break;
-        block_barrier();  // all waves done with the ring before it is refilled
         baseA += nk * slabA;
         baseB += nk * slabB;
         static_for<NACC>([&](auto z) {
@@ -728,7 +731,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void residue_gemm_kernel(GemmArgs a)
 template <int KIND, typename C>
 __global__ __launch_bounds__(C::THREADS, C::WAVES) void once_gemm_kernel(GemmArgs a) {
     const BlockWork w = block_work<KIND, C>(a, blockIdx.x);
-    once_tile<KIND, C>(a, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
+    once_tile<KIND, C, false>(a, w.ep, w.l, w.ti, w.tj, w.s0, w.nk);
 }
 
 template <int KIND, typename C>
@@ -750,8 +753,8 @@ struct BatchTile {
 template <int KIND, int WM, int WN, int BN, int NSTAGE, int NACC, int WAVES>
 struct BatchTile<KIND, OnceCfg<WM, WN, BN, NSTAGE, NACC, WAVES>> {
     __device__ static __forceinline__ void run(const GemmArgs &a, int l, int64_t ti, int64_t tj) {
-        once_tile<KIND, OnceCfg<WM, WN, BN, NSTAGE, NACC, WAVES>>(a, eprime_of<KIND>(a, l), l, ti, tj, 0,
-                                                                 (int)(a.k_pad / BK));
+        once_tile<KIND, OnceCfg<WM, WN, BN, NSTAGE, NACC, WAVES>, true>(a, eprime_of<KIND>(a, l), l, ti, tj, 0,
+                                                                       (int)(a.k_pad / BK));
     }
 };
 
