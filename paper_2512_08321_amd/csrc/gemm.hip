@@ -36,6 +36,7 @@
 #include <cmath>
 #include <utility>
 
+#include "acc_math.h"
 #include "internal.h"
 
 namespace ozc {
@@ -82,7 +83,6 @@ struct ModRule {
     uint32_t wb, bias;
     float p, ip, rb;
 };
-constexpr int kAccBias = (int)0x80000000;
 __device__ __forceinline__ ModRule mod_rule(const NTable *tab, int l) {
     const OZC_AS_CONST ModConst &mc = const_ptr(tab)->mod[l];
     return ModRule{mc.wbyte[0], mc.wbias[0], mc.pf, mc.ipf, mc.rbias};
@@ -433,7 +433,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             static_for<4>([&](auto t) {
                 uint32_t x = 0;
                 static_for<4>([&](auto u) {
-                    x = put_residue<u>((uint32_t)value(t, (int)u) ^ (DUMP ? (uint32_t)kAccBias : 0u), rule, x);
+                    x = put_residue<u>(value(t, (int)u) ^ (DUMP ? (uint32_t)kAccBias : 0u), rule, x);
                 });
                 w[(int)t] = x ^ 0x80808080u;
             });
@@ -479,7 +479,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
             // E' = mod(A'_l B'_l): one reduction per output (Algorithm 1 Step V-iv)
             static_for<BM / 4>([&](auto q) {
                 static_for<BN>([&](auto bj) {
-                    *e16(ER, q, bj) = residues([&](int t, int r) { return acc[4 * (int)q + t][bj][r]; });
+                    *e16(ER, q, bj) = residues([&](int t, int r) { return (uint32_t)acc[4 * (int)q + t][bj][r]; });
                 });
             });
         } else {
@@ -507,14 +507,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const BoundArgs &b,
                         else *ei = o;
                     };
                     if (sgi == 0 || (!karatsuba && sgi == 2)) {
-                        carry(residues(x));
+                        carry(residues([&](int t, int r) { return (uint32_t)x(t, r); }));
                     } else if (sgi == 1) {
                         // Karatsuba: E'_R = mod(D - E), carry mod(D + E); expanded: E'_R = mod(RR - II)
-                        *er = residues([&](int t, int r) { return d(t, r) - x(t, r); });
-                        if constexpr (karatsuba) carry(residues([&](int t, int r) { return d(t, r) + x(t, r); }));
+                        *er = residues([&](int t, int r) { return acc_sub(d(t, r), x(t, r)); });
+                        if constexpr (karatsuba) carry(residues([&](int t, int r) { return acc_add(d(t, r), x(t, r)); }));
                     } else {
                         // Karatsuba: E'_I = mod(F - mod(D + E)); expanded: E'_I = mod(RI + IR)
-                        *ei = residues([&](int t, int r) { return karatsuba ? x(t, r) - d(t, r) : d(t, r) + x(t, r); });
+                        *ei = residues([&](int t, int r) { return karatsuba ? acc_sub(x(t, r), d(t, r)) : acc_add(d(t, r), x(t, r)); });
                     }
                 });
             });
@@ -645,8 +645,8 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
                 static_for<BN>([&](auto bj) {
                     static_for<4>([&](auto r) {
                         const int v = acc[z][bi][bj][(int)r];
-                        const uint32_t u = put_residue<0>((uint32_t)(z == 0 ? v : v ^ kAccBias), rule, 0u);
-                        acc[z][bi][bj][(int)r] = (int)u - 128 + (z == 0 ? kAccBias : 0);
+                        const uint32_t u = put_residue<0>(z == 0 ? (uint32_t)v : acc_flip(v), rule, 0u);
+                        acc[z][bi][bj][(int)r] = acc_refill(u, z == 0);
                     });
                 });
             });
@@ -660,19 +660,19 @@ __device__ __forceinline__ void once_tile(const GemmArgs &a, int8_t *ep, int l, 
         u32x4 w;
         static_for<4>([&](auto t) {
             uint32_t x = 0;
-            static_for<4>([&](auto u) { x = put_residue<u>((uint32_t)value(t, (int)u), rule, x); });
+            static_for<4>([&](auto u) { x = put_residue<u>(value(t, (int)u), rule, x); });
             w[(int)t] = x ^ 0x80808080u;
         });
         *global_ptr(reinterpret_cast<u32x4 *>(E + plane * planeC + (col0 + 4 * bj) * a.m_pad)) = w;
     };
     static_for<BN>([&](auto bj) {
         if constexpr (P::real) {
-            store(bj, 0, [&](int t, int r) { return acc[0][t][bj][r]; });
+            store(bj, 0, [&](int t, int r) { return (uint32_t)acc[0][t][bj][r]; });
         } else {
-            store(bj, 0, [&](int t, int r) { return acc[0][t][bj][r] - acc[1][t][bj][r]; });
+            store(bj, 0, [&](int t, int r) { return acc_sub(acc[0][t][bj][r], acc[1][t][bj][r]); });
             store(bj, 1, [&](int t, int r) {
-                if constexpr (KIND == KIND_4M) return acc[2][t][bj][r] ^ kAccBias;
-                else return acc[2][t][bj][r] - acc[0][t][bj][r] - acc[1][t][bj][r];
+                if constexpr (KIND == KIND_4M) return acc_flip(acc[2][t][bj][r]);
+                else return acc_sub(acc[2][t][bj][r], acc[0][t][bj][r]) - (uint32_t)acc[1][t][bj][r];
             });
         }
     });
