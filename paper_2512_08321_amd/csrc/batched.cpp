@@ -527,6 +527,13 @@ ozc_status_t record_graph(ozc_context *h, BatchState *bs, BatchPlan &P) {
     return st;
 }
 
+// A call that fails before its plan's launches, which clear the non-finite flag: no
+// non-finite input was met.
+ozc_status_t failed_before_launch(ozc_context *h, ozc_status_t st) {
+    (void)launch_fill_u64(h->status_dev, 1, 0, h->stream);
+    return st;
+}
+
 // One batch, problem p with Ns[p] moduli: plan lookup (or build and record), launch.
 ozc_status_t run_plan(ozc_context *h, BatchState *bs, bool single,
                       const std::vector<Problem> &probs, const std::vector<int> &Ns) {
@@ -542,7 +549,7 @@ ozc_status_t run_plan(ozc_context *h, BatchState *bs, bool single,
         }
     if (!P) {
         BatchPlan *Q = new (std::nothrow) BatchPlan();
-        if (!Q) return OZC_STATUS_ALLOC_FAILED;
+        if (!Q) return failed_before_launch(h, OZC_STATUS_ALLOC_FAILED);
         ozc_status_t st = plan_batch(h, single, pol, probs, Ns, *Q);
         if (st == OZC_STATUS_SUCCESS) st = ensure_batch_ws(h, bs, Q->ws_bytes);
         if (st == OZC_STATUS_SUCCESS) st = bind(h, *Q, bs->ws);
@@ -550,8 +557,7 @@ ozc_status_t run_plan(ozc_context *h, BatchState *bs, bool single,
         if (st != OZC_STATUS_SUCCESS) {
             Q->release();
             delete Q;
-            (void)launch_fill_u64(h->status_dev, 1, 0, h->stream);  // nothing ran: no non-finite input met
-            return st;
+            return failed_before_launch(h, st);
         }
         Q->key = std::move(key);
         if (bs->plans.size() >= BatchState::kMaxPlans) {  // evict the least recently used
@@ -619,7 +625,7 @@ ozc_status_t run_plan_verified(ozc_context *h, BatchState *bs, bool single,
     const size_t o_chk = o_desc + desc_bytes;
     const size_t o_cin = o_chk + chk_bytes;
     ozc_status_t st = ensure_vws(h, o_cin + cin_bytes);
-    if (st != OZC_STATUS_SUCCESS) return st;
+    if (st != OZC_STATUS_SUCCESS) return failed_before_launch(h, st);
     char *vw = (char *)h->vws;
     unsigned long long *words = (unsigned long long *)vw;
     for (size_t p : chk) {  // C_in for the check and for reruns
@@ -769,7 +775,7 @@ ozc_status_t run_vbatched(ozc_context *h, bool single, int count, const ozc_op_t
         return OZC_STATUS_SUCCESS;
     }
     st = grid_sizes(h, bs);
-    if (st != OZC_STATUS_SUCCESS) return st;
+    if (st != OZC_STATUS_SUCCESS) return failed_before_launch(h, st);
     std::vector<int> Ns(probs.size(), h->nmod);
     if (!h->auto_n)
         return h->verify ? run_plan_verified(h, bs, single, probs, Ns)
@@ -791,7 +797,7 @@ ozc_status_t run_vbatched(ozc_context *h, bool single, int count, const ozc_op_t
         }
         std::vector<int> pred;
         st = predict_moduli_many(h, single, va, vb, pred);
-        if (st != OZC_STATUS_SUCCESS) return st;
+        if (st != OZC_STATUS_SUCCESS) return failed_before_launch(h, st);
         for (size_t i = 0; i < which.size(); ++i) Ns[which[i]] = pred[i];
     }
     // num_moduli: the largest count used
