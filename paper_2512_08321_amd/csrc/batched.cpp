@@ -309,7 +309,7 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
             o->blk_rows = P.blk_rows;
             P.blk_rows += batch_row_scan_blocks(*o);
             o->blk_finish = P.blk_finish;
-            P.blk_finish += batch_scan_finish_blocks(*o);
+            P.blk_finish += batch_scan_finish_blocks(*o, P.accurate);
             o->blk_split = sr.blocks;
             sr.blocks += batch_split_blocks(o->rows_pad, o->k_pad);
             ++sr.count;

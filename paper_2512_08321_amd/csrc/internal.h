@@ -253,7 +253,7 @@ hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, 
 // (or null) and ncounters counters.
 void batch_row_scan_plan(BatchOperand &op);
 int64_t batch_row_scan_blocks(const BatchOperand &op);
-int64_t batch_scan_finish_blocks(const BatchOperand &op);
+int64_t batch_scan_finish_blocks(const BatchOperand &op, bool accurate);
 hipError_t launch_batch_row_scan(const BatchOperand *ops, int nops, int64_t blocks, int64_t finish,
                                  bool single, bool accurate, uint32_t *status, uint32_t *counters,
                                  int ncounters, hipStream_t s);

@@ -309,13 +309,15 @@ __global__ __launch_bounds__(256) void pair_accu_exponents_kernel(AccuSide a, Ac
 // ---------------------------------------------------------------- one-read scaling scan
 // Maximum and FP64 sum of squares of every row in ONE read of the operand, and the
 // exponents from them (exponent_from_squares); the integer sums are formed only for the
-// rows that need them.  The maxima-then-integer-sums scans read every operand twice.
+// rows that need them, by a second read of these rows (exact_sums).
 // Bound by HBM: 16 rows x `chunk` k-elements per block of 1024 threads, eight loads in
 // flight per thread.  Rows with contiguous k take a wave each; rows contiguous with each
 // other take 16 rows (256-byte runs of complex128) x 64 k per load.
 // With one part per row (chunk >= k) the block finishes its rows, exponents included: one
 // launch, no atomics and nothing to clear.  With several parts they go to part_max and
-// part_sq ([part][row]) and scan_finish_kernel combines them.
+// part_sq ([part][row]) and scan_finish_kernel combines them: a block per group and part, each
+// with the whole of its rows' parts, so that all of them see which rows need their integer sums;
+// each block then forms its own part of these and the last one to arrive has the total.
 // Accurate mode takes the maxima only, and clears the rows' bound-product maxima X.
 // Whole calls against the two-read scans with their fill and exponent launches: ZGEMM 64^3
 // 46.1 -> 29.0 us (9 launches -> 4, one split launch among them), 384 x 320 x 40000
@@ -324,36 +326,81 @@ constexpr int kScanRows = 16, kScanThreads = 1024, kScanLanes = kScanThreads / k
 constexpr int kScanUnroll = 8;
 
 struct RowScan {
+    // places the parts' results in `scratch` (row_scan_scratch bytes)
+    __host__ __device__ __forceinline__ void use(void *scratch) {
+        part_max = (uint64_t *)scratch;
+        part_sq = (double *)(part_max + parts * rows_pad);
+        part_sum = (uint64_t *)(part_sq + parts * rows_pad);
+        arrived = (uint32_t *)(part_sum + rows_pad);
+    }
     OperandView v;
     int64_t rows_pad, chunk;
     int32_t parts, groups;   // parts per row, groups of kScanRows rows (rows_pad / 16)
     uint64_t *part_max;      // parts > 1: [parts][rows_pad]
     double *part_sq;
+    uint64_t *part_sum;      // [rows_pad]: integer sums ...
+    uint32_t *arrived;       // [groups]: ... and the blocks that have added to them
     int16_t *mu;             // fast mode: exponents
     uint64_t *maxbits;       // accurate mode: row maxima ...
     int32_t *X;              // ... and bound maxima to clear
 };
 
-// sigma of one row by `lanes` threads (thread `lane` of them): the partial sum.
+// Integer sums over the k-elements h0 .. h1 - 1 of the block's rows from r0 on with need[i] != 0
+// (the rows' maxima; `rows` of them), added to exact[i] (cleared).  All threads of the block
+// call this.  Up to four rows are taken one by one by all threads (rows next to a threshold,
+// one in 10^3..10^4), more of them together in the scan's access pattern, one more read of the
+// operand: operands beyond the range of FP64 squares need every row.  One by one, a load at a
+// time and by the few blocks that combine the parts, whole operands took ZGEMM 384 x 320 x 40000
+// 2250 us (now 1007; 781 within the range), DGEMM 8000 x 64 x 9000 2041 (821; 715), ZGEMM
+// 2048^3 (A as it is, B transposed) 668 (549; 530).
+constexpr int kExactByRow = 4, kExactUnroll = 4;
 template <int EK>
-__device__ __forceinline__ uint64_t exact_sigma_part(const OperandView &v, int64_t r, uint64_t mb,
-                                                     int lane, int lanes) {
-    const int sh = kSigmaFracBits - ilogb_bits(mb);
+__device__ __forceinline__ void exact_sums(const OperandView &v, int64_t r0, int64_t h0, int64_t h1,
+                                           const uint64_t *need, int rows, unsigned long long *exact) {
+    int tid = threadIdx.x;  // not shared with the scan's loop, which has no register to spare
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const bool each = rows <= kExactByRow, together = !each && !v.contig_h;
+    // this thread's rows i, i + di, ... and elements `first`, first + step, ... of them
+    const int threads = blockDim.x;
+    int i = each ? 0 : (together ? lane % kScanRows : tid >> 6);
+    const int di = each ? 1 : (together ? kScanRows : threads / 64);
+    const int first = each ? tid : (together ? tid / kScanRows : lane);
+    const int step = each ? threads : (together ? threads / kScanRows : 64);
     uint64_t s = 0;
-    for (int64_t h = lane; h < v.k; h += lanes) {
-        double re, im;
-        load_elem<EK>(v.base, r * v.stride_r + h * v.stride_h, re, im);
-        const uint64_t a = ceil_scaled(re, sh), b = ceil_scaled(im, sh);
-        s += a * a + b * b;
+    for (; i < kScanRows; i += di) {
+        if (need[i] == 0) continue;
+        const int sh = kSigmaFracBits - ilogb_bits(need[i]);
+        const int64_t base = (r0 + i) * v.stride_r;
+        s = 0;
+#pragma unroll 1
+        for (int64_t h = h0 + first; h < h1; h += step * kExactUnroll) {
+            double re[kExactUnroll], im[kExactUnroll];
+#pragma unroll
+            for (int u = 0; u < kExactUnroll; ++u)
+                load_elem<EK>(v.base, base + min(h + u * step, h1 - 1) * v.stride_h, re[u], im[u]);
+#pragma unroll
+            for (int u = 0; u < kExactUnroll; ++u) {
+                const uint64_t a = ceil_scaled(re[u], sh), b = ceil_scaled(im[u], sh);
+                if (h + u * step < h1) s += a * a + b * b;
+            }
+        }
+        if (together) break;
+        s = wave_sum_u64(s);
+        if (lane == 0) atomicAdd(&exact[i], (unsigned long long)s);
     }
-    return s;
+    if (!together) return;
+#pragma unroll
+    for (int off = 32; off >= kScanRows; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane < kScanRows && s) atomicAdd(&exact[lane], (unsigned long long)s);
 }
 
 // Exponents (or, accurate mode, maxima) of the block's kScanRows rows from r0 on: m and q
-// hold row r0 + tid's maximum and sum of squares in threads tid < kScanRows.  All threads
-// of the block call this (it synchronises).
+// hold row r0 + tid's maximum and sum of squares in threads tid < kScanRows.  `part` of
+// a.parts blocks on the same rows; each has the same m and q.  All threads of the block call
+// this (it synchronises).
 template <int EK, bool ACCU>
-__device__ __forceinline__ void scan_finish(const RowScan &a, int64_t r0, uint64_t m, double q,
+__device__ __forceinline__ void scan_finish(const RowScan &a, int64_t r0, int part, uint64_t m, double q,
                                             const NTable *tab) {
     __shared__ uint64_t need[kScanRows];
     __shared__ unsigned long long exact[kScanRows];
@@ -379,17 +426,27 @@ __device__ __forceinline__ void scan_finish(const RowScan &a, int64_t r0, uint64
         need[tid] = open ? m : 0;
         exact[tid] = 0;
     }
-    if (__syncthreads_or(open)) {
-        for (int i = 0; i < kScanRows; ++i) {
-            if (need[i] == 0) continue;
-            uint64_t s = exact_sigma_part<EK>(a.v, r0 + i, need[i], tid, blockDim.x);
-            s = wave_sum_u64(s);
-            if ((tid & 63) == 0) atomicAdd(&exact[i], (unsigned long long)s);
-        }
+    if (mine && !open && part == 0) a.mu[row] = (int16_t)mu;
+    const int rows = __syncthreads_count(open);
+    if (rows == 0) return;
+    const int64_t h0 = part * a.chunk;
+    exact_sums<EK>(a.v, r0, h0, min(a.v.k, h0 + a.chunk), need, rows, exact);
+    __syncthreads();
+    // (everything a thread keeps across the sums costs the scan a register: from LDS again)
+    const uint64_t top = threadIdx.x < kScanRows ? need[threadIdx.x] : 0;
+    uint64_t s = top ? exact[threadIdx.x] : 0;
+    if (a.parts > 1) {  // the parts meet: the last block to arrive has the sums
+        __shared__ bool last;
+        uint64_t *sum = a.part_sum + r0 + threadIdx.x;
+        if (top) atomicAdd((unsigned long long *)sum, (unsigned long long)s);
+        __threadfence();
+        if (threadIdx.x == 0) last = atomicAdd(&a.arrived[r0 / kScanRows], 1u) == (uint32_t)a.parts - 1;
         __syncthreads();
-        if (open) mu = ct->fast_tmax - fast_index(exact[tid], ct) - ilogb_bits(m);
+        if (!last) return;
+        __threadfence();
+        if (top) s = atomicAdd((unsigned long long *)sum, 0ull);
     }
-    if (mine) a.mu[row] = (int16_t)mu;
+    if (top) a.mu[r0 + threadIdx.x] = (int16_t)(ct->fast_tmax - fast_index(s, ct) - ilogb_bits(top));
 }
 
 template <int EK, bool ACCU>
@@ -452,15 +509,26 @@ __device__ __forceinline__ void row_scan_body(const RowScan &a, int group, int p
         }
         if (a.parts > 1 && r0 + tid < a.rows_pad) {
             a.part_max[part * a.rows_pad + r0 + tid] = m;
-            if constexpr (!ACCU) a.part_sq[part * a.rows_pad + r0 + tid] = q;
+            if constexpr (!ACCU) {
+                a.part_sq[part * a.rows_pad + r0 + tid] = q;
+                if (part == 0) a.part_sum[r0 + tid] = 0;
+                if (part == 0 && tid == 0) a.arrived[group] = 0;
+            }
         }
     }
-    if (a.parts == 1) scan_finish<EK, ACCU>(a, r0, m, q, tab);
+    if (a.parts == 1) scan_finish<EK, ACCU>(a, r0, 0, m, q, tab);
 }
 
-// Rows scanned in several parts: the 16 rows from r0 on, 16 threads per row over the parts.
+// Rows scanned in several parts: group and part of block `blk` (accurate mode: one block per
+// group), 16 threads per row over the parts.
+template <bool ACCU>
+__host__ __device__ __forceinline__ int64_t scan_finish_blocks(int64_t groups, int64_t parts) {
+    return parts > 1 ? (ACCU ? groups : groups * parts) : 0;
+}
 template <int EK, bool ACCU>
-__device__ __forceinline__ void scan_combine(const RowScan &w, int64_t r0, const NTable *tab) {
+__device__ __forceinline__ void scan_combine(const RowScan &w, int blk, const NTable *tab) {
+    const int part = blk / w.groups;
+    const int64_t r0 = (int64_t)(blk - part * w.groups) * kScanRows;
     __shared__ uint64_t lm[16][kScanRows];
     __shared__ double lq[16][kScanRows];
     const int tid = threadIdx.x, rl = tid % kScanRows, pl = tid / kScanRows;
@@ -481,7 +549,7 @@ __device__ __forceinline__ void scan_combine(const RowScan &w, int64_t r0, const
             q += lq[p][tid];
         }
     }
-    scan_finish<EK, ACCU>(w, r0, m, q, tab);
+    scan_finish<EK, ACCU>(w, r0, part, m, q, tab);
 }
 
 // ---------------------------------------------------------------- accurate-mode magnitudes
@@ -751,6 +819,22 @@ struct SplitSide {
 // block (CGEMM 4096 x 4096 x 512 at N = 6: 352 us with 4 rows, 341 with 16, 344 in two launches);
 // longer rows are no faster in one launch (1000^3 113 against 107 us: too few waves per block).
 constexpr int kPrepMaxK = 512;
+
+// sigma of one row by `lanes` threads (thread `lane` of them): the partial sum.
+template <int EK>
+__device__ __forceinline__ uint64_t exact_sigma_part(const OperandView &v, int64_t r, uint64_t mb,
+                                                     int lane, int lanes) {
+    const int sh = kSigmaFracBits - ilogb_bits(mb);
+    uint64_t s = 0;
+    for (int64_t h = lane; h < v.k; h += lanes) {
+        double re, im;
+        load_elem<EK>(v.base, r * v.stride_r + h * v.stride_h, re, im);
+        const uint64_t a = ceil_scaled(re, sh), b = ceil_scaled(im, sh);
+        s += a * a + b * b;
+    }
+    return s;
+}
+
 template <int EK, int NPLANES, int W>
 __device__ __forceinline__ void prep_rows_body(const SplitSide &w, int64_t r0, int64_t k_pad,
                                                const NTable *__restrict__ tab, int nmod) {
@@ -849,7 +933,7 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(RowScan a, RowScan b, 
                                                           const NTable *tab) {
     const int blk = (int)blockIdx.x;
     const bool second = blk >= blocksA;
-    scan_combine<EK, ACCU>(second ? b : a, (int64_t)(second ? blk - blocksA : blk) * kScanRows, tab);
+    scan_combine<EK, ACCU>(second ? b : a, second ? blk - blocksA : blk, tab);
 }
 // The predictor's scans (maxima, then integer sums with its statistics) of both operands
 // of one call in one launch per pass, blocks of A first, then those of B, each on the grid its own launch would have: one ramp-up and tail per pass
@@ -983,8 +1067,7 @@ __device__ __forceinline__ RowScan row_scan_of(const BatchOperand &op) {
     w.chunk = op.scan_chunk;
     w.parts = op.scan_parts;
     w.groups = (int32_t)(op.rows_pad / kScanRows);
-    w.part_max = (uint64_t *)op.res;  // free until the split
-    w.part_sq = (double *)(w.part_max + op.scan_parts * op.rows_pad);
+    w.use(op.res);  // free until the split
     w.mu = op.mu;
     w.maxbits = op.maxbits;
     w.X = op.X;
@@ -1010,7 +1093,7 @@ template <int EK, bool ACCU>
 __global__ __launch_bounds__(256) void batch_scan_finish_kernel(const BatchOperand *ops, int nops) {
     const int64_t b = blockIdx.x;  // an operand scanned in one part has no blocks here
     const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_finish; });
-    scan_combine<EK, ACCU>(row_scan_of(ops[o]), (b - ops[o].blk_finish) * kScanRows, ops[o].tab);
+    scan_combine<EK, ACCU>(row_scan_of(ops[o]), (int)(b - ops[o].blk_finish), ops[o].tab);
 }
 
 __global__ __launch_bounds__(256) void batch_accu_exponents_kernel(const BatchOperand *ops, int nops,
@@ -1165,8 +1248,7 @@ static RowScan row_scan_of(const OperandView &v, int64_t rows_pad, int64_t group
         parts = std::max<int64_t>(1, std::min((v.k + 2047) / 2048, (1023 + groups_all) / groups_all));
     w.chunk = (v.k + parts - 1) / parts;
     w.parts = (int32_t)parts;
-    w.part_max = (uint64_t *)scratch;
-    w.part_sq = (double *)(w.part_max + parts * rows_pad);
+    w.use(scratch);
     return w;
 }
 
@@ -1174,7 +1256,8 @@ template <int EK>
 static hipError_t row_scans_ek(const RowScan &a, const RowScan &b, bool accurate, const NTable *tab,
                                uint32_t *status, hipStream_t s) {
     const int64_t blocks = (int64_t)a.groups * a.parts + (int64_t)b.groups * b.parts;
-    const int fa = a.parts > 1 ? a.groups : 0, fb = b.parts > 1 ? b.groups : 0;
+    const int fa = (int)(accurate ? scan_finish_blocks<true>(a.groups, a.parts) : scan_finish_blocks<false>(a.groups, a.parts));
+    const int fb = (int)(accurate ? scan_finish_blocks<true>(b.groups, b.parts) : scan_finish_blocks<false>(b.groups, b.parts));
     if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks), block(kScanThreads);
     if (accurate) hipLaunchKernelGGL((pair_row_scan_kernel<EK, true>), grid, block, 0, s, a, b, tab, status);
@@ -1342,8 +1425,9 @@ void batch_row_scan_plan(BatchOperand &op) {
     op.scan_chunk = (op.v.k + parts - 1) / parts;
 }
 int64_t batch_row_scan_blocks(const BatchOperand &op) { return op.rows_pad / kScanRows * op.scan_parts; }
-int64_t batch_scan_finish_blocks(const BatchOperand &op) {
-    return op.scan_parts > 1 ? op.rows_pad / kScanRows : 0;
+int64_t batch_scan_finish_blocks(const BatchOperand &op, bool accurate) {
+    const int64_t groups = op.rows_pad / kScanRows;
+    return accurate ? scan_finish_blocks<true>(groups, op.scan_parts) : scan_finish_blocks<false>(groups, op.scan_parts);
 }
 
 template <int EK, bool ACCU>
