@@ -472,6 +472,8 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     // Statistics computed by the moduli-count prediction of this call (same operands, same
     // k) are taken over; otherwise one scan reads both operands.  Partial results of rows
     // scanned in several parts go where the residues will be written.
+    const int64_t res_row = (int64_t)h->nmod * L.planes * L.k_pad;
+    const ScanScratch scan{resA, res_row * L.m_pad, resB, res_row * L.n_pad};
     uint32_t *clear = h->keep_status ? nullptr : status;
     // Short rows are scanned and split by one launch (the test hook's exponents come between).
     const bool in_one = h->mode == OZC_MODE_FAST && !pre && !ins && fault == 0 && prep_in_one(k);
@@ -483,14 +485,14 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
             OZC_TRY(launch_pair_fast_exponents(h->pre.maxA, h->pre.sigA, m, L.m_pad, muA, h->pre.maxB,
                                                h->pre.sigB, n, L.n_pad, nuB, tab, status, s));
         else
-            OZC_TRY(launch_row_exponents(vA, vB, ek, L.m_pad, L.n_pad, muA, nuB, resA, resB, tab, clear, s));
+            OZC_TRY(launch_row_exponents(vA, vB, ek, L.m_pad, L.n_pad, muA, nuB, scan, tab, clear, s));
         abits = th.max_abits_fast;
     } else {
         int8_t *barA = (int8_t *)(ws + L.barA), *barB = (int8_t *)(ws + L.barB);
         const uint64_t *cmaxA = pre ? h->pre.maxA : maxA, *cmaxB = pre ? h->pre.maxB : maxB;
         if (pre) OZC_TRY(launch_fill_u64((uint64_t *)XA, (int64_t)(L.muA - L.XA) / 8, 0, s));
         else
-            OZC_TRY(launch_row_maxima(vA, vB, ek, L.m_pad, L.n_pad, maxA, maxB, XA, YB, resA, resB, clear, s));
+            OZC_TRY(launch_row_maxima(vA, vB, ek, L.m_pad, L.n_pad, maxA, maxB, XA, YB, scan, clear, s));
         const AccuSide sA{vA, cmaxA, barA, XA, muA, L.m_pad}, sB{vB, cmaxB, barB, YB, nuB, L.n_pad};
         OZC_TRY(launch_pair_ceil7(sA, sB, ek, L.k_pad, s));
         BoundArgs ba{barA, barB, L.m_pad, L.n_pad, L.k_pad, XA, YB, L.tile, real ? 1 : 0};

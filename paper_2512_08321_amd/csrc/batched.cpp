@@ -305,7 +305,7 @@ ozc_status_t plan_batch(const ozc_context *h, bool single, const ozc_batch_polic
                 o->blk_exp = P.blk_exp;
                 P.blk_exp += batch_exp_blocks(o->rows_pad);
             }
-            batch_row_scan_plan(*o);
+            if (!batch_row_scan_plan(*o, o->nmod * P.planes * o->rows_pad * o->k_pad)) return OZC_STATUS_NOT_SUPPORTED;
             o->blk_rows = P.blk_rows;
             P.blk_rows += batch_row_scan_blocks(*o);
             o->blk_finish = P.blk_finish;

@@ -84,21 +84,26 @@ __host__ __device__ constexpr bool elem_real(int ek) { return ek >= kElemD; }
 
 // Kernel launchers (all asynchronous on `stream`).
 hipError_t launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s);
+struct ScanScratch {  // free memory for rows scanned in several parts, row_scan_scratch bytes
+    void *A;
+    int64_t bytesA;
+    void *B;
+    int64_t bytesB;
+};
+// Parts that the rows of k elements are scanned in, with `groups` groups of 16 rows in the
+// call (0: in a batch), and the memory they take for rows_pad rows.
+int64_t row_scan_parts(int64_t k, int64_t groups);
+int64_t row_scan_scratch(int64_t rows_pad, int64_t parts);
 // Fast-mode exponents of the rows of op(A) (mu, m_pad entries) and the columns of op(B)
-// (nu, n_pad), one read of each operand.  scratchA and scratchB: free memory for rows
-// scanned in several parts, at least row_scan_scratch(rows_pad, k) bytes each.  status (or
-// null): cleared (the residue split sets it for rows holding inf or NaN).
+// (nu, n_pad), one read of each operand.  status (or null): cleared (the residue split sets
+// it for rows holding inf or NaN).
 hipError_t launch_row_exponents(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
-                                int64_t n_pad, int16_t *mu, int16_t *nu, void *scratchA,
-                                void *scratchB, const NTable *tab, uint32_t *status, hipStream_t s);
+                                int64_t n_pad, int16_t *mu, int16_t *nu, const ScanScratch &scratch,
+                                const NTable *tab, uint32_t *status, hipStream_t s);
 // The same scan for accurate mode: row maxima, and the bound maxima X, Y cleared.
 hipError_t launch_row_maxima(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
                              int64_t n_pad, uint64_t *maxA, uint64_t *maxB, int32_t *X, int32_t *Y,
-                             void *scratchA, void *scratchB, uint32_t *status, hipStream_t s);
-// Parts have at least 1024 k-elements and take 16 bytes per padded row.
-inline int64_t row_scan_scratch(int64_t rows_pad, int64_t k) {
-    return 16 * rows_pad * ((k + 1023) / 1024);
-}
+                             const ScanScratch &scratch, uint32_t *status, hipStream_t s);
 // The predictor's scans of both operands of one call in one launch: row maxima (no sums
 // given), or, maxima final and the sums zeroed, sigma = sum ceil(|x| 2^(20 - e_r))^2,
 // tau = sum ceil(|x| 2^(20 - e_r)) and the zero-real count (zeros is shared).
@@ -249,9 +254,10 @@ int64_t batch_split_blocks(int64_t rows_pad, int64_t k_pad);
 hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, bool single,
                              bool stats, hipStream_t s);
 // The scaling scan: exponents (accurate mode: maxima, and the bound maxima cleared) of every
-// operand.  scan_parts and scan_chunk come from batch_row_scan_plan.  Clears the status word
-// (or null) and ncounters counters.
-void batch_row_scan_plan(BatchOperand &op);
+// operand.  scan_parts and scan_chunk come from batch_row_scan_plan (false: the parts' results
+// have no room in the operand's res_bytes of residues, where they go).  Clears the status
+// word (or null) and ncounters counters.
+bool batch_row_scan_plan(BatchOperand &op, int64_t res_bytes);
 int64_t batch_row_scan_blocks(const BatchOperand &op);
 int64_t batch_scan_finish_blocks(const BatchOperand &op, bool accurate);
 hipError_t launch_batch_row_scan(const BatchOperand *ops, int nops, int64_t blocks, int64_t finish,

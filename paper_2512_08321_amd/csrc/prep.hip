@@ -1237,15 +1237,23 @@ hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, bool 
 
 // Parts of a row: one while a thread's share of it is at most 64 loads or both operands'
 // row groups give every CU a block of 1024 threads (one launch does the whole phase then);
-// otherwise parts of at least 2048 k that bring the grid to about 1024 blocks.
+// otherwise parts of 1024 k and more that bring the grid to about 1024 blocks.  A batch
+// (groups_all = 0) has other blocks to fill the chip with: only the serial chain of a long row is cut.
+int64_t row_scan_parts(int64_t k, int64_t groups_all) {
+    if (k <= 64 * kScanLanes || groups_all >= 512) return 1;
+    const int64_t parts = (k + 2047) / 2048;
+    return groups_all > 0 ? std::max<int64_t>(1, std::min(parts, (1023 + groups_all) / groups_all)) : parts;
+}
+int64_t row_scan_scratch(int64_t rows_pad, int64_t parts) {
+    return parts > 1 ? 16 * parts * rows_pad + 8 * rows_pad + 4 * (rows_pad / kScanRows) : 0;
+}
+
 static RowScan row_scan_of(const OperandView &v, int64_t rows_pad, int64_t groups_all, void *scratch) {
     RowScan w{};
     w.v = v;
     w.rows_pad = rows_pad;
     w.groups = (int32_t)(rows_pad / kScanRows);
-    int64_t parts = 1;
-    if (v.k > 64 * kScanLanes && groups_all < 512)
-        parts = std::max<int64_t>(1, std::min((v.k + 2047) / 2048, (1023 + groups_all) / groups_all));
+    const int64_t parts = row_scan_parts(v.k, groups_all);
     w.chunk = (v.k + parts - 1) / parts;
     w.parts = (int32_t)parts;
     w.use(scratch);
@@ -1282,12 +1290,14 @@ static hipError_t row_scans(RowScan &a, RowScan &b, int ek, bool accurate, const
 }
 
 hipError_t launch_row_exponents(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
-                                int64_t n_pad, int16_t *mu, int16_t *nu, void *scratchA,
-                                void *scratchB, const NTable *tab, uint32_t *status, hipStream_t s) {
+                                int64_t n_pad, int16_t *mu, int16_t *nu, const ScanScratch &sc,
+                                const NTable *tab, uint32_t *status, hipStream_t s) {
     if (va.rows <= 0 || vb.rows <= 0 || va.k <= 0 || m_pad % kScanRows || n_pad % kScanRows)
         return hipErrorInvalidValue;
     const int64_t groups = (m_pad + n_pad) / kScanRows;
-    RowScan a = row_scan_of(va, m_pad, groups, scratchA), b = row_scan_of(vb, n_pad, groups, scratchB);
+    RowScan a = row_scan_of(va, m_pad, groups, sc.A), b = row_scan_of(vb, n_pad, groups, sc.B);
+    if (row_scan_scratch(m_pad, a.parts) > sc.bytesA || row_scan_scratch(n_pad, b.parts) > sc.bytesB)
+        return hipErrorInvalidValue;
     a.mu = mu;
     b.mu = nu;
     return row_scans(a, b, ek, false, tab, status, s);
@@ -1295,11 +1305,13 @@ hipError_t launch_row_exponents(const OperandView &va, const OperandView &vb, in
 
 hipError_t launch_row_maxima(const OperandView &va, const OperandView &vb, int ek, int64_t m_pad,
                              int64_t n_pad, uint64_t *maxA, uint64_t *maxB, int32_t *X, int32_t *Y,
-                             void *scratchA, void *scratchB, uint32_t *status, hipStream_t s) {
+                             const ScanScratch &sc, uint32_t *status, hipStream_t s) {
     if (va.rows <= 0 || vb.rows <= 0 || va.k <= 0 || m_pad % kScanRows || n_pad % kScanRows)
         return hipErrorInvalidValue;
     const int64_t groups = (m_pad + n_pad) / kScanRows;
-    RowScan a = row_scan_of(va, m_pad, groups, scratchA), b = row_scan_of(vb, n_pad, groups, scratchB);
+    RowScan a = row_scan_of(va, m_pad, groups, sc.A), b = row_scan_of(vb, n_pad, groups, sc.B);
+    if (row_scan_scratch(m_pad, a.parts) > sc.bytesA || row_scan_scratch(n_pad, b.parts) > sc.bytesB)
+        return hipErrorInvalidValue;
     a.maxbits = maxA;
     b.maxbits = maxB;
     a.X = X;
@@ -1416,13 +1428,11 @@ hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, 
     return hipGetLastError();
 }
 
-// As row_scan_of for a single call, on the operand alone: a batch has other blocks to fill
-// the chip with, so only the serial chain of a long row is cut.
-void batch_row_scan_plan(BatchOperand &op) {
-    int64_t parts = 1;
-    if (op.v.k > 64 * kScanLanes) parts = (op.v.k + 2047) / 2048;
+bool batch_row_scan_plan(BatchOperand &op, int64_t res_bytes) {
+    const int64_t parts = row_scan_parts(op.v.k, 0);
     op.scan_parts = (int32_t)parts;
     op.scan_chunk = (op.v.k + parts - 1) / parts;
+    return row_scan_scratch(op.rows_pad, parts) <= res_bytes;
 }
 int64_t batch_row_scan_blocks(const BatchOperand &op) { return op.rows_pad / kScanRows * op.scan_parts; }
 int64_t batch_scan_finish_blocks(const BatchOperand &op, bool accurate) {
