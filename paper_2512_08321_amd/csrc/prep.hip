@@ -142,12 +142,12 @@ __device__ __forceinline__ void maxabs_strided_body(const OperandView &v, uint64
 // ---------------------------------------------------------------- fast-mode sum of squares
 // sigma_r = sum over the 2k reals of ceil(|x| 2^(F - e_r))^2, e_r = floor(log2 max|x|):
 // an integer upper bound of 2^(2F) ||row / 2^e_r||_2^2, independent of summation order.
-// With STATS (the moduli-count predictor's statistics, taken in the same pass):
+// The moduli-count predictor takes it with its statistics in one pass:
 // tau_r = sum ceil(|x| 2^(F - e_r)) (an upper bound of 2^F ||row / 2^e_r||_1) and the
 // number of zero reals of the operand, added to *zeros (all rows, finite or not).
 // Real operands have k reals per row (the imaginary parts do not exist).
 
-template <int EK, bool STATS>
+template <int EK>
 __device__ __forceinline__ void sigma_contig_body(const OperandView &v, const uint64_t *maxbits,
                                                   uint64_t *sigma, uint64_t *tau, uint64_t *zeros,
                                                   int64_t bx, int64_t by) {
@@ -156,7 +156,6 @@ __device__ __forceinline__ void sigma_contig_body(const OperandView &v, const ui
     if (r >= v.rows) return;
     const uint64_t mb = maxbits[r];
     const bool live = mb != 0 && mb < kInfBits;
-    if (!STATS && !live) return;
     const int sh = live ? kSigmaFracBits - ilogb_bits(mb) : 0;
     const int64_t h0 = by * kHChunk;
     const int64_t h1 = min(v.k, h0 + kHChunk);
@@ -164,23 +163,21 @@ __device__ __forceinline__ void sigma_contig_body(const OperandView &v, const ui
     for (int64_t h = h0 + lane; h < h1; h += 64) {
         double re, im;
         load_elem<EK>(v.base, r * v.stride_r + h, re, im);
-        if constexpr (STATS) z += (re == 0.0) + (!elem_real(EK) && im == 0.0);
+        z += (re == 0.0) + (!elem_real(EK) && im == 0.0);
         if (!live) continue;
         uint64_t a = ceil_scaled(re, sh), b = ceil_scaled(im, sh);
         s += a * a + b * b;
-        if constexpr (STATS) t += a + b;
+        t += a + b;
     }
     s = wave_sum_u64(s);
     if (lane == 0 && s) atomicAdd((unsigned long long *)&sigma[r], (unsigned long long)s);
-    if constexpr (STATS) {
-        t = wave_sum_u64(t);
-        z = wave_sum_u64(z);
-        if (lane == 0 && t) atomicAdd((unsigned long long *)&tau[r], (unsigned long long)t);
-        if (lane == 0 && z) atomicAdd((unsigned long long *)zeros, (unsigned long long)z);
-    }
+    t = wave_sum_u64(t);
+    z = wave_sum_u64(z);
+    if (lane == 0 && t) atomicAdd((unsigned long long *)&tau[r], (unsigned long long)t);
+    if (lane == 0 && z) atomicAdd((unsigned long long *)zeros, (unsigned long long)z);
 }
 
-template <int EK, bool STATS>
+template <int EK>
 __device__ __forceinline__ void sigma_strided_body(const OperandView &v, const uint64_t *maxbits,
                                                    uint64_t *sigma, uint64_t *tau, uint64_t *zeros,
                                                    int64_t bx, int64_t by, int hc) {
@@ -188,7 +185,6 @@ __device__ __forceinline__ void sigma_strided_body(const OperandView &v, const u
     if (r >= v.rows) return;
     const uint64_t mb = maxbits[r];
     const bool live = mb != 0 && mb < kInfBits;
-    if (!STATS && !live) return;
     const int sh = live ? kSigmaFracBits - ilogb_bits(mb) : 0;
     const int64_t h0 = by * hc;
     const int64_t h1 = min(v.k, h0 + hc);
@@ -196,17 +192,15 @@ __device__ __forceinline__ void sigma_strided_body(const OperandView &v, const u
     for (int64_t h = h0; h < h1; ++h) {
         double re, im;
         load_elem<EK>(v.base, r + h * v.stride_h, re, im);
-        if constexpr (STATS) z += (re == 0.0) + (!elem_real(EK) && im == 0.0);
+        z += (re == 0.0) + (!elem_real(EK) && im == 0.0);
         if (!live) continue;
         uint64_t a = ceil_scaled(re, sh), b = ceil_scaled(im, sh);
         s += a * a + b * b;
-        if constexpr (STATS) t += a + b;
+        t += a + b;
     }
     if (s) atomicAdd((unsigned long long *)&sigma[r], (unsigned long long)s);
-    if constexpr (STATS) {
-        if (t) atomicAdd((unsigned long long *)&tau[r], (unsigned long long)t);
-        if (z) atomicAdd((unsigned long long *)zeros, (unsigned long long)z);
-    }
+    if (t) atomicAdd((unsigned long long *)&tau[r], (unsigned long long)t);
+    if (z) atomicAdd((unsigned long long *)zeros, (unsigned long long)z);
 }
 
 // ---------------------------------------------------------------- exponents
@@ -943,28 +937,28 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(RowScan a, RowScan b, 
 struct ScanSide {
     OperandView v;
     uint64_t *maxbits, *sigma;
-    uint64_t *tau, *zeros;  // pass 2: the predictor's statistics
+    uint64_t *tau, *zeros;  // with the sums: the predictor's statistics
     int64_t gx, blocks;     // grid columns and blocks of this operand
     int hc;                 // strided layout: k-elements per thread
 };
-// PASS 0: row maxima; 1: sums of squares; 2: sums of squares and the statistics
-template <int EK, int PASS>
+// Row maxima, or (SUMS) sums of squares and the statistics
+template <int EK, bool SUMS>
 __device__ __forceinline__ void scan_side(const ScanSide &sd, int64_t lb) {
     const int64_t bx = lb % sd.gx, by = lb / sd.gx;
     if (sd.v.contig_h) {
-        if constexpr (PASS > 0) sigma_contig_body<EK, PASS == 2>(sd.v, sd.maxbits, sd.sigma, sd.tau, sd.zeros, bx, by);
+        if constexpr (SUMS) sigma_contig_body<EK>(sd.v, sd.maxbits, sd.sigma, sd.tau, sd.zeros, bx, by);
         else maxabs_contig_body<EK>(sd.v, sd.maxbits, bx, by);
     } else {
-        if constexpr (PASS > 0)
-            sigma_strided_body<EK, PASS == 2>(sd.v, sd.maxbits, sd.sigma, sd.tau, sd.zeros, bx, by, sd.hc);
+        if constexpr (SUMS)
+            sigma_strided_body<EK>(sd.v, sd.maxbits, sd.sigma, sd.tau, sd.zeros, bx, by, sd.hc);
         else maxabs_strided_body<EK>(sd.v, sd.maxbits, bx, by, sd.hc);
     }
 }
-template <int EK, int PASS>
+template <int EK, bool SUMS>
 __global__ __launch_bounds__(256) void pair_scan_kernel(ScanSide a, ScanSide b) {
     const int64_t blk = blockIdx.x;
-    if (blk < a.blocks) scan_side<EK, PASS>(a, blk);
-    else scan_side<EK, PASS>(b, blk - a.blocks);
+    if (blk < a.blocks) scan_side<EK, SUMS>(a, blk);
+    else scan_side<EK, SUMS>(b, blk - a.blocks);
 }
 // The exponents of both operands of one call in one launch (the blocks of A first).
 struct ExpSide {
@@ -1040,9 +1034,9 @@ __host__ __device__ __forceinline__ int64_t scan_grid_y(const OperandView &v) {
     return (v.k + hc - 1) / hc;
 }
 
-// The predictor's scans.  PASS 0: row maxima; 2: integer sums and statistics
+// The predictor's scans: row maxima, or (SUMS) integer sums and statistics
 // (BatchOperand::sigma, tau, zeros)
-template <int EK, int PASS>
+template <int EK, bool SUMS>
 __global__ __launch_bounds__(256) void batch_scan_kernel(const BatchOperand *ops, int nops) {
     const int64_t b = blockIdx.x;
     const int o = find_seg(nops, b, [&](int i) { return ops[i].blk_scan; });
@@ -1051,11 +1045,11 @@ __global__ __launch_bounds__(256) void batch_scan_kernel(const BatchOperand *ops
     const int64_t bx = lb % gx, by = lb / gx;
     const BatchOperand &op = ops[o];
     if (v.contig_h) {
-        if constexpr (PASS > 0) sigma_contig_body<EK, true>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by);
+        if constexpr (SUMS) sigma_contig_body<EK>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by);
         else maxabs_contig_body<EK>(v, op.maxbits, bx, by);
     } else {
-        if constexpr (PASS > 0)
-            sigma_strided_body<EK, true>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by, kHChunk / 8);
+        if constexpr (SUMS)
+            sigma_strided_body<EK>(v, op.maxbits, op.sigma, op.tau, op.zeros, bx, by, kHChunk / 8);
         else maxabs_strided_body<EK>(v, op.maxbits, bx, by, kHChunk / 8);
     }
 }
@@ -1212,13 +1206,13 @@ static ScanSide scan_side_of(const OperandView &v, uint64_t *maxbits, uint64_t *
 }
 
 template <int EK>
-hipError_t pair_scans_ek(const ScanSide &a, const ScanSide &b, int pass, hipStream_t s) {
+hipError_t pair_scans_ek(const ScanSide &a, const ScanSide &b, bool sums, hipStream_t s) {
     const int64_t blocks = a.blocks + b.blocks;
     if (blocks == 0) return hipSuccess;
     if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks);
-    if (pass == 2) hipLaunchKernelGGL((pair_scan_kernel<EK, 2>), grid, dim3(256), 0, s, a, b);
-    else hipLaunchKernelGGL((pair_scan_kernel<EK, 0>), grid, dim3(256), 0, s, a, b);
+    if (sums) hipLaunchKernelGGL((pair_scan_kernel<EK, true>), grid, dim3(256), 0, s, a, b);
+    else hipLaunchKernelGGL((pair_scan_kernel<EK, false>), grid, dim3(256), 0, s, a, b);
     return hipGetLastError();
 }
 
@@ -1231,8 +1225,7 @@ hipError_t launch_pair_scans(const OperandView &va, const OperandView &vb, bool 
         return hipErrorInvalidValue;
     const ScanSide a = scan_side_of(va, maxA, sigA, tauA, zeros);
     const ScanSide b = scan_side_of(vb, maxB, sigB, tauB, zeros);
-    return single ? pair_scans_ek<kElemC>(a, b, stats ? 2 : 0, s)
-                  : pair_scans_ek<kElemZ>(a, b, stats ? 2 : 0, s);
+    return single ? pair_scans_ek<kElemC>(a, b, stats, s) : pair_scans_ek<kElemZ>(a, b, stats, s);
 }
 
 // Parts of a row: one while a thread's share of it is at most 64 loads or both operands'
@@ -1418,11 +1411,11 @@ hipError_t launch_batch_scan(const BatchOperand *ops, int nops, int64_t blocks, 
     dim3 grid((unsigned)blocks);
 #define OZC_SCAN(EKV, PV) hipLaunchKernelGGL((batch_scan_kernel<EKV, PV>), grid, dim3(256), 0, s, ops, nops)
     if (single) {
-        if (stats) OZC_SCAN(kElemC, 2);
-        else OZC_SCAN(kElemC, 0);
+        if (stats) OZC_SCAN(kElemC, true);
+        else OZC_SCAN(kElemC, false);
     } else {
-        if (stats) OZC_SCAN(kElemZ, 2);
-        else OZC_SCAN(kElemZ, 0);
+        if (stats) OZC_SCAN(kElemZ, true);
+        else OZC_SCAN(kElemZ, false);
     }
 #undef OZC_SCAN
     return hipGetLastError();
