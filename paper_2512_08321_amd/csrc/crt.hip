@@ -8,7 +8,7 @@
 // of two doubles and reduces it in double-double arithmetic (Section II,
 // equation (5); Section IV-A); here S is accumulated exactly as 38-bit chunks
 // in FP64 (s_l split into 38-bit chunks, every partial sum an integer below
-// 24 * 2^38 * 2^7 < 2^53), and reduced mod P on the same chunks, which removes
+// kMaxPartSum * 2^38 * 2^7 < 2^52), and reduced mod P on the same chunks, which removes
 // the reconstruction error altogether and makes the output bit-reproducible
 // against an exact reference; C' is rounded once, by error-free sums of its chunks (the
 // double-double output and rare values: as a 256-bit integer).
@@ -20,8 +20,13 @@ namespace {
 using ConstTab = const OZC_AS_CONST NTable *;
 
 // The reduction works on the 38-bit chunks of S held in FP64: every value it
-// forms is an integer below 2^53, so every operation below is exact.
+// forms is an integer below 2^53, so every operation below is exact.  Bounds, with
+// E = kMaxPartSum = 96 terms s_l E'_l at most (one per modulus and part, |E'_l| <= 2^7):
+// |S| < 2^7 E P, |r_c| < 2^7 E 2^38 < 2^52 for a chunk of S, |q| <= 2^7 E + 1 < 2^14 for
+// the quotient, so |q P_c| < (2^7 E + 1) 2^38 and |r_c - q P_c| < (2^8 E + 1) 2^38 < 2^53.
 constexpr double kChunk = (double)(1ull << kChunkBits);   // 2^38
+static_assert(kMaxModuli <= kMaxPartSum, "one term per modulus at least");
+static_assert(((256ull * kMaxPartSum + 2) << kChunkBits) < (1ull << 53), "exact in FP64, a carry included");
 constexpr double kInvChunk = 1.0 / kChunk;                 // 2^-38, exact
 
 // Chunks 0 .. C-2 into [0, 2^38), the carries into the top chunk (which keeps the sign).
@@ -114,11 +119,11 @@ __device__ __forceinline__ bool rounding_residual(const uint64_t (&w)[4], double
 }
 
 // mod(S, P) rounded to nearest-even as d * 2^sh; S given as C unnormalised 38-bit
-// chunks in FP64 (|r_c| < 2^50).  With low (and shl) non-null, also the rounding
+// chunks in FP64 (|r_c| < 2^52).  With low (and shl) non-null, also the rounding
 // residual mod(S, P) - d 2^sh rounded to nearest-even as *low * 2^shl (0 when d is
 // exact), for double-double outputs.
 // The quotient q = rint(S / P) comes from the chunks' Horner sum times fl(1/P) (error
-// far below 2^-20, since |S| < 2^7 N P); R = S - q P chunk by chunk (|q P_c| < 2^50,
+// far below 2^-20, since |S| < 2^7 E P); R = S - q P chunk by chunk (|q P_c| < 2^52,
 // exact); a quotient within 2^-20 of a tie is checked exactly (settle_range).  |R| then
 // goes to a 256-bit integer for the rounding.
 template <int C>
@@ -128,7 +133,7 @@ __device__ __forceinline__ double reconstruct(double (&r)[C], ConstTab tab, int 
 #pragma unroll
     for (int c = C - 2; c >= 0; --c) sa = fma(sa, kChunk, r[c]);
     const double x = sa * tab->inv_P;  // ~ S / P
-    const double qd = rint(x);         // |q| <= 128 N + 1 < 2^12
+    const double qd = rint(x);         // |q| < 2^14
 #pragma unroll
     for (int c = 0; c < C; ++c) r[c] = fma(-qd, tab->Pchunk[c], r[c]);
     normalize<C>(r);
@@ -299,8 +304,8 @@ __device__ __forceinline__ void crt_output_body(const CrtArgs &a, int64_t bx) {
     if (j >= a.n || ib >= a.m) return;
 
     const int64_t planeC = a.n_pad * a.m_pad;
-    // S = sum_l s_l E'_l in 38-bit chunks: |partial sums| < kMaxPartSum 2^38 2^7 < 2^52
-    // (< 24 2^45 < 2^50 without parts), every fused multiply-add exact
+    // S = sum_l s_l E'_l in 38-bit chunks: |partial sums| < kMaxPartSum 2^38 2^7 < 2^52,
+    // every fused multiply-add exact
     double accR[4][C], accI[4][C];
 #pragma unroll
     for (int u = 0; u < 4; ++u)

@@ -7,7 +7,7 @@
 namespace ozc {
 
 constexpr int kMaxModuli = 24;
-constexpr int kChunkBits = 38;      // CRT in FP64 chunks: N * 128 * 2^38 < 2^53 for N <= 24
+constexpr int kChunkBits = 38;      // CRT in FP64 chunks: kMaxPartSum * 128 * 2^38 < 2^52
 constexpr int kMaxChunks = 5;       // ceil(bits(P) / 38) for N <= 24 (P below 2^185)
 constexpr int kMaxSplitWords = 4;  // residue split: a' as a biased integer of up to 4 32-bit
                                     // words, so |a'| < 2^127 (N <= 24 needs at most 97 bits)
