@@ -83,16 +83,17 @@ def model_line(m, n, k, N, args, copy_bw, achieved_tops, measured_ms):
 
 def phase_rates(m, n, k, N, single, algo, mode, prof):
     """Algorithmic HBM bytes of the memory-side phases over their measured times (TB/s):
-    the scans read both operands twice (fast mode; in accurate mode the scaling phase also
-    holds the bound product and is left out), the split reads each operand once and writes
-    its residue planes, the reconstruction reads the E' planes and writes C (beta = 0)."""
+    the scan reads both operands once (fast mode beyond k = 512; up to there scan and split
+    are one launch, timed as the split, and in accurate mode the scaling phase also holds
+    the bound product: left out), the split reads each operand once and writes its residue
+    planes, the reconstruction reads the E' planes and writes C (beta = 0)."""
     eb = 8 if single else 16
     planes = 3 if algo == "karatsuba" else 2
     calls = max(1, prof["calls"])
     out = {}
     byts = {"split": (m + n) * k * (eb + planes * N), "crt": m * n * (2 * N + eb)}
-    if mode == "fast":
-        byts["scale"] = 2 * (m + n) * k * eb
+    if mode == "fast" and k > 512:
+        byts["scale"] = (m + n) * k * eb
     for key, b in byts.items():
         t = prof[f"{key}_ms"] / calls
         out[key] = round(b / (t * 1e-3) / 1e12, 3) if t > 0 else None
