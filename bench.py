@@ -81,19 +81,25 @@ def model_line(m, n, k, N, args, copy_bw, achieved_tops, measured_ms):
                     "((14N + c) mn bytes); the product kernel here reduces in registers"}
 
 
-def phase_rates(m, n, k, N, single, algo, mode, prof):
+def scan_reads(k):
+    """Reads of the operands by the scaling scan's own launches: one beyond k = 512, none up
+    to there, where scan and split are one launch (timed as the split)."""
+    return 1 if k > 512 else 0
+
+
+def phase_rates(m, n, k, N, single, algo, mode, prof, reads=2):
     """Algorithmic HBM bytes of the memory-side phases over their measured times (TB/s):
-    the scan reads both operands once (fast mode beyond k = 512; up to there scan and split
-    are one launch, timed as the split, and in accurate mode the scaling phase also holds
-    the bound product: left out), the split reads each operand once and writes its residue
-    planes, the reconstruction reads the E' planes and writes C (beta = 0)."""
+    the scan reads both operands `reads` times (the library's count is scan_reads; 0: left
+    out, as in accurate mode, where the scaling phase also holds the bound product), the
+    split reads each operand once and writes its residue planes, the reconstruction reads
+    the E' planes and writes C (beta = 0)."""
     eb = 8 if single else 16
     planes = 3 if algo == "karatsuba" else 2
     calls = max(1, prof["calls"])
     out = {}
     byts = {"split": (m + n) * k * (eb + planes * N), "crt": m * n * (2 * N + eb)}
-    if mode == "fast" and k > 512:
-        byts["scale"] = (m + n) * k * eb
+    if mode == "fast" and reads:
+        byts["scale"] = reads * (m + n) * k * eb
     for key, b in byts.items():
         t = prof[f"{key}_ms"] / calls
         out[key] = round(b / (t * 1e-3) / 1e12, 3) if t > 0 else None
@@ -348,7 +354,7 @@ def main():
         "parity_sample": parity,
         "phase_ms": {key: round(prof[key] / max(1, prof["calls"]), 4)
                      for key in ("scale_ms", "split_ms", "gemm_ms", "crt_ms", "total_ms")},
-        "phase_hbm_TBps": phase_rates(m, n, k, N, args.single, args.algo, args.mode, prof),
+        "phase_hbm_TBps": phase_rates(m, n, k, N, args.single, args.algo, args.mode, prof, scan_reads(k)),
         "roofline": {"bound": "mfma", "kernel": "residue_gemm_kernel",
                      "achieved": round(achieved, 2), "peak": INT8_PEAK_TOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / INT8_PEAK_TOPS, 4),

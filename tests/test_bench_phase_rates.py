@@ -6,11 +6,11 @@ import pytest
 @pytest.mark.parametrize("k,mode,scale", [(16384, "fast", True), (513, "fast", True), (512, "fast", False),
                                           (16384, "accurate", False)])
 def test_phase_rates(k, mode, scale):
-    from bench import phase_rates
+    from bench import phase_rates, scan_reads
 
     m, n, N = 4096, 2048, 14
     prof = {"calls": 2, "scale_ms": 2.0, "split_ms": 4.0, "crt_ms": 6.0}
-    rates = phase_rates(m, n, k, N, False, "karatsuba", mode, prof)
+    rates = phase_rates(m, n, k, N, False, "karatsuba", mode, prof, scan_reads(k))
     operands = (m + n) * k * 16
     want = {"split": operands * (16 + 3 * N) / 16 / 2e-3, "crt": m * n * (2 * N + 16) / 3e-3}
     if scale:
