@@ -436,7 +436,7 @@ ozc_status_t run(ozc_context *h, int ek, ozc_op_t ta, ozc_op_t tb, int64_t m, in
     // outputs take whole ones
     const int galgo = real ? 2 : (h->algo == OZC_ALGO_KARATSUBA ? 0 : 1);
     KSplit ks{h->nmod, 1};
-    if (!ins && !h->dd_lo) ks = choose_k_split(L.tile, galgo, h->nmod, L.m_pad, L.n_pad, L.k_pad, h->cus);
+    if (!ins && !h->dd_lo) ks = choose_k_split(L.tile, galgo, h->nmod, m, n, L.k_pad, h->cus);
     char *ep_parts = nullptr;
     size_t extra = (size_t)(h->nmod - ks.l_split) * (ks.parts - 1) * L.eplanes * (size_t)L.m_pad * L.n_pad;
     st = ensure_workspace(h, L.total, extra, &ws, &ep_parts);

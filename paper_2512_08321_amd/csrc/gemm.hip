@@ -902,43 +902,84 @@ int gemm_kstep_for(int) { return BK; }
 int gemm_tile_rows(int tile) { return tile == 256 ? CfgLarge::TM : CfgSmall::TM; }
 int gemm_tile_cols(int tile) { return tile == 256 ? CfgLarge::TN : CfgSmall::TN; }
 
+// Whether a single call's products run on 64 x 64 tiles.  Where a call's 128 x 128 tiles leave
+// CUs idle, its time is one block's: the reductions of 64 x 64 outputs per wave (some 320 x 8
+// vector instructions, 4 us for complex products) behind a chain of slabs.  A quarter of that
+// on four times the CUs is shorter; once the CUs are full, the smaller tile's operand reads
+// (five LDS reads per four matrix instructions, against two per four) cost more than that.
+// Products in us, 128 x 128 against 64 x 64, blocks of the latter on 256 CUs:
+//   ZGEMM N = 14, 64 x 64 (14 blocks)   k = 64   8.5 -> 6.8,   k = 256  11.0 -> 8.2
+//   ZGEMM N = 14, 256 x 256 (224)       k = 64   9.0 -> 7.1,   k = 512  14.3 -> 10.8,  k = 1024 20.3 -> 15.2
+//   ZGEMM N = 14, 256 x 512 (448)       k = 64   9.8 -> 8.4,   k = 512  14.9 -> 12.4,  k = 1024 20.3 -> 16.4
+//   ZGEMM N = 14, 320 x 576 (630)       k = 64   11.0 -> 9.6,  k = 512  14.9 -> 14.1,  k = 1024 20.9 -> 20.7
+//   ZGEMM N = 14, 384 x 512 (672)       k = 64   10.4 -> 9.6,  k = 512  14.9 -> 14.2,  k = 1024 20.6 -> 21.0
+//   ZGEMM N = 14, 448 x 512 (784)       k = 64   11.3 -> 11.4, k = 512  15.0 -> 16.4,  k = 1024 20.9 -> 25.9
+//   ZGEMM N = 14, 320 x 576 (630)       k = 1088 21.3 -> 21.3, k = 2048 32.3 -> 33.2
+//   DGEMM N = 14, 256 x 512 (448)       k = 64   7.3 -> 6.8,   k = 1024 11.1 -> 9.8
+//   DGEMM N = 14, 320 x 576 (630)       k = 64   7.8 -> 7.3,   k = 1024 11.6 -> 11.0
+//   DGEMM N = 14, 448 x 512 (784)       k = 64   8.1 -> 8.3,   k = 1024 11.7 -> 12.7
+// Products that are cut along k keep 128 x 128 tiles (the cut's parts are sized for them).
+bool choose_64_tiles(int tile, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus) {
+    if (tile != 128 || m > (int64_t)64 * 1024 || n > (int64_t)64 * 1024) return false;
+    const int64_t blocks = (int64_t)nmod * ((m + 63) / 64) * ((n + 63) / 64);
+    return blocks <= cus || (2 * blocks <= 5 * (int64_t)cus && k_pad <= 1024);
+}
+
 // How a single call's products are cut along k.  A launch whose tiles leave CUs idle, or
 // whose last round of blocks is short, gains from more and shorter blocks; every part pays
-// an epilogue and E' planes of its own that the reconstruction reads too.  Times in us, one
-// slab (64 k) of one product of a tile and the rest of a block, from sweeps over k on one
-// part: 128 x 128 tiles 0.38 alone on a CU and 0.6 with a second block there, 256 x 256 tiles
-// 0.8; the rest 4 and 17 (one real product: 2 and 6).
-// 384 x 320 x 40000 at N = 14 (126 tiles): 4 parts; 2048^3 at N = 13 (832 tiles of 256 x 256 on
-// 256 CUs): the last modulus in 4 parts instead of a fourth round that is a quarter full.
-KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad, int64_t k_pad, int cus) {
+// an epilogue, and E' planes of its own that the reconstruction reads too.  The choice is
+// the least of these times in us, fitted to whole calls (1010 of 16 .. 4000 rows and columns and
+// k of 128 .. 60000, all four types, each timed whole and in every number of parts):
+//   one slab (64 k) of one product: 64 x 64 tiles 0.2; 128 x 128 tiles 0.26 alone on a CU, 0.43
+//   for two of them; 256 x 256 tiles 0.9; where the residues pass the Infinity Cache (300 MB) 0.28,
+//   0.34 and 0.5;
+//   the rest of a block: 3, 5 and 11.5 (one real product: 2, 3 and 5);
+//   a further entry of the reconstruction's sums: 0.165 (real 0.125), its share of a load's
+//   latency in a chain of loads four entries apart, or its bytes at 4.2 TB/s; and 0.5 for the call.
+// Over those calls the choice is 0.3% from the best of them (geometric mean; 1.9% with constants
+// from older kernels and no term for the entries' latency, which took 77 of them slower than whole,
+// by up to 25%; now 8, by up to 7%).  384 x 320 x 40000 at N = 14 (126 tiles): 4 parts, products
+// 685 -> 346 us; 2048^3 at N = 13 (832 tiles of 256 x 256 on 256 CUs): the last modulus in 3 parts instead
+// of a fourth round that is a quarter full, 345 -> 323 us.  Calls, whole against 8, 4 and 6 parts:
+// ZGEMM 47 x 110 x 791 at N = 11 30.4 and 40.7 us, 256 x 256 x 512 expanded at N = 14 29.6 and 37.4, DGEMM
+// 80 x 136 x 2022 at N = 14 31.3 and 37.3.
+KSplit choose_k_split(int tile, int algo, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus) {
     const bool real = algo == 2, small = tile == 128;
-    const int nseg = real ? 1 : (algo == 1 ? 4 : 3);
-    const double T = (double)(m_pad / tile) * (double)(n_pad / tile);
+    const int nseg = real ? 1 : (algo == 1 ? 4 : 3), nplanes = real ? 1 : (algo == 1 ? 2 : 3);
+    const int64_t TR = (m + tile - 1) / tile, TC = (n + tile - 1) / tile;
+    const double T = (double)TR * (double)TC;
     const int64_t slabs = k_pad / BK;
-    const double rest = small ? (real ? 2.0 : 4.0) : (real ? 6.0 : 17.0);
+    const bool far = (double)nmod * nplanes * (double)((TR + TC) * tile) * (double)k_pad > 3e8;
+    const double rest = small ? (real ? 3.0 : 5.0) : (real ? 5.0 : 11.5);
     const double slots = small ? 2.0 * cus : cus;
-    // a further E' plane written and read, and the reconstruction's longer chain of loads
-    const double plane_us = (real ? 1.0 : 2.0) * (double)m_pad * (double)n_pad * 2.0 / 4e6;
+    const double alone = small ? (far ? 0.34 : 0.26) : 0.9, full = small ? (far ? 0.5 : 0.43) : 0.9;
+    // a block of n slabs with this many on the chip, and a launch of them
     auto block_us = [&](int64_t n, double blocks) {
-        return nseg * (double)n * (small ? (blocks <= cus ? 0.38 : 0.6) : 0.8) + rest;
+        return nseg * (double)n * (blocks <= cus ? alone : full) + rest;
     };
-    auto rounds = [&](double blocks) { return std::ceil(blocks / slots); };
+    auto launch_us = [&](int64_t n, double blocks) {
+        const double rounds = std::floor(blocks / slots), more = blocks - rounds * slots;
+        return rounds * block_us(n, slots) + (more > 0.0 ? block_us(n, more) : 0.0);
+    };
     KSplit best{nmod, 1};
-    const double whole = rounds(nmod * T) * block_us(slabs, nmod * T);
-    double best_us = 0.93 * whole;
+    const double whole = choose_64_tiles(tile, nmod, m, n, k_pad, cus)
+                             ? nseg * (double)slabs * (far ? 0.28 : 0.2) + (real ? 2.0 : 3.0)
+                             : launch_us(slabs, nmod * T);
+    double best_us = 0.97 * whole;
     // what an even spread of the blocks over the slots would take, epilogues included: no
     // split does better
-    if (nmod * T >= slots && nmod * T / slots * block_us(slabs, nmod * T) + 4.0 >= best_us) return best;
-    if (whole <= 4.0 + 2.0 * rest) return best;  // too short for another epilogue
+    if (nmod * T >= slots && nmod * T / slots * block_us(slabs, nmod * T) + 0.5 >= best_us) return best;
+    const double entry_us = std::max(real ? 0.125 : 0.165, (real ? 1.0 : 2.0) * T * tile * tile / 4.2e6);
     for (int parts : {2, 3, 4, 6, 8}) {
         if (parts > slabs) break;
         for (int ls = 0; ls < nmod; ++ls) {
             if (ls + (nmod - ls) * parts > kMaxPartSum) continue;
             const double n1 = ls * T, n2 = (nmod - ls) * T * parts;
-            const double b1 = block_us(slabs, n1 + n2), b2 = block_us((slabs + parts - 1) / parts, n1 + n2);
-            double us = ls == 0 ? rounds(n2) * b2
-                                : std::max(rounds(n1) * b1, (n1 * b1 + n2 * b2) / slots + 0.5 * b2);
-            us += (nmod - ls) * (parts - 1) * plane_us + 4.0;
+            const int64_t part_slabs = (slabs + parts - 1) / parts;
+            const double b1 = block_us(slabs, n1 + n2), b2 = block_us(part_slabs, n1 + n2);
+            double us = ls == 0 ? launch_us(part_slabs, n2)
+                                : std::max(std::ceil(n1 / slots) * b1, (n1 * b1 + n2 * b2) / slots + 0.5 * b2);
+            us += (nmod - ls) * (parts - 1) * entry_us + 0.5;
             if (us < best_us) {
                 best_us = us;
                 best = KSplit{ls, parts};
@@ -946,27 +987,6 @@ KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad
         }
     }
     return best;
-}
-
-// Whether a single call's products run on 64 x 64 tiles.  Where a call's 128 x 128 tiles leave
-// CUs idle, its time is one block's: the reductions of 64 x 64 outputs per wave (some 320 x 8
-// vector instructions, 4 us for complex products) behind a chain of slabs.  A quarter of that
-// on four times the CUs is shorter; once the CUs are full, the smaller tile's operand reads
-// (five LDS reads per four matrix instructions, against two per four) cost more than that.
-// Products in us, 128 x 128 against 64 x 64, blocks of the latter on 256 CUs:
-//   ZGEMM N = 14, 64 x 64 (14 blocks)   k = 64   8.5 -> 6.8,  k = 256  11.0 -> 8.2
-//   ZGEMM N = 14, 256 x 256 (224)       k = 64   9.0 -> 7.2,  k = 512  14.4 -> 11.0
-//   DGEMM N = 14, 256 x 256 (224)       k = 64   7.5 -> 6.8,  k = 1000 10.8 -> 8.8
-//   ZGEMM N = 14, 256 x 512 (448)       k = 512  15.1 -> 12.6, k = 2048 22.8 -> 25.2
-//   CGEMM N = 8, 333 x 777 (624)        k = 64   10.4 -> 9.4, k = 1000 21.0 -> 20.8
-//   ZGEMM N = 14, 512 x 512 (896)       k = 64   12.1 -> 12.0, k = 512  15.6 -> 16.7
-//   DGEMM N = 14, 512 x 512 (896)       k = 64   8.2 -> 8.6,  k = 1000 12.0 -> 13.0
-// Products that are cut along k keep 128 x 128 tiles (as fast there, and the cut's parts are
-// sized for them).
-bool choose_64_tiles(int tile, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus) {
-    if (tile != 128 || m > (int64_t)64 * 1024 || n > (int64_t)64 * 1024) return false;
-    const int64_t blocks = (int64_t)nmod * ((m + 63) / 64) * ((n + 63) / 64);
-    return blocks <= cus || (2 * blocks <= 5 * (int64_t)cus && k_pad <= 1024);
 }
 
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s) {

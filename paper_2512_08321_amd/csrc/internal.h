@@ -168,7 +168,7 @@ constexpr int kMaxParts = 8;
 struct KSplit {
     int l_split, parts;
 };
-KSplit choose_k_split(int tile, int algo, int nmod, int64_t m_pad, int64_t n_pad, int64_t k_pad, int cus);
+KSplit choose_k_split(int tile, int algo, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus);
 bool choose_64_tiles(int tile, int nmod, int64_t m, int64_t n, int64_t k_pad, int cus);
 hipError_t launch_residue_gemm(const GemmArgs &a, hipStream_t s);
 // Output tile edge used for an m x n product (the padding of every buffer follows it).

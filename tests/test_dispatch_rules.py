@@ -24,12 +24,12 @@ def rules():
 
     def choose(t, m, n, k, N, algo):
         tile = 256 if m >= 1024 and n >= 1024 else 128
-        up = lambda x, a: (x + a - 1) // a * a
         form = 2 if t in "ds" else int(algo == "4m")
-        r = split(tile, form, N, up(m, tile), up(n, tile), up(k, 64), CUS)
+        k_pad = (k + 63) // 64 * 64
+        r = split(tile, form, N, m, n, k_pad, CUS)
         parts, first = r >> 32, r & 0xffffffff
-        cut = parts > 1 and first < N
-        return "parts" if cut else ("64" if t64(tile, N, m, n, up(k, 64), CUS) else "whole")
+        small = t64(tile, N, m, n, k_pad, CUS)
+        return "parts" if parts > 1 and first < N else ("64" if small else "whole"), small
 
     return choose
 
@@ -40,18 +40,23 @@ def _cases(test):
 
 def test_shapes_of_the_kernel_comparisons(rules):
     for t, m, n, k, N, algo in _cases(tiles_test) + [NEARLY_FULL]:
-        # one of the list is cut along k; NEARLY_FULL is its neighbour that is not
-        want = "parts" if (m, k, algo) == (256, 512, "4m") else "64"
-        assert rules(t, m, n, k, N, algo) == want, (t, m, n, k, N)
+        assert rules(t, m, n, k, N, algo)[0] == "64", (t, m, n, k, N)
     for t, m, n, k, N, _, algo in _cases(parts_test):
-        assert rules(t, m, n, k, N, algo) == "parts", (t, m, n, k, N)
+        assert rules(t, m, n, k, N, algo)[0] == "parts", (t, m, n, k, N)
 
 
 def test_where_64_tiles_end(rules):
     # 640 blocks of 64 x 64 (2.5 a CU) up to k = 1024, 256 beyond
-    assert rules("z", 640, 512, 1024, 8, "karatsuba") == "64"
-    assert rules("z", 641, 512, 1024, 8, "karatsuba") == "whole"
-    assert rules("z", 640, 512, 1025, 8, "karatsuba") == "whole"
-    assert rules("d", 256, 512, 1025, 8, "karatsuba") == "64"
-    assert rules("d", 257, 512, 1025, 8, "karatsuba") != "64"
-    assert rules("z", 2048, 2048, 64, 2, "karatsuba") != "64"
+    for shape, small in (((640, 512, 1024), True), ((641, 512, 1024), False), ((640, 512, 1025), False),
+                         ((256, 512, 1025), True), ((257, 512, 1025), False), ((2048, 2048, 64), False)):
+        assert rules("z", *shape, 8, "karatsuba")[1] == small, shape
+
+
+def test_short_parts_do_not_pay(rules):
+    """Calls of a few slabs that ran up to a third longer cut than whole."""
+    for case in (("z", 47, 110, 791, 11, "karatsuba"), ("z", 256, 256, 512, 14, "4m"), ("c", 366, 65, 326, 10, "4m"),
+                 ("d", 80, 136, 2022, 14, "karatsuba"), ("c", 179, 128, 1146, 16, "karatsuba")):
+        assert rules(*case)[0] != "parts", case
+    for case in (("z", 384, 320, 40000, 14, "karatsuba"), ("z", 21, 21, 24942, 13, "karatsuba"),
+                 ("c", 169, 96, 6215, 6, "4m"), ("z", 2048, 2048, 2048, 13, "karatsuba")):
+        assert rules(*case)[0] == "parts", case
