@@ -119,8 +119,8 @@ void *own_parts(ozc_context *h, size_t bytes) {
     });
 }
 
-// The call's workspace of `bytes`, and `extra` bytes more at *more where they can be had
-// without a change to the workspace (null where not).
+// The call's workspace of `bytes`, and `extra` bytes more at *more where they can be had (null
+// where not).  The workspace moves only for a call that it does not suffice for.
 ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t extra, char **ws, char **more) {
     *more = nullptr;
     if (h->use_fixed) {  // checked against the size before any work was enqueued
@@ -143,12 +143,19 @@ ozc_status_t ensure_workspace(ozc_context *h, size_t bytes, size_t extra, char *
             h->ws_own_bytes = 0;
             h->parts.release([](void *p) { (void)hipFree(p); });
         }
-        if (hipMalloc(&h->ws_own, bytes) != hipSuccess) {
+        // with the extra bytes, so that a new handle's first call allocates once
+        size_t size = bytes + extra;
+        hipError_t e = hipMalloc(&h->ws_own, size);
+        if (e != hipSuccess && extra) {
+            (void)hipGetLastError();
+            e = hipMalloc(&h->ws_own, size = bytes);
+        }
+        if (e != hipSuccess) {
             h->ws_own = nullptr;
             (void)hipGetLastError();
             return OZC_STATUS_ALLOC_FAILED;
         }
-        h->ws_own_bytes = bytes;
+        h->ws_own_bytes = size;
     }
     *ws = (char *)h->ws_own;
     if (extra)
