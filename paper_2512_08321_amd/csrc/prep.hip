@@ -421,8 +421,9 @@ __device__ __forceinline__ void scan_finish(const RowScan &a, int64_t r0, int pa
         exact[tid] = 0;
     }
     if (mine && !open && part == 0) a.mu[row] = (int16_t)mu;
-    const int rows = __syncthreads_count(open);
-    if (rows == 0) return;
+    if (!__syncthreads_or(open)) return;
+    int rows = 0;
+    for (int i = 0; i < kScanRows; ++i) rows += need[i] != 0;
     const int64_t h0 = part * a.chunk;
     exact_sums<EK>(a.v, r0, h0, min(a.v.k, h0 + a.chunk), need, rows, exact);
     __syncthreads();
