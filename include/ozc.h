@@ -103,14 +103,20 @@ ozc_status_t ozc_set_config(ozc_handle_t handle, int num_moduli, ozc_mode_t mode
                             ozc_algo_t algo);
 
 /* Device workspace in bytes that ozc_zgemm/ozc_cgemm need for this shape
- * under the current configuration (element size does not matter). */
+ * under the current configuration (element size does not matter).  Calls
+ * whose tiles leave compute units idle run faster with more (their products
+ * are cut along k, results unchanged): at most min(7 N, 96) * 2 m' n' bytes
+ * beyond it for N moduli, m' and n' rounded up to 128 (256 where m and n are
+ * at least 1024).  ozc_last_info reports what a call has used. */
 ozc_status_t ozc_workspace_size(ozc_handle_t handle, ozc_op_t transa, ozc_op_t transb,
                                 int64_t m, int64_t n, int64_t k, size_t *bytes);
 
 /* Use caller-owned device memory as workspace (ptr == NULL returns to the
  * handle's own growing workspace).  The caller keeps ownership and must keep
  * it alive while calls using it are in flight.  A later call whose shape
- * needs more than `bytes` fails with ALLOC_FAILED. */
+ * needs more than `bytes` fails with ALLOC_FAILED.  The handle's own
+ * workspace is reallocated only by a call that it does not suffice for, so
+ * a captured graph stays valid until then. */
 ozc_status_t ozc_set_workspace(ozc_handle_t handle, void *ptr, size_t bytes);
 
 /* C := alpha op(A) op(B) + beta C, complex128 (double2) elements.
